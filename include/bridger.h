@@ -329,14 +329,23 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
  * thresholds (9): per kernel tree, levels taken in pairs, one 16-byte block {w(m), w(2m),
  * w(2m + 1), f(m) | f(2m) << 10 | f(2m + 1) << 20} per node m of a pair's upper level, then
  * either one block {w(m), f(m), leaf value of 2m, of 2m + 1} per node of the last level or
- * the 2^D leaf values (absent with vector leaves or more than 1024 features), 10 the ragged
- * trees' two-level treelets (16 bytes a slot: a 4-ary heap per tree, slot s holding a node of
- * an even level and its two children, {w(n), v(c0), v(c1), f(n) | f(c0) << 10 | f(c1) << 20 |
- * leaf(c0) << 30 | leaf(c1) << 31}, v the child's threshold or leaf value; the grandchild of
- * steps b1, b2 in slot 4s + 1 + 2 b1 + b2; a leaf n as {0, v(n), v(n), 3 << 30}), 11 each
- * kernel tree's first slot (int32 [n_trees + 1]), 12 the leaf id of each slot's two children
- * (int32 pairs), 13 the treelets with ranks in place of thresholds (absent when the plan does
- * not use them).  *ptr stays valid until destroy or set_kernel.
+ * the 2^D leaf values (absent with vector leaves or more than 1024 features).  10 to 13, one-class
+ * ragged trees as two-level treelets, a view made at the call (absent when the plan does not use
+ * heaps): 10 the blocks (16 bytes a slot: a 4-ary heap per tree, slot s holding a node of an even
+ * level and its two children, {w(n), v(c0), v(c1), f(n) | f(c0) << 10 | f(c1) << 20 | leaf(c0) <<
+ * 30 | leaf(c1) << 31}, v the child's threshold or leaf value; the grandchild of steps b1, b2 in
+ * slot 4s + 1 + 2 b1 + b2; a leaf n as {0, v(n), v(n), 3 << 30}), 11 each kernel tree's first slot
+ * (int32 [n_trees + 1]), 12 the leaf id of each slot's two children (int32 pairs), 13 the blocks
+ * with ranks in place of thresholds.  14 to 18, the ragged trees' padded heaps that the kernel
+ * walks (absent when the plan does not use them): 14 the top levels (L = 5, 6 or 7: a complete
+ * 1-based heap of 2^L 8-byte records {threshold, f << 8} per tree, slot 0 {first block}; 4 zero
+ * heaps follow the last tree, 2 when L = 7), 15 below them a 4-byte leaf word per slot of level L
+ * (no tree deeper than L), or 16-byte blocks {w(n), v(c0), v(c1), fields}, level j holding 2^L 4^j
+ * slots, the grandchild of slot m by steps b1, b2 in slot 4m + 2 b1 + b2 of the next level, fields
+ * = f(n) << 8 | rotl(c0, 10) | rotl(c1, 21) with c = (f(c) | leaf(c) << 10) << 8; a leaf word is
+ * the value's bits or, with vector leaves, the leaf's place among the leaf records; 16 the leaf id
+ * of each leaf word, or of each block's two children, 17 and 18 as 14 and 15 for bins (ranks, and
+ * 7 in place of 8).  *ptr stays valid until destroy or set_kernel.
  */
 bridger_status bridger_forest_packed(bridger_forest_t h, int32_t which, const void **ptr,
                                      int64_t *bytes);

@@ -19,7 +19,8 @@ CALIB_LIB = os.path.join(PKG, "libbridger_calib.so")
 CALIB_SOURCES = [os.path.join(CSRC, "calib.hip")]
 SOURCES = [os.path.join(CSRC, n) for n in
            ("bridger_host.cpp", "perfect.hip", "perfect_binned.hip", "perfect_fixed.hip",
-            "perfect_global.hip", "ragged.hip", "direct.hip", "gemm.hip", "bin.hip",
+            "perfect_global.hip", "ragged.hip", "ragged_heap5.hip", "ragged_heap6.hip",
+            "ragged_heap7.hip", "direct.hip", "gemm.hip", "bin.hip",
             "normalize.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <mutex>
 #include <new>
 #include <string>
 #include <tuple>
@@ -143,12 +144,27 @@ struct bridger_forest {
   std::vector<uint8_t> perfect_deep, perfect_bdeep;
   int32_t deep_tl = 0;
   void *d_perfect_deep = nullptr, *d_perfect_bdeep = nullptr;
-  // RAGGED treelets (layout in internal.h): blocks (fp32 thresholds / ranks), per kernel tree
-  // the first slot, per slot the leaf ids of its two children (4 words, 4 words, 1, 2 per slot)
+  // RAGGED treelets, an inspection view made on request (bridger_forest_packed): blocks (fp32
+  // thresholds / ranks), per kernel tree the first slot, per slot the leaf ids of its two children
+  // (4 words, 4 words, 1, 2 per slot)
   std::vector<uint32_t> treelets, btreelets;
   std::vector<int32_t> treelet_start, treelet_leaf;
-  void *d_treelets = nullptr, *d_btreelets = nullptr, *d_treelet_start = nullptr,
-       *d_treelet_leaf = nullptr;
+  std::mutex view_mutex;  // guards the making of that view
+  // RAGGED heaps (layout in internal.h): fp32 thresholds, and ranks for bins
+  struct RaggedHeaps {
+    std::vector<uint64_t> tops;
+    std::vector<uint32_t> blocks;
+    void *d_tops = nullptr, *d_blocks = nullptr;
+  };
+  bool heap_ok = false, heap_bok = false;
+  int32_t heap_levels = 0;  // L
+  bool heap_flat = false;   // no tree deeper than L
+  int32_t heap_waves = 0;   // BRIDGER_WAVES at create
+  int32_t heap_span[5] = {};  // most classes a lane group's trees span, of 1, 2, 4, 8, 16 groups
+  RaggedHeaps heap, bheap;
+  std::vector<int32_t> heap_leaf;  // leaf ids: two per block, or one per leaf word (flat)
+  std::vector<float> vec_heap;     // vector leaves: class rows of the leaves, in record order
+  void *d_heap_leaf = nullptr, *d_vec_heap = nullptr;
   std::vector<uint64_t> ragged_brec;    // RAGGED records with ranks in place of thresholds
   std::vector<uint64_t> ragged_tops, ragged_btops;  // top-level heaps (fp32 / binned records)
   std::vector<int32_t> ragged_bchunk_first, ragged_bchunk_rec;
@@ -458,6 +474,16 @@ void build_vector_leaves(bridger_forest *h, const int64_t *offs, const int32_t *
     for (int32_t k = 0; k < h->n_trees; ++k)
       for (int32_t r = h->ragged_tree_start[k]; r < h->ragged_tree_start[k + 1]; ++r)
         put(h->vec_ragged, r, h->tree_order[k], h->ragged_rec_node[r]);
+    if (h->heap_ok) {  // the leaves' rows alone, in record order
+      size_t n = 0;
+      for (size_t r = 0; r < h->ragged_rec.size(); ++r)
+        n += ((h->ragged_rec[r] >> 32) & (uint32_t)kLeafFlag) && h->ragged_rec_node[r] >= 0;
+      h->vec_heap.assign(n * KS, 0.0f);
+      n = 0;
+      for (size_t r = 0; r < h->ragged_rec.size(); ++r)
+        if (((h->ragged_rec[r] >> 32) & (uint32_t)kLeafFlag) && h->ragged_rec_node[r] >= 0)
+          std::memcpy(&h->vec_heap[n++ * KS], &h->vec_ragged[r * KS], sizeof(float) * KS);
+    }
   }
   h->vec_direct.assign(h->direct_rec_node.size() * KS, 0.0f);
   for (int32_t k = 0; k < h->n_trees; ++k) {
@@ -762,6 +788,17 @@ int32_t ragged_chunks(const bridger_forest *h, int64_t chunk_bytes, std::vector<
   return (int32_t)first.size() - 1;
 }
 
+// Most bytes of the heaps made of the RAGGED records: they are sparse where trees are (a ragged
+// tree fills few of its deep slots), so at most 8x the packed records' bytes + 1 KB a tree (the
+// complete top levels of small trees) + 1 MB, and 512 MB, else the record walk serves.
+int64_t heap_bytes_limit(const bridger_forest *h) {
+  return std::min<int64_t>(8 * 8 * (int64_t)h->ragged_rec.size() + 1024 * (int64_t)h->n_trees + (1 << 20),
+                           int64_t(512) << 20);
+}
+
+// A threshold's bits with -0 as +0.
+uint32_t plus_zero(uint32_t w) { return w == 0x80000000u ? 0u : w; }
+
 // The chunked plan, or the global-node plan when the chunked one leaves fewer than eight
 // compute waves per CU (wide rows) and, for PERFECT, the forest fits in L2, or when a RAGGED
 // forest does not fit in L2.
@@ -971,91 +1008,75 @@ void build_sized_plans(bridger_forest *h, PlanInput pin, const Plan &big, bool b
   }
 }
 
-// RAGGED treelets (layout in internal.h) of every kernel tree, thresholds as bits or (binned)
-// their ranks; false when a tree needs more than 2^27 slots in all (32-bit byte offsets).
-bool make_treelets(const bridger_forest *h, const int64_t *offs, const int32_t *feat,
-                   const float *thr, const int32_t *left, const int32_t *right,
-                   const float *value, bool binned, std::vector<uint32_t> &blk,
-                   std::vector<int32_t> &start, std::vector<int32_t> *leaf_ids) {
+// One packed RAGGED record.
+struct RaggedRec {
+  uint32_t w, f, rel;  // threshold bits or rank / leaf value bits; feature; left child's offset
+  bool leaf;
+  explicit RaggedRec(uint64_t r)
+      : w((uint32_t)r), f((uint32_t)(r >> 48)), rel((uint32_t)(r >> 32) & (uint32_t)kMaxRel),
+        leaf(((r >> 32) & (uint32_t)kLeafFlag) != 0) {}
+};
+
+// Depth of every record below its root (breadth-first records: a parent precedes its children).
+std::vector<int32_t> record_depths(const bridger_forest *h) {
+  std::vector<int32_t> d(h->ragged_rec.size(), 0);
+  for (int32_t k = 0; k < h->n_trees; ++k)
+    for (int32_t r = h->ragged_tree_start[k]; r < h->ragged_tree_start[k + 1]; ++r) {
+      const RaggedRec n(h->ragged_rec[r]);
+      if (!n.leaf) d[r + n.rel] = d[r + n.rel + 1] = d[r] + 1;
+    }
+  return d;
+}
+
+// The treelet view (two-level blocks in a 4-ary heap per tree; see bridger_forest_packed) of the
+// packed records `rec`; false when the heaps would take more than 8x the records' bytes + 1 MB,
+// or 512 MB.
+bool make_treelets(const bridger_forest *h, const std::vector<uint64_t> &rec,
+                   std::vector<uint32_t> &blk, std::vector<int32_t> &start,
+                   std::vector<int32_t> *leaf_ids) {
+  const std::vector<int32_t> depth = record_depths(h);
   start.assign((size_t)h->n_trees + 1, 0);
   int64_t total = 0;
-  std::vector<std::pair<int32_t, int32_t>> stack;
   for (int32_t k = 0; k < h->n_trees; ++k) {
-    const int32_t t = h->tree_order[k];
-    const int64_t a = offs[t];
-    int32_t depth = 0;  // the tree's largest leaf depth
-    stack.assign(1, {0, 0});
-    while (!stack.empty()) {
-      const auto [nd, d] = stack.back();
-      stack.pop_back();
-      depth = std::max(depth, d);
-      if (left[a + nd] != -1) {
-        stack.push_back({left[a + nd], d + 1});
-        stack.push_back({right[a + nd], d + 1});
-      }
-    }
-    const int levels = depth / 2 + 1;  // treelet levels: nodes at tree levels 0, 2, ..., 2(levels-1)
+    const auto b = depth.begin() + h->ragged_tree_start[k], e = depth.begin() + h->ragged_tree_start[k + 1];
+    const int levels = *std::max_element(b, e) / 2 + 1;
     if (2 * levels > 26) return false;
     start[k] = (int32_t)total;
     total += ((int64_t(1) << (2 * levels)) - 1) / 3;
     if (total > (int64_t(1) << 27)) return false;
   }
-  // the heaps are sparse (a ragged tree fills few of its deep slots): at most 8x the packed
-  // records' bytes and 512 MB, else the record walk serves (1000 trees up to depth 12: 74 MB
-  // against 11.3 MB)
-  if (total * 16 > std::min<int64_t>(8 * 8 * (int64_t)h->ragged_rec.size() + (1 << 20),
-                                     int64_t(512) << 20))
-    return false;
+  if (total * 16 > heap_bytes_limit(h)) return false;
   start[h->n_trees] = (int32_t)total;
-  // an LDS copy reads up to 21 slots (treelet levels 0-2) from every tree's first slot, so the
-  // last tree is followed by that many zero slots
-  const int64_t pad = 21;
+  const int64_t pad = 21;  // zero slots after the last tree
   blk.assign((size_t)(total + pad) * 4, 0u);
   if (leaf_ids) leaf_ids->assign((size_t)(total + pad) * 2, -1);
-  auto w_of = [&](int64_t i) {
-    float th = thr[i];
-    if (th == 0.0f) th = 0.0f;
-    uint32_t w;
-    if (binned) w = rank_of(h, feat[i], th);
-    else std::memcpy(&w, &th, 4);
-    return w;
-  };
-  auto bits = [](float v) {
-    uint32_t w;
-    std::memcpy(&w, &v, 4);
-    return w;
-  };
-  std::vector<std::pair<int64_t, int32_t>> todo;  // (slot, node)
+  std::vector<std::pair<int64_t, int32_t>> todo;  // (slot, record)
   for (int32_t k = 0; k < h->n_trees; ++k) {
-    const int32_t t = h->tree_order[k];
-    const int64_t a = offs[t];
-    todo.assign(1, {0, 0});
+    todo.assign(1, {0, h->ragged_tree_start[k]});
     while (!todo.empty()) {
-      const auto [sl, nd] = todo.back();
+      const auto [sl, r] = todo.back();
       todo.pop_back();
       uint32_t *b = &blk[(size_t)(start[k] + sl) * 4];
       int32_t *lid = leaf_ids ? &(*leaf_ids)[(size_t)(start[k] + sl) * 2] : nullptr;
-      if (left[a + nd] == -1) {
-        b[0] = 0u;
-        b[1] = b[2] = bits(value[a + nd]);
+      const RaggedRec n(rec[r]);
+      if (n.leaf) {
+        b[1] = b[2] = n.w;
         b[3] = 3u << 30;
-        if (lid) lid[0] = lid[1] = nd;
+        if (lid) lid[0] = lid[1] = h->ragged_rec_node[r];
         continue;
       }
-      const int32_t c[2] = {left[a + nd], right[a + nd]};
-      b[0] = w_of(a + nd);
-      b[3] = (uint32_t)feat[a + nd];
+      b[0] = plus_zero(n.w);
+      b[3] = n.f;
       for (int j = 0; j < 2; ++j) {
-        const int64_t ci = a + c[j];
-        if (left[ci] == -1) {
-          b[1 + j] = bits(value[ci]);
-          b[3] |= 1u << (30 + j);
-          if (lid) lid[j] = c[j];
+        const int32_t c = r + (int32_t)n.rel + j;
+        const RaggedRec ch(rec[c]);
+        b[1 + j] = ch.leaf ? ch.w : plus_zero(ch.w);
+        b[3] |= ch.leaf ? 1u << (30 + j) : ch.f << (10 + 10 * j);
+        if (ch.leaf) {
+          if (lid) lid[j] = h->ragged_rec_node[c];
         } else {
-          b[1 + j] = w_of(ci);
-          b[3] |= (uint32_t)feat[ci] << (10 + 10 * j);
-          todo.push_back({4 * sl + 1 + 2 * j, left[ci]});
-          todo.push_back({4 * sl + 2 + 2 * j, right[ci]});
+          todo.push_back({4 * sl + 1 + 2 * j, c + (int32_t)ch.rel});
+          todo.push_back({4 * sl + 2 + 2 * j, c + (int32_t)ch.rel + 1});
         }
       }
     }
@@ -1063,8 +1084,160 @@ bool make_treelets(const bridger_forest *h, const int64_t *offs, const int32_t *
   return true;
 }
 
-bool treelets_wanted(const bridger_forest *h) {
-  return env_int("BRIDGER_TREELETS", 1) != 0 && !h->vec && h->F <= kDeepMaxFeatures;
+// Top levels of the RAGGED heaps.  Forests no deeper than 7: that depth (at least 5), with a leaf
+// word per slot below.  Deeper ones: the number that leaves the deepest leaves to be children of
+// a block's node rather than a block of their own (one load fewer for the lanes that get there).
+int heap_top_levels(int max_depth) {
+  if (max_depth <= 7) return std::max(max_depth, 5);
+  const int l = env_int("BRIDGER_HEAP_LEVELS", 0);
+  if (l >= 5 && l <= 7) return l;
+  return max_depth % 2 == 0 ? 5 : 6;
+}
+
+// RAGGED heaps (layout in internal.h) of the packed records `rec` (fp32 thresholds, or ranks when
+// `binned`); leaf_ids as the layout's leaf_map, when wanted.  False when they would take more
+// than heap_bytes_limit.
+bool make_ragged_heaps(const bridger_forest *h, const std::vector<uint64_t> &rec, bool binned,
+                       bridger_forest::RaggedHeaps &out, std::vector<int32_t> *leaf_ids) {
+  const int L = h->heap_levels;
+  const uint32_t s = binned ? 7 : 8;
+  const int64_t slots = int64_t(1) << L;
+  // vector leaves: a leaf's word is its row of class values, the leaf records in order
+  std::vector<int32_t> leaf_row;
+  if (h->vec) {
+    leaf_row.assign(rec.size(), -1);
+    int32_t n = 0;
+    for (size_t r = 0; r < rec.size(); ++r)
+      if (RaggedRec(rec[r]).leaf && h->ragged_rec_node[r] >= 0) leaf_row[r] = n++;
+  }
+  auto word = [&](int32_t r, const RaggedRec &n) { return h->vec ? (uint32_t)leaf_row[r] : n.w; };
+  std::vector<int64_t> first((size_t)h->n_trees + 1, 0);  // each tree's first block (or leaf word)
+  if (h->heap_flat) {
+    for (int32_t k = 0; k <= h->n_trees; ++k) first[k] = k * slots;
+  } else {
+    const std::vector<int32_t> depth = record_depths(h);
+    for (int32_t k = 0; k < h->n_trees; ++k) {
+      const int d = *std::max_element(depth.begin() + h->ragged_tree_start[k],
+                                      depth.begin() + h->ragged_tree_start[k + 1]);
+      const int levels = d <= L ? 1 : (d - L) / 2 + 1;
+      if (2 * levels > 26) return false;
+      first[k + 1] = first[k] + slots * (((int64_t(1) << (2 * levels)) - 1) / 3);
+      if (first[k + 1] > (int64_t(1) << 27)) return false;
+    }
+  }
+  const int64_t total = first[h->n_trees];
+  const int words = h->heap_flat ? 1 : 4;
+  if (total * 4 * words + h->n_trees * slots * 8 > heap_bytes_limit(h)) return false;
+  out.tops.assign((size_t)(h->n_trees + heap_batch(L)) * slots, 0);
+  out.blocks.assign((size_t)total * words, 0u);
+  if (leaf_ids) leaf_ids->assign((size_t)total * (h->heap_flat ? 1 : 2), -1);
+  std::vector<int32_t> at((size_t)2 * slots);             // heap slot -> record
+  std::vector<std::pair<int64_t, int32_t>> cur, next;     // (slot, record) of one block level
+  for (int32_t k = 0; k < h->n_trees; ++k) {
+    uint64_t *top = &out.tops[(size_t)k * slots];
+    top[0] = (uint64_t)(uint32_t)first[k];
+    at[1] = h->ragged_tree_start[k];
+    for (int64_t m = 1; m < slots; ++m) {
+      const RaggedRec n(rec[at[m]]);
+      if (!n.leaf) top[m] = (uint64_t)(binned ? n.w : plus_zero(n.w)) | (uint64_t)(n.f << s) << 32;
+      at[2 * m] = n.leaf ? at[m] : at[m] + (int32_t)n.rel;
+      at[2 * m + 1] = n.leaf ? at[m] : at[m] + (int32_t)n.rel + 1;
+    }
+    if (h->heap_flat) {
+      for (int64_t m = 0; m < slots; ++m) {
+        const int32_t r = at[slots + m];
+        out.blocks[first[k] + m] = word(r, RaggedRec(rec[r]));
+        if (leaf_ids) (*leaf_ids)[first[k] + m] = h->ragged_rec_node[r];
+      }
+      continue;
+    }
+    cur.clear();
+    for (int64_t m = slots; m < 2 * slots; ++m) cur.push_back({m, at[m]});
+    int64_t level0 = first[k], width = slots;  // first block and slot count of the level
+    while (!cur.empty()) {
+      next.clear();
+      for (const auto &[m, r] : cur) {
+        const int64_t i = level0 + m - width;
+        uint32_t *b = &out.blocks[(size_t)i * 4];
+        int32_t *lid = leaf_ids ? &(*leaf_ids)[(size_t)i * 2] : nullptr;
+        const RaggedRec n(rec[r]);
+        uint32_t c[2] = {1024u, 1024u};  // the children's fields {f, leaf << 10}
+        if (n.leaf) {
+          b[1] = b[2] = word(r, n);
+          if (lid) lid[0] = lid[1] = h->ragged_rec_node[r];
+        } else {
+          b[0] = binned ? n.w : plus_zero(n.w);
+          b[3] = n.f << s;
+          for (int j = 0; j < 2; ++j) {
+            const int32_t cr = r + (int32_t)n.rel + j;
+            const RaggedRec ch(rec[cr]);
+            b[1 + j] = ch.leaf ? word(cr, ch) : (binned ? ch.w : plus_zero(ch.w));
+            if (ch.leaf) {
+              if (lid) lid[j] = h->ragged_rec_node[cr];
+            } else {
+              c[j] = ch.f;
+              next.push_back({4 * m + 2 * j, cr + (int32_t)ch.rel});
+              next.push_back({4 * m + 2 * j + 1, cr + (int32_t)ch.rel + 1});
+            }
+          }
+        }
+        for (int j = 0; j < 2; ++j) {
+          const uint32_t rot = j ? 21 : 10, v = c[j] << s;
+          b[3] |= (v << rot) | (v >> (32 - rot));
+        }
+      }
+      level0 += width;
+      width *= 4;
+      cur.swap(next);
+    }
+  }
+  return true;
+}
+
+// The padded-heap kernel serves tiles of 64 rows, up to kDeepMaxFeatures features.  The tuning
+// overrides of the record walks (which serve the forests without heaps) keep those walks.
+bool heaps_wanted(const bridger_forest *h) {
+  return env_int("BRIDGER_TREELETS", 1) != 0 && env_int("BRIDGER_TOPS", 1) != 0 &&
+         env_int("BRIDGER_GLOBAL", -1) == -1 && env_int("BRIDGER_ILP", 0) == 0 &&
+         env_int("BRIDGER_ROWS", 0) == 0 && h->F <= kDeepMaxFeatures;
+}
+
+// Launch plan of the padded-heap kernel for n_rows rows (waves == 0: does not fit): W waves, one
+// lane group of the 64 rows each, that split the trees.  Takes the W that puts the most waves on
+// the chip: large batches fill it with any W that keeps 32 waves on a CU, small ones need W = 16
+// to use more than a wave per 64 rows (100 trees, 3,001 rows of 28 features: one 512-row tile per
+// workgroup took 66 us).
+Plan choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
+  Plan best{};
+  const int64_t n_wg = (std::max<int64_t>(n_rows, 1) + 63) / 64;
+  const int64_t tile = (int64_t)h->F * 64 * (binned ? 2 : 4);
+  int64_t most = 0;
+  for (int i = 0; i < 5; ++i) {
+    const int W = 1 << i;
+    if (h->heap_waves && W != h->heap_waves) continue;
+    if (W > h->n_trees) continue;
+    const int64_t sums = (int64_t)h->K * W * 64 * 8;
+    // sums kept in LDS during the walk, or written over the tile after it
+    const bool regs = h->vec ? h->K <= 8 : h->K == 1 || h->heap_span[i] <= kHeapClassRegs;
+    const int64_t walk = tile + (int64_t)W * heap_wave_bytes(h->heap_levels);
+    const int64_t lds = regs ? std::max(walk, sums) : walk + sums;
+    if (lds > kLdsBytesPerCU) continue;
+    const int m = (int)std::min<int64_t>(kLdsBytesPerCU / lds, kMaxWavesPerCU / W);
+    const int64_t active = std::min<int64_t>(n_wg, (int64_t)kNumCUs * m) * W;
+    if (active <= most) continue;
+    most = active;
+    best = Plan{};
+    best.waves = best.groups = W;
+    best.rows_per_wg = 64;
+    best.lds_bytes = (int32_t)lds;
+    best.acc_in_lds = 1;
+    best.acc_alias = regs ? 1 : 0;
+    best.global_nodes = 1;
+    best.tops = h->heap_levels;
+    best.ilp = heap_batch(h->heap_levels);
+    best.waves_per_cu = m * W;
+  }
+  return best;
 }
 
 // RAGGED records for bins: an internal record's threshold becomes its rank.
@@ -1151,8 +1324,8 @@ void free_all(bridger_forest *h) {
       free_dev(c.d_trav);
       free_dev(c.d_roots);
     }
-  for (void **q : {&h->d_treelets, &h->d_btreelets, &h->d_treelet_start, &h->d_treelet_leaf,
-                   &h->d_perfect_deep, &h->d_perfect_bdeep, &h->d_ragged_tops,
+  for (void **q : {&h->heap.d_tops, &h->heap.d_blocks, &h->bheap.d_tops, &h->bheap.d_blocks,
+                   &h->d_heap_leaf, &h->d_vec_heap, &h->d_perfect_deep, &h->d_perfect_bdeep, &h->d_ragged_tops,
                    &h->d_ragged_btops, &h->d_q_values, &h->d_q_off,
                    &h->d_perfect_btrav, &h->d_ragged_brec,
                    &h->d_ragged_bchunk_first, &h->d_ragged_bchunk_rec, &h->d_pre_a, &h->d_pre_b,
@@ -1192,12 +1365,13 @@ bridger_status upload_all(bridger_forest *h) {
     if ((s = upload(&h->d_ragged.chunk_first, h->ragged_chunk_first)) != BRIDGER_OK) return s;
     if ((s = upload(&h->d_ragged.chunk_rec, h->ragged_chunk_rec)) != BRIDGER_OK) return s;
     if ((s = upload(&h->d_ragged.leaf_map, h->ragged_rec_node)) != BRIDGER_OK) return s;
-    if (!h->ragged_tops.empty() && (s = upload(&h->d_ragged_tops, h->ragged_tops)) != BRIDGER_OK)
+    if (h->heap_ok) {
+      if ((s = upload(&h->heap.d_tops, h->heap.tops)) != BRIDGER_OK) return s;
+      if ((s = upload(&h->heap.d_blocks, h->heap.blocks)) != BRIDGER_OK) return s;
+      if ((s = upload(&h->d_heap_leaf, h->heap_leaf)) != BRIDGER_OK) return s;
+    } else if (!h->ragged_tops.empty() &&
+               (s = upload(&h->d_ragged_tops, h->ragged_tops)) != BRIDGER_OK) {
       return s;
-    if (!h->treelets.empty()) {
-      if ((s = upload(&h->d_treelets, h->treelets, 1024)) != BRIDGER_OK) return s;
-      if ((s = upload(&h->d_treelet_start, h->treelet_start)) != BRIDGER_OK) return s;
-      if ((s = upload(&h->d_treelet_leaf, h->treelet_leaf)) != BRIDGER_OK) return s;
     }
   }
   if (h->bin_bytes) {
@@ -1219,11 +1393,13 @@ bridger_status upload_all(bridger_forest *h) {
     if ((s = upload(&h->d_ragged_brec, h->ragged_brec, 1024)) != BRIDGER_OK) return s;
     if ((s = upload(&h->d_ragged_bchunk_first, h->ragged_bchunk_first)) != BRIDGER_OK) return s;
     if ((s = upload(&h->d_ragged_bchunk_rec, h->ragged_bchunk_rec)) != BRIDGER_OK) return s;
-    if (!h->ragged_btops.empty() &&
-        (s = upload(&h->d_ragged_btops, h->ragged_btops)) != BRIDGER_OK)
+    if (h->heap_bok) {
+      if ((s = upload(&h->bheap.d_tops, h->bheap.tops)) != BRIDGER_OK) return s;
+      if ((s = upload(&h->bheap.d_blocks, h->bheap.blocks)) != BRIDGER_OK) return s;
+    } else if (!h->ragged_btops.empty() &&
+               (s = upload(&h->d_ragged_btops, h->ragged_btops)) != BRIDGER_OK) {
       return s;
-    if (!h->btreelets.empty() && (s = upload(&h->d_btreelets, h->btreelets, 1024)) != BRIDGER_OK)
-      return s;
+    }
   }
   if ((s = upload(&h->d_direct.nodes, h->direct_rec)) != BRIDGER_OK) return s;
   if ((s = upload(&h->d_direct.tree_start, h->direct_root)) != BRIDGER_OK) return s;
@@ -1233,6 +1409,7 @@ bridger_status upload_all(bridger_forest *h) {
       return s;
     if (!h->vec_ragged.empty() && (s = upload(&h->d_vec_ragged, h->vec_ragged)) != BRIDGER_OK)
       return s;
+    if (!h->vec_heap.empty() && (s = upload(&h->d_vec_heap, h->vec_heap)) != BRIDGER_OK) return s;
     if ((s = upload(&h->d_vec_direct, h->vec_direct)) != BRIDGER_OK) return s;
   }
   return BRIDGER_OK;
@@ -1370,9 +1547,11 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   if (h->kernel_active == kPerfect || h->kernel_active == kRagged) {
     const bool perfect = h->kernel_active == kPerfect;
     const bridger_forest::SizedPlan *sp = perfect ? sized_plan(h, n_rows, binned) : nullptr;
-    const Plan &p = sp ? sp->plan
-                       : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
-                                 : (binned ? h->ragged_bplan : h->ragged_plan);
+    const bool heaps = !perfect && (binned ? h->heap_bok : h->heap_ok);
+    const Plan p = sp ? sp->plan
+                      : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
+                      : heaps   ? choose_heap_plan(h, n_rows, binned)
+                                : (binned ? h->ragged_bplan : h->ragged_plan);
     const DevArrays &d = perfect ? h->d_perfect : h->d_ragged;
     if (perfect)
       a.nodes = (const uint8_t *)(binned ? h->d_perfect_btrav : h->d_perfect_trav);
@@ -1439,16 +1618,22 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
       err = launch_perfect_fixed(h->perfect_depth, a, p.waves, n_wg, p.lds_bytes, stream);
     else if (h->kernel_active == kPerfect)
       err = launch_perfect(h->perfect_depth, a, p.waves, n_wg, p.lds_bytes, stream);
-    else if (p.global_nodes && p.tops && (binned ? h->d_btreelets : h->d_treelets)) {
-      a.nodes = (const uint8_t *)(binned ? h->d_btreelets : h->d_treelets);
-      a.nodes_bytes = (uint32_t)(4 * (binned ? h->btreelets.size() : h->treelets.size()));
-      a.tree_start = (const int32_t *)h->d_treelet_start;
-      a.leaf_map = (const int32_t *)h->d_treelet_leaf;
-      a.lds_top_off = h->F * p.rows_per_wg * xsz;
-      // treelet levels from the LDS copy: 3 (three trees a batch; 4M x 256 rows 14.15 ms,
-      // 1M x 28 rows 0.362 ms) or 2 (four trees: 14.22 and 0.374 ms)
-      a.top_levels = env_int("BRIDGER_TREELET_LDS_LEVELS", 3) == 2 ? 2 : 3;
-      err = launch_ragged_treelet(a, p.waves, n_wg, p.lds_bytes, stream);
+    else if (heaps) {
+      const auto &hp = binned ? h->bheap : h->heap;
+      a.nodes = (const uint8_t *)hp.d_blocks;
+      a.nodes_bytes = (uint32_t)(4 * hp.blocks.size());
+      a.tops = (const uint64_t *)hp.d_tops;
+      a.flat = h->heap_flat ? 1 : 0;
+      a.leaf_map = (const int32_t *)h->d_heap_leaf;
+      a.leaf_vec = (const float *)h->d_vec_heap;
+      a.lds_top_off = h->F * 64 * (binned ? 2 : 4);
+      // class sums over the tile after the walk, or behind the copies during it
+      a.acc_alias = p.acc_alias;
+      a.lds_acc_off =
+          p.acc_alias ? 0 : a.lds_top_off + p.waves * heap_wave_bytes(h->heap_levels);
+      err = (h->heap_levels == 5   ? launch_ragged_heap5
+             : h->heap_levels == 6 ? launch_ragged_heap6
+                                   : launch_ragged_heap7)(a, p.waves, n_wg, p.lds_bytes, stream);
     } else if (p.global_nodes && p.tops) {
       a.tops = (const uint64_t *)(binned ? h->d_ragged_btops : h->d_ragged_tops);
       a.nodes_bytes = (uint32_t)(8 * h->ragged_rec.size());
@@ -1698,10 +1883,14 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
       if (h->ragged_ok && h->ragged_plan.tops) {
         build_ragged_tops(h->ragged_rec, h->ragged_tree_start, h->n_trees, h->ragged_plan.tops,
                           h->ragged_tops);
-        if (treelets_wanted(h) &&
-            !make_treelets(h, tree_offsets, feature, threshold, left, right, value, false,
-                           h->treelets, h->treelet_start, &h->treelet_leaf))
-          h->treelets.clear();
+      }
+      if (h->ragged_ok && heaps_wanted(h)) {
+        h->heap_levels = heap_top_levels(h->max_depth);
+        h->heap_flat = h->max_depth <= h->heap_levels;
+        h->heap_waves = env_int("BRIDGER_WAVES", 0);
+        for (int i = 0; i < 5; ++i) h->heap_span[i] = class_span(h, 1 << i);
+        h->heap_ok = choose_heap_plan(h, pin.n_rows, false).waves > 0 &&
+                     make_ragged_heaps(h, h->ragged_rec, false, h->heap, &h->heap_leaf);
       }
     }
     // binned variants of the same layouts (used by bridger_forest_predict_binned)
@@ -1732,11 +1921,9 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
           if (h->ragged_bplan.tops) {
             build_ragged_tops(h->ragged_brec, h->ragged_tree_start, h->n_trees,
                               h->ragged_bplan.tops, h->ragged_btops);
-            if (!h->treelets.empty() &&
-                !make_treelets(h, tree_offsets, feature, threshold, left, right, value, true,
-                               h->btreelets, h->treelet_start, nullptr))
-              h->btreelets.clear();
           }
+          if (h->heap_ok && choose_heap_plan(h, pin.n_rows, true).waves > 0)
+            h->heap_bok = make_ragged_heaps(h, h->ragged_brec, true, h->bheap, nullptr);
           if (!h->ragged_bplan.global_nodes)
             h->ragged_bplan.n_chunks = ragged_chunks(h, h->ragged_bplan.chunk_bytes,
                                                      h->ragged_bchunk_first, h->ragged_bchunk_rec);
@@ -2037,7 +2224,7 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
     p = sp ? sp->plan : h->perfect_plan;
     forest_bytes = (double)h->perfect_blob.size();
   } else if (h->kernel_active == kRagged) {
-    p = h->ragged_plan;
+    p = h->heap_ok ? choose_heap_plan(h, n_rows, false) : h->ragged_plan;
     forest_bytes = 8.0 * h->ragged_rec.size();
   } else if (h->kernel_active == kGemm) {
     p.rows_per_wg = 64;
@@ -2096,14 +2283,34 @@ bridger_status bridger_forest_packed(bridger_forest_t h, int32_t which, const vo
       if (which == 1) return give(h->ragged_tree_start.data(), h->ragged_tree_start.size() * 4);
       if (which == 2) return give(h->ragged_rec_node.data(), h->ragged_rec_node.size() * 4);
       if (which == 4) return give(h->ragged_chunk_first.data(), h->ragged_chunk_first.size() * 4);
-      if (which == 10 && !h->treelets.empty())
-        return give(h->treelets.data(), h->treelets.size() * 4);
-      if (which == 11 && !h->treelet_start.empty())
-        return give(h->treelet_start.data(), h->treelet_start.size() * 4);
-      if (which == 12 && !h->treelet_leaf.empty())
-        return give(h->treelet_leaf.data(), h->treelet_leaf.size() * 4);
-      if (which == 13 && !h->btreelets.empty())
-        return give(h->btreelets.data(), h->btreelets.size() * 4);
+      if (which >= 10 && which <= 13 && h->heap_ok && !h->vec && h->K == 1) {
+        // the treelet view is made when it is first asked for
+        std::lock_guard<std::mutex> lock(h->view_mutex);
+        try {
+          if (h->treelets.empty() && !make_treelets(h, h->ragged_rec, h->treelets, h->treelet_start,
+                                                    &h->treelet_leaf))
+            h->treelets.clear();
+          if (which == 13 && h->heap_bok && h->btreelets.empty() &&
+              !make_treelets(h, h->ragged_brec, h->btreelets, h->treelet_start, nullptr))
+            h->btreelets.clear();
+        } catch (const std::bad_alloc &) {
+          return fail(BRIDGER_ERR_OUT_OF_MEMORY, "host allocation failed");
+        }
+        if (which == 10 && !h->treelets.empty())
+          return give(h->treelets.data(), h->treelets.size() * 4);
+        if (which == 11 && !h->treelets.empty())
+          return give(h->treelet_start.data(), h->treelet_start.size() * 4);
+        if (which == 12 && !h->treelets.empty())
+          return give(h->treelet_leaf.data(), h->treelet_leaf.size() * 4);
+        if (which == 13 && !h->btreelets.empty())
+          return give(h->btreelets.data(), h->btreelets.size() * 4);
+      }
+      if (h->heap_ok && which == 14) return give(h->heap.tops.data(), h->heap.tops.size() * 8);
+      if (h->heap_ok && which == 15) return give(h->heap.blocks.data(), h->heap.blocks.size() * 4);
+      if (h->heap_ok && which == 16) return give(h->heap_leaf.data(), h->heap_leaf.size() * 4);
+      if (h->heap_bok && which == 17) return give(h->bheap.tops.data(), h->bheap.tops.size() * 8);
+      if (h->heap_bok && which == 18)
+        return give(h->bheap.blocks.data(), h->bheap.blocks.size() * 4);
       if (which == 7 && !h->ragged_tops.empty())
         return give(h->ragged_tops.data(), h->ragged_tops.size() * 8);
       break;

@@ -83,18 +83,22 @@ constexpr bool perfect_fixed_ok(int D, int CT) {
 // node m of level D - 1, {w(m), f(m), leaf value of 2m, leaf value of 2m + 1}, else the 2^D
 // leaf values.  Every block of a level is indexed by m - 2^level.
 constexpr int kDeepMaxFeatures = 1024;
-// RAGGED treelets (the global-node ragged kernel): per kernel tree a 4-ary heap of 16-byte
-// blocks, slot s holding the node n at tree level 2l of treelet level l and its two children:
-// {w(n), v(c0), v(c1), f(n) | f(c0) << 10 | f(c1) << 20 | leaf(c0) << 30 | leaf(c1) << 31},
-// v(c) = w(c) for an internal child, its leaf value for a leaf; the grandchild reached by
-// steps b1 (at n) and b2 (at c_b1) sits in slot 4s + 1 + 2 b1 + b2.  A leaf n takes {0, v(n),
-// v(n), 3 << 30}; unreachable slots are zero.  Feature indices below kDeepMaxFeatures.  The
-// first kTreeletTopSlots slots (levels 0-3) of each tree of a batch are copied to the wave's
-// LDS, kTreeletCopyBytes per tree (or the first 21 slots, levels 0-5, 336 bytes per tree);
-// the last tree is followed by 21 zero slots.
-constexpr int kTreeletTopSlots = 5;
-constexpr int kTreeletCopyBytes = 128;
-constexpr int kTreeletBatch = kTopWaveBytes / kTreeletCopyBytes;
+// RAGGED heaps (the padded-heap kernel, tiles of 64 rows): the first L levels of every kernel tree
+// as a complete 1-based heap of 8-byte records {w, byte offset of the feature's row in the tile}
+// (2^L records; slot 0 holds the tree's first block, or first leaf word, in its low word), a leaf
+// above level L padded with {0, 0} records down to level L; heap_batch(L) zero heaps follow the
+// last tree.  Below them either (no tree deeper than L) one leaf word per slot of level L, or
+// 16-byte blocks: level j = 0, 1, .. of the blocks has 2^L 4^j slots, slot m (continuing the heap's
+// numbering) holding the node n at tree level L + 2j and its two children {w(n), v(c0), v(c1),
+// fields}, the grandchild of steps b1, b2 in slot 4m + 2 b1 + b2 of the next level.  v(c) is a
+// child's w, or a leaf child's leaf word: its value's bits, or (vector leaves) its row of the
+// class values.  A leaf n takes {0, v(n), v(n), both leaf flags}; slots below a leaf are zero and
+// never read.  fields, with s = log2 of the bytes of a feature's row of the tile (fp32: 8, bins:
+// 7): f(n) << s, and the 11 bits {f(c), leaf(c) << 10} of child c << s, rotated left by 10 (c0) or
+// 21 (c1) bits.  Feature indices below kDeepMaxFeatures.
+constexpr int heap_batch(int L) { return L == 7 ? 2 : 4; }  // trees a wave walks at once
+constexpr int heap_wave_bytes(int L) { return heap_batch(L) * (8 << L); }
+constexpr int kHeapClassRegs = 4;  // class sums of a lane group that the kernel keeps in registers
 constexpr int deep_pair_off(int TL, int i) {
   int o = 0;
   for (int j = 0; j < i; ++j) o += 16 << (TL + 2 * j);
@@ -187,6 +191,7 @@ struct LaunchArgs {
   int32_t deep_tree_bytes;     // their bytes per kernel tree (deep_tree_bytes(D, top_levels))
   int32_t top_group_bytes;     // PERFECT global: bytes of a lane group's top-level copy
   int32_t tile_coalesced;      // global-node RAGGED kernels: the row tile read 8 rows x 128 B a load
+  int32_t flat;                // RAGGED heaps: no tree deeper than the heaps, leaf words only
 };
 
 // Vector leaves: floats per leaf in leaf_vec, K rounded up to whole 16-byte groups.
@@ -210,8 +215,9 @@ int launch_ragged(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, v
 int launch_ragged_global(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes,
                          void *stream);
 int launch_ragged_top(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
-int launch_ragged_treelet(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes,
-                          void *stream);
+int launch_ragged_heap5(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
+int launch_ragged_heap6(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
+int launch_ragged_heap7(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
 int launch_direct(const LaunchArgs &a, int64_t n_wg, void *stream);
 int launch_gemm(int depth, const LaunchArgs &a, int64_t n_wg, void *stream);
 

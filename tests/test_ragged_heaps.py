@@ -1,0 +1,172 @@
+"""Ragged trees as padded heaps (packed arrays 14-18): a CPU interpreter of the layout against the
+oracle, and the kernel at the edges of its tiles, groups, batches and layouts."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2405_12491_amd as B
+from oracle import binning
+from parity_util import assert_scores
+from synth import (AGG_MEAN, AGG_SUM, XFORM_IDENTITY, XFORM_SIGMOID, XFORM_SOFTMAX, permute_nodes,
+                   random_tiny_forest, with_vector_leaves)
+
+GRID = [-1.0, -0.0, 0.0, 0.5, 1.0]
+VALUES = np.array([-1.0, -0.0, 0.0, 0.5, 1.0, 2.0, np.nan, np.inf, -np.inf], np.float32)
+
+
+def batch(levels):
+    return 2 if levels == 7 else 4
+
+
+def walk_heaps(f, X, bins=None):
+    """Leaf ids and leaf words of every (row, tree) by the kernel's walk of the layout."""
+    binned = bins is not None
+    top = B.bridger_forest_packed(f.handle, 17 if binned else 14, np.uint32).reshape(-1, 2)
+    blk = B.bridger_forest_packed(f.handle, 18 if binned else 15, np.uint32)
+    ids = B.bridger_forest_packed(f.handle, 16, np.int32)
+    order = B.bridger_forest_packed(f.handle, 3, np.int32)
+    T, n = f.n_trees, X.shape[0]
+    L = [l for l in (5, 6, 7) if top.shape[0] == (T + batch(l)) << l]
+    assert len(L) == 1
+    L = L[0]
+    top = top.reshape(-1, 1 << L, 2)
+    assert not top[T:].any()
+    flat = f.info()["max_depth"] <= L
+    s = 7 if binned else 8
+    V = bins if binned else X
+    rows = np.arange(n)
+
+    def right(w, x):
+        return (x > w.astype(np.int64)) if binned else ~(x <= w.view(np.float32))
+
+    leaves, words = np.empty((n, T), np.int32), np.empty((n, T), np.uint32)
+    for k in range(T):
+        first = int(top[k, 0, 0])
+        m = np.ones(n, np.int64)
+        for _ in range(L):
+            rec = top[k][m]
+            m = 2 * m + right(rec[:, 0].copy(), V[rows, rec[:, 1] >> s])
+        if flat:
+            i = first + m - (1 << L)
+            leaves[:, order[k]], words[:, order[k]] = ids[i], blk[i]
+            continue
+        b4 = blk.reshape(-1, 4)
+        level0, width = first, 1 << L
+        done = np.zeros(n, bool)
+        for _ in range(30):
+            i = np.where(done, first, level0 + m - width)
+            q = b4[i]
+            b1 = right(q[:, 0].copy(), V[rows, (q[:, 3] >> s) & 1023]).astype(np.int64)
+            rot = np.where(b1 == 1, 21, 10).astype(np.uint32)
+            m2 = (q[:, 3] >> rot) | (q[:, 3] << (32 - rot))
+            wc = np.where(b1 == 1, q[:, 2], q[:, 1]).astype(np.uint32)
+            fin = ~done & ((m2 >> s) & 1024 != 0)
+            leaves[fin, order[k]] = ids[2 * i[fin] + b1[fin]]
+            words[fin, order[k]] = wc[fin]
+            done |= fin
+            if done.all():
+                break
+            m = 4 * m + 2 * b1 + right(wc, V[rows, (m2 >> s) & 1023])
+            level0, width = level0 + width, 4 * width
+        assert done.all()
+    return leaves, words
+
+
+@pytest.mark.parametrize("depth", [0, 1, 4, 5, 6, 7, 8, 9, 10, 11])
+def test_heap_layout(depth):
+    """Forests of every layout (leaf words below 5, 6 or 7 levels; blocks below 5 or 6), with
+    leaves at every level, ties and non-finite inputs: the oracle's leaf ids and values."""
+    rng = np.random.default_rng(500 + depth)
+    F = int(rng.integers(1, 12))
+    model = permute_nodes(random_tiny_forest(rng, 17, F, max_depth=depth, p_split=0.85, thr_grid=GRID), rng)
+    X = rng.choice(VALUES, (96, F))
+    _, ref_lv, _ = oracle.predict(model, X, want_leaves=True)
+    ref_val = model.value[model.tree_offsets[:-1][None, :] + ref_lv].astype(np.float32)
+    with B.Forest(model, host_only=True) as f:
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
+        for bins in (None, binning.bin_rows(binning.tables(model), X)):
+            lv, words = walk_heaps(f, X, bins)
+            assert np.array_equal(lv, ref_lv)
+            assert np.array_equal(words.view(np.float32), ref_val)
+
+
+def test_heap_layout_vector_leaves():
+    """Vector leaves: a leaf's word is its place among the leaf records."""
+    rng = np.random.default_rng(7)
+    model = with_vector_leaves(random_tiny_forest(rng, 9, 5, max_depth=10, p_split=0.85), 3, rng)
+    X = rng.standard_normal((64, 5)).astype(np.float32)
+    with B.Forest(model, host_only=True) as f:
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
+        lv, words = walk_heaps(f, X)
+        rec = B.bridger_forest_packed(f.handle, 0, np.uint32).reshape(-1, 2)
+        node = B.bridger_forest_packed(f.handle, 2, np.int32)
+        start = B.bridger_forest_packed(f.handle, 1, np.int32)
+        leaf_rec = np.flatnonzero(((rec[:, 1] & 0x8000) != 0) & (node >= 0))
+        got = leaf_rec[words]
+        tree = np.searchsorted(start, got, side="right") - 1
+        assert np.array_equal(tree, np.broadcast_to(np.arange(9), tree.shape))
+        assert np.array_equal(node[got], lv)
+
+
+@pytest.mark.parametrize("n_rows,features,bytes_", [(1, 28, 4), (3001, 28, 4), (10**6, 28, 4), (10**6, 256, 4),
+                                                    (5000, 600, 4)])
+def test_heap_plan_fits(n_rows, features, bytes_):
+    """Every batch size gets a 64-row plan within a CU's LDS."""
+    rng = np.random.default_rng(3)
+    model = random_tiny_forest(rng, 40, features, max_depth=9)
+    with B.Forest(model, host_only=True) as f:
+        p = f.plan(n_rows)
+        assert p["rows_per_wg"] == 64 and 0 < p["lds_bytes"] <= 163840
+        waves = (p["lds_bytes"] - features * 64 * bytes_) // 2048  # 6 top levels: 2 KB a wave
+        assert waves in (1, 2, 4, 8, 16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("waves", [0, 1, 2, 8, 16])
+@pytest.mark.parametrize("depth", [3, 6, 7, 8, 9, 12])
+def test_heap_kernel(depth, waves, monkeypatch):
+    """Scores, labels, leaf ids, bins and CSR rows around the tile's edges, for every number of
+    lane groups, scalar leaves of 1, 3 and 13 classes and vector leaves of 2, 7 and 9."""
+    import dataclasses
+
+    import torch
+
+    from oracle import vector
+    if waves:
+        monkeypatch.setenv("BRIDGER_WAVES", str(waves))
+    rng = np.random.default_rng(900 + depth)
+    F = 7 if depth % 2 else 12
+    T = 17 if depth != 8 else 43
+    grid = GRID if depth != 9 else None
+    base = random_tiny_forest(rng, T, F, max_depth=depth, p_split=0.9, thr_grid=grid)
+    models = [dataclasses.replace(base, transform=XFORM_SIGMOID)]
+    for K in (3, 13):
+        models.append(dataclasses.replace(base, n_classes=K, aggregate=AGG_MEAN, transform=XFORM_SOFTMAX,
+                                          base_score=rng.standard_normal(K).astype(np.float32)))
+    models += [with_vector_leaves(base, 2, rng), with_vector_leaves(base, 7, rng),
+               with_vector_leaves(base, 9, rng, AGG_SUM, XFORM_IDENTITY)]
+    for model in models:
+        for n in (1, 63, 64, 65, 130):
+            X = rng.choice(VALUES[:7], (n, F)) if grid else rng.standard_normal((n, F)).astype(np.float32)
+            what = f"depth {depth} waves {waves} K {model.n_classes} rows {n}"
+            print(what, flush=True)
+            if model.value.ndim == 2:
+                ref, ref_lv = vector.predict(model, X)
+            else:
+                ref, ref_lv, _ = oracle.predict(model, X, want_leaves=True)
+            Xd = torch.from_numpy(X).cuda()
+            with B.Forest(model) as f:
+                f.kernel = B.BRIDGER_KERNEL_RAGGED
+                q = f.bin(Xd)
+                idx = np.tile(np.arange(F, dtype=np.int32), n)
+                csr = (torch.arange(0, n * F + 1, F).cuda(), torch.from_numpy(idx).cuda(), Xd.reshape(-1))
+                outs = [f.predict(Xd), f.predict_csr(*csr, n)]
+                lvs = [f.predict_leaves(Xd), f.predict_csr(*csr, n, leaves=True)]
+                if waves != 1:  # a record plan of one wave has no 128-row tile for 8-bit bins
+                    outs.append(f.predict_binned(q))
+                    lvs.append(f.predict_binned_leaves(q))
+                torch.cuda.synchronize()
+            for o in outs:
+                assert_scores(o.cpu().numpy(), ref, what)
+            for l in lvs:
+                assert np.array_equal(l.cpu().numpy(), ref_lv), what

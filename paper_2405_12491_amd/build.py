@@ -22,6 +22,9 @@ SOURCES = [os.path.join(CSRC, n) for n in
             "perfect_global.hip", "ragged.hip", "ragged_heap5.hip", "ragged_heap6.hip",
             "ragged_heap7.hip", "direct.hip", "gemm.hip", "bin.hip",
             "normalize.hip")]
+# Sources compiled once per value of a macro (one trees' depth each: their kernels are many), and
+# once without it; every other source once.
+UNITS = {"perfect_global.hip": ["BRIDGER_DEPTH=%d" % d for d in range(10, 0, -1)]}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 ARCH = ["--offload-arch=gfx950"]
@@ -33,9 +36,19 @@ FLAGS = ARCH + [
 ]
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", "-o", obj]
+def _units(srcs):
+    """(source, macro or None) of every object."""
+    parts = [(s, m) for s in srcs for m in UNITS.get(os.path.basename(s), [])]
+    return [(s, None) for s in srcs] + parts
+
+
+def _object(src: str, macro) -> str:
+    return os.path.join(BUILD_DIR, os.path.basename(src) + ("." + macro if macro else "") + ".o")
+
+
+def _compile(src: str, macro, verbose: bool) -> str:
+    obj = _object(src, macro)
+    cmd = [HIPCC, *FLAGS, *(["-D" + macro] if macro else []), "-c", "-o", obj]
     cmd += ["-x", "hip", src] if src.endswith(".cpp") else [src]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -62,12 +75,17 @@ def build(verbose: bool = False) -> str:
     """Build libbridger.so (the prediction library) and libbridger_calib.so (the calibration
     microbenchmarks used by the benchmark); returns the prediction library's path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    srcs = SOURCES + CALIB_SOURCES
-    jobs = max(1, min(len(srcs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
+    lib, calib = _units(SOURCES), _units(CALIB_SOURCES)
+    units = lib + calib
+    keep = {os.path.basename(_object(*u)) for u in units}
+    for name in os.listdir(BUILD_DIR):  # objects of sources that are no longer built
+        if name.endswith(".o") and name not in keep:
+            os.remove(os.path.join(BUILD_DIR, name))
+    jobs = max(1, min(len(units), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
     with ThreadPoolExecutor(jobs) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
-    _link(objs[:len(SOURCES)], LIB, verbose)
-    _link(objs[len(SOURCES):], CALIB_LIB, verbose)
+        list(ex.map(lambda u: _compile(*u, verbose), units))
+    _link([_object(*u) for u in lib], LIB, verbose)
+    _link([_object(*u) for u in calib], CALIB_LIB, verbose)
     return LIB
 
 

@@ -102,6 +102,8 @@ struct bridger_forest {
   std::vector<uint8_t> perfect_trav;  // traversal copy: {threshold, feature * 4R}
   std::vector<uint32_t> perfect_roots;  // per tree: the traversal copy's root record
   std::vector<int32_t> perfect_leaf_map;
+  bool leaf_bfs = false;       // leaf j of every tree is node 2^D - 1 + j
+  bool trees_in_order = false; // tree_order is the identity
   bool finite_thresholds = false;
   bool fixed_chunks = true;           // allow the compile-time chunk kernel variants
   Plan perfect_plan{};
@@ -323,6 +325,9 @@ void pack_perfect(bridger_forest *h, int D, const int64_t *offs, const int32_t *
       h->perfect_leaf_map[(size_t)k * n_leaf + j] = nd;
     }
   }
+  h->leaf_bfs = true;
+  for (size_t i = 0; i < h->perfect_leaf_map.size() && h->leaf_bfs; ++i)
+    h->leaf_bfs = h->perfect_leaf_map[i] == n_int + (int32_t)(i % (size_t)n_leaf);
 }
 
 // Records of the PERFECT kernel: the feature index becomes the byte offset of the feature's
@@ -1533,6 +1538,8 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   a.class_count = (const int32_t *)h->d_class_count;
   a.base = (const float *)h->d_base;
   a.tree_order = (const int32_t *)h->d_tree_order;
+  a.trees_in_order = h->trees_in_order ? 1 : 0;
+  a.leaf_bfs = h->leaf_bfs ? 1 : 0;
   a.n_trees = h->n_trees;
   a.K = h->K;
   a.aggregate = h->aggregate;
@@ -1587,7 +1594,10 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
     a.ilp = p.ilp;
     const int64_t n_wg = (n_rows + p.rows_per_wg - 1) / p.rows_per_wg;
     // (bins compare exactly whatever the thresholds; fp32 needs them finite)
-    const bool fixed = h->kernel_active == kPerfect && !out_leaf && h->K == 1 && !h->vec &&
+    // (leaf ids of any class count: no sums are kept)
+    const bool fixed = h->kernel_active == kPerfect &&
+                       (out_leaf ? h->perfect_tree_bytes == perfect_tree_bytes(h->perfect_depth)
+                                 : h->K == 1 && !h->vec) &&
                        p.groups == 1 && p.waves <= 8 && (binned || h->finite_thresholds) &&
                        p.ilp == 4 &&
                        perfect_fixed_ok(h->perfect_depth, p.trees_per_chunk) &&
@@ -1838,6 +1848,7 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
       std::vector<int32_t> fill(h->class_begin.begin(), h->class_begin.end() - 1);
       for (int32_t t = 0; t < n_trees; ++t) h->tree_order[fill[klass[t]]++] = t;
     }
+    h->trees_in_order = std::is_sorted(h->tree_order.begin(), h->tree_order.end());
     h->base.assign(n_classes, 0.0f);
     if (base_score)
       for (int32_t k = 0; k < n_classes; ++k) h->base[k] = base_score[k];

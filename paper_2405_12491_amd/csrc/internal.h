@@ -191,6 +191,8 @@ struct LaunchArgs {
   int32_t deep_tree_bytes;     // their bytes per kernel tree (deep_tree_bytes(D, top_levels))
   int32_t top_group_bytes;     // PERFECT global: bytes of a lane group's top-level copy
   int32_t tile_coalesced;      // global-node RAGGED kernels: the row tile read 8 rows x 128 B a load
+  int32_t trees_in_order;      // kernel tree order is the caller's
+  int32_t leaf_bfs;            // PERFECT: the caller numbers every tree's nodes breadth-first
   int32_t flat;                // RAGGED heaps: no tree deeper than the heaps, leaf words only
 };
 

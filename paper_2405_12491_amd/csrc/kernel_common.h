@@ -421,6 +421,42 @@ __device__ void groups_finalize_store(const LaunchArgs &a, double *z0, int R, in
   if (tid < R && row_ok) finalize_store(a, z0 + tid, stride, row);
 }
 
+// Leaf ids of kernel trees q .. q + N - 1 of one row.  Stored one by one, the lanes of a wave write
+// 64 lines for 4 bytes each; where the kernel's tree order is the caller's, 16 bytes of a row go
+// out per store (4-byte aligned: rows of any tree count).
+template <int N>
+__device__ __forceinline__ void store_leaf_ids(const LaunchArgs &a, int64_t row, int q,
+                                               const int32_t (&id)[N]) {
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  int32_t *o = a.out_leaf + row * (int64_t)a.n_trees;
+  if (a.trees_in_order) {
+#pragma unroll
+    for (int u = 0; u + 4 <= N; u += 4)
+      *reinterpret_cast<i32x4 *>(o + q + u) = i32x4{id[u], id[u + 1], id[u + 2], id[u + 3]};
+#pragma unroll
+    for (int u = N & ~3; u < N; ++u) o[q + u] = id[u];
+  } else {
+#pragma unroll
+    for (int u = 0; u < N; ++u) o[a.tree_order[q + u]] = id[u];
+  }
+}
+
+// The caller's id of the leaf at heap slot m of perfect kernel tree t of depth D.  In trees whose
+// nodes the caller numbers breadth-first (leaf_bfs) slot m is node m - 1: no table is read.
+template <int D>
+__device__ __forceinline__ int32_t perfect_leaf_id(const LaunchArgs &a, int t, uint32_t m) {
+  return a.leaf_bfs ? (int32_t)m - 1 : a.leaf_map[(int64_t)t * (1 << D) + (m - (1u << D))];
+}
+
+template <int D, int N>
+__device__ __forceinline__ void store_perfect_leaves(const LaunchArgs &a, int64_t row, int q,
+                                                     const uint32_t (&m)[N]) {
+  int32_t id[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) id[u] = perfect_leaf_id<D>(a, q + u, m[u]);
+  store_leaf_ids(a, row, q, id);
+}
+
 // Per-lane class bookkeeping for forests with several classes or several tree groups.
 struct ClassAcc {
   double acc;

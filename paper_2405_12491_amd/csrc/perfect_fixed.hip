@@ -8,7 +8,10 @@ namespace bridger {
 // loop is unrolled over the two buffers, so every tree's LDS base folds into the gathers'
 // offset field and a level's node address is a single shift.  A last chunk with fewer than CT
 // trees is walked with run-time bases.  XB: fp32 rows (4) or rows of 16- / 8-bit bins.
-template <int D, int CT, int XB = 4>
+// LEAVES: leaf ids instead of the score, any class count.  The ids of kIds = 16 trees stay in
+// registers and go out together, 64 consecutive bytes of a row: the stores of one wave touch 64
+// lines whatever they write, so they are made few and whole.
+template <int D, int CT, int XB = 4, bool LEAVES = false>
 __global__ __launch_bounds__(1024) void perfect_fixed_kernel(LaunchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int U = 4;
@@ -34,9 +37,15 @@ __global__ __launch_bounds__(1024) void perfect_fixed_kernel(LaunchArgs a) {
   load_tile_any<XB, true>(smem, a, tid, row, row_ok, 0, 1);
   __syncthreads();
 
-  double acc = a.aggregate == 0 ? (double)a.base[0] : 0.0;
-  auto chunk = [&](auto buf_tag, int c) {
-    constexpr uint32_t BUF = decltype(buf_tag)::value ? CB : 0u;
+  double acc = !LEAVES && a.aggregate == 0 ? (double)a.base[0] : 0.0;
+  constexpr int kIds = CT > 16 ? CT : 16;  // LEAVES: trees between stores
+  constexpr int NU = LEAVES ? (kIds / CT > 2 ? kIds / CT : 2) : 2;  // chunks per unrolled step
+  int32_t ids[LEAVES ? NU * CT : 1];
+  // chunk c in buffer POS mod 2; LEAVES: the ids to ids[POS * CT ..] (POS < NU), or stored at
+  // once (POS = NU, for the chunks after the last whole step)
+  auto chunk = [&](auto pos_tag, int c) {
+    constexpr int POS = decltype(pos_tag)::value;
+    constexpr uint32_t BUF = (POS & 1) ? CB : 0u;
     const int t0 = c * CT;
     if (t0 + CT <= T) {
       // the chunk's root records, wave-uniform: scalar loads through the constant address space
@@ -52,6 +61,16 @@ __global__ __launch_bounds__(1024) void perfect_fixed_kernel(LaunchArgs a) {
       for (int j = 0; j < CT / U; ++j) {
         uint32_t m[U];
         walk_trees_root<D, U, XB>(smem, BUF + (uint32_t)(j * U) * TB, TB, lane_off, root + j * U, m);
+        if constexpr (LEAVES) {
+          if constexpr (POS < NU) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              ids[POS * CT + j * U + u] = perfect_leaf_id<D>(a, t0 + j * U + u, m[u]);
+          } else if (row_ok) {
+            store_perfect_leaves<D>(a, row, t0 + j * U, m);
+          }
+          continue;
+        }
         float lv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -65,6 +84,10 @@ __global__ __launch_bounds__(1024) void perfect_fixed_kernel(LaunchArgs a) {
         const uint32_t b0 = BUF + (uint32_t)(q - t0) * TB;
         uint32_t m[U];
         walk_trees<D, U, true, XB>(smem, b0, TB, lane_off, m);
+        if constexpr (LEAVES) {
+          if (row_ok) store_perfect_leaves<D>(a, row, q, m);
+          continue;
+        }
         float lv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) lv[u] = lds_f32(smem, (m[u] << 2) + b0 + (uint32_t)u * TB + kLeafOff);
@@ -75,12 +98,41 @@ __global__ __launch_bounds__(1024) void perfect_fixed_kernel(LaunchArgs a) {
         const uint32_t b0 = BUF + (uint32_t)(q - t0) * TB;
         uint32_t m[1];
         walk_trees<D, 1, true, XB>(smem, b0, TB, lane_off, m);
+        if constexpr (LEAVES) {
+          if (row_ok) store_perfect_leaves<D>(a, row, q, m);
+          continue;
+        }
         acc += (double)lds_f32(smem, (m[0] << 2) + b0 + kLeafOff);
       }
     }
     __syncthreads();
   };
   int c = 0;
+  if constexpr (LEAVES) {
+    constexpr int NS = NU * CT / 16;  // stores of 16 trees per step
+    for (; (c + NU) * CT <= T; c += NU) {
+      chunk(std::integral_constant<int, 0>{}, c);
+      chunk(std::integral_constant<int, 1>{}, c + 1);
+      if constexpr (NU == 4) {
+        chunk(std::integral_constant<int, 2>{}, c + 2);
+        chunk(std::integral_constant<int, 3>{}, c + 3);
+      }
+      if (row_ok) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          int32_t id[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) id[u] = ids[16 * k + u];
+          store_leaf_ids(a, row, c * CT + 16 * k, id);
+        }
+      }
+    }
+    for (; c < n_chunks; c += 2) {  // (c is even)
+      chunk(std::integral_constant<int, NU>{}, c);
+      if (c + 1 < n_chunks) chunk(std::integral_constant<int, NU + 1>{}, c + 1);
+    }
+    return;
+  }
   for (; c + 2 <= n_chunks; c += 2) {
     chunk(std::integral_constant<int, 0>{}, c);
     chunk(std::integral_constant<int, 1>{}, c + 1);
@@ -99,6 +151,12 @@ static int launch_fixed_dc(const LaunchArgs &a, int waves, int64_t n_wg, int lds
                            void *stream) {
   if constexpr (perfect_fixed_ok(D, CT)) {
     const int threads = 64 * (waves + 1);
+    if (a.out_leaf && a.x_bytes == 2)
+      return launch_common(perfect_fixed_kernel<D, CT, 2, true>, threads, n_wg, lds_bytes, stream, a);
+    if (a.out_leaf && a.x_bytes == 1)
+      return launch_common(perfect_fixed_kernel<D, CT, 1, true>, threads, n_wg, lds_bytes, stream, a);
+    if (a.out_leaf)
+      return launch_common(perfect_fixed_kernel<D, CT, 4, true>, threads, n_wg, lds_bytes, stream, a);
     if (a.x_bytes == 2)
       return launch_common(perfect_fixed_kernel<D, CT, 2>, threads, n_wg, lds_bytes, stream, a);
     if (a.x_bytes == 1)

@@ -12,6 +12,12 @@
 
 namespace bridger {
 
+// The kernels of one depth, in a translation unit of their own (BRIDGER_DEPTH).
+template <int D>
+int launch_global_d(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
+
+#ifdef BRIDGER_DEPTH
+
 // Whether a row goes right at a node: the step bit of step_slot.
 template <bool FIN, int XB>
 __device__ __forceinline__ uint32_t go_right(uint32_t w, uint32_t x) {
@@ -132,14 +138,7 @@ __global__ __launch_bounds__(DEEP && U > 8 ? 512 : 1024) void perfect_global_ker
   auto finish = [&](auto &m, int q) {
     constexpr int N = sizeof(m) / sizeof(m[0]);
     if (LEAVES) {
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        if (row_ok) {
-          const int t = q + u;
-          a.out_leaf[row * (int64_t)T + a.tree_order[t]] =
-              a.leaf_map[(int64_t)t * (1 << D) + (m[u] - kFirstLeaf)];
-        }
-      }
+      if (row_ok) store_perfect_leaves<D>(a, row, q, m);
     } else if (VK) {
       int64_t leaf[N];
 #pragma unroll
@@ -277,11 +276,14 @@ __global__ __launch_bounds__(DEEP && U > 8 ? 512 : 1024) void perfect_global_ker
           lv[u] = *reinterpret_cast<const float *>(a.nodes + base[u] + kLeafOff + (m[u] << 2));
       }
       if (LEAVES) {
+        if (row_ok && q + U <= t_end) {
+          store_perfect_leaves<D>(a, row, q, m);
+        } else if (row_ok) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (row_ok && q + u < t_end)
-            a.out_leaf[row * (int64_t)T + a.tree_order[q + u]] =
-                a.leaf_map[(int64_t)(q + u) * (1 << D) + (m[u] - kFirstLeaf)];
+          for (int u = 0; u < U; ++u) {
+            const uint32_t m1[1] = {m[u]};
+            if (q + u < t_end) store_perfect_leaves<D>(a, row, q + u, m1);
+          }
         }
       } else {
 #pragma unroll
@@ -411,13 +413,17 @@ static int launch_global_dfx(const LaunchArgs &a, int waves, int64_t n_wg, int l
 }
 
 template <int D>
-static int launch_global_d(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes,
-                           void *stream) {
+int launch_global_d(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream) {
   if (a.x_bytes == 2) return launch_global_dfx<D, true, 2>(a, waves, n_wg, lds_bytes, stream);
   if (a.x_bytes == 1) return launch_global_dfx<D, true, 1>(a, waves, n_wg, lds_bytes, stream);
   return a.finite_thresholds ? launch_global_dfx<D, true, 4>(a, waves, n_wg, lds_bytes, stream)
                              : launch_global_dfx<D, false, 4>(a, waves, n_wg, lds_bytes, stream);
 }
+
+template int launch_global_d<BRIDGER_DEPTH>(const LaunchArgs &a, int waves, int64_t n_wg,
+                                            int lds_bytes, void *stream);
+
+#else
 
 int launch_perfect_global(int depth, const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes,
                           void *stream) {
@@ -435,5 +441,7 @@ int launch_perfect_global(int depth, const LaunchArgs &a, int waves, int64_t n_w
     default: return (int)hipErrorInvalidValue;
   }
 }
+
+#endif
 
 }  // namespace bridger

@@ -80,14 +80,7 @@ __global__ __launch_bounds__(1024) void perfect_kernel(LaunchArgs a) {
   auto finish = [&](auto &m, int q, uint32_t b0) {
     constexpr int N = sizeof(m) / sizeof(m[0]);
     if (LEAVES) {
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        if (row_ok) {
-          const int t = q + u;
-          a.out_leaf[row * (int64_t)T + a.tree_order[t]] =
-              a.leaf_map[(int64_t)t * (1 << D) + (m[u] - kFirstLeaf)];
-        }
-      }
+      if (row_ok) store_perfect_leaves<D>(a, row, q, m);
     } else if (VK == 2 || VK == 4) {
       // the leaf rows (16 bytes) follow the records in the staged tree blocks
       uint32_t addr[N];

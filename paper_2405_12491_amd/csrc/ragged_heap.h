@@ -203,9 +203,18 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
     // trees q .. q + nvalid - 1 in order
     if (LEAVES) {
       if (row_ok) {
+        int32_t id[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (u < nvalid) a.out_leaf[row * (int64_t)T + a.tree_order[q + u]] = a.leaf_map[oi[u]];
+        for (int u = 0; u < U; ++u) id[u] = a.leaf_map[oi[u]];
+        if (nvalid == U) {
+          store_leaf_ids(a, row, q, id);
+        } else {
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int32_t id1[1] = {id[u]};
+            if (u < nvalid) store_leaf_ids(a, row, q + u, id1);
+          }
+        }
       }
     } else if (VK != 0) {
       // 5..8 classes: one tree's row at a time (four in flight took 86 registers: 128 us against

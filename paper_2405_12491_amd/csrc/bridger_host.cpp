@@ -187,6 +187,12 @@ struct bridger_forest {
   std::vector<int32_t> direct_rec;  // 4 ints per record
   std::vector<int32_t> direct_root;
   std::vector<int32_t> direct_rec_node;
+  // its pair records (layout in internal.h), for the forests that the tile kernel serves
+  bool pair_ok = false;
+  std::vector<uint64_t> pair_rec;
+  std::vector<int32_t> pair_start, pair_node;  // per tree the first record; caller's node id
+  std::vector<float> vec_pair;                 // vector leaves: the leaves' class rows
+  void *d_vec_pair = nullptr;
 
   // device copies
   void *d_class_begin = nullptr, *d_class_count = nullptr, *d_base = nullptr,
@@ -442,6 +448,78 @@ void pack_direct(bridger_forest *h, const int64_t *offs, const int32_t *feat, co
   }
 }
 
+// Pair records of the DIRECT records; false when a tree or a feature index is too large for them.
+bool make_pair_records(bridger_forest *h) {
+  const int64_t n_all = (int64_t)h->direct_rec_node.size();
+  h->pair_rec.resize(n_all);
+  h->pair_node.resize(n_all);
+  h->pair_start = h->direct_root;
+  // of one tree, by breadth-first index: tree-local node; left child's index (-1: leaf; the right
+  // one is next); nodes of the subtree; position among the pair records
+  std::vector<int32_t> node, left, size, pos, roots, sub;
+  for (int32_t k = 0; k < h->n_trees; ++k) {
+    const int64_t a = h->direct_root[k];
+    const int32_t n = (int32_t)((k + 1 < h->n_trees ? h->direct_root[k + 1] : n_all) - a);
+    if (n >= (int32_t(1) << (32 - kPairRelShift))) return false;
+    const int32_t *rec = &h->direct_rec[(size_t)4 * a];
+    node.resize(n);
+    left.resize(n);
+    size.resize(n);
+    pos.resize(n);
+    node[0] = 0;
+    for (int32_t i = 0, end = 1; i < n; ++i) {
+      const int32_t *r = rec + 4 * (size_t)node[i];
+      left[i] = -1;
+      if (r[1] < 0) continue;
+      if (r[1] >= kDeepMaxFeatures) return false;
+      left[i] = end;
+      node[end++] = r[2] - (int32_t)a;
+      node[end++] = r[3] - (int32_t)a;
+    }
+    for (int32_t i = n - 1; i >= 0; --i)
+      size[i] = left[i] < 0 ? 1 : 1 + size[left[i]] + size[left[i] + 1];
+    // the large subtrees' nodes and their children first (their positions are set when the
+    // parent is met), then each small subtree below them
+    std::fill(pos.begin(), pos.end(), -1);
+    roots.clear();
+    int32_t next = 0;
+    pos[0] = next++;
+    for (int32_t i = 0; i < n; ++i) {
+      if (pos[i] < 0 || left[i] < 0) continue;
+      if (size[i] <= kPairCluster) {
+        roots.push_back(i);
+      } else {
+        pos[left[i]] = next++;
+        pos[left[i] + 1] = next++;
+      }
+    }
+    for (const int32_t root : roots) {
+      sub.assign(1, root);
+      for (size_t j = 0; j < sub.size(); ++j) {
+        const int32_t c = left[sub[j]];
+        if (c < 0) continue;
+        pos[c] = next++;
+        pos[c + 1] = next++;
+        sub.push_back(c);
+        sub.push_back(c + 1);
+      }
+    }
+    for (int32_t i = 0; i < n; ++i) {
+      const int32_t *r = rec + 4 * (size_t)node[i];
+      const uint32_t meta = left[i] < 0 ? kPairLeaf
+                                        : (uint32_t)r[1] | (uint32_t)(pos[left[i]] - pos[i]) << kPairRelShift;
+      h->pair_rec[a + pos[i]] = (uint64_t)(uint32_t)r[0] | (uint64_t)meta << 32;
+      h->pair_node[a + pos[i]] = h->direct_rec_node[a + node[i]];
+    }
+  }
+  if (h->vec) {  // a leaf's word is its row: the leaves in record order
+    uint32_t row = 0;
+    for (uint64_t &r : h->pair_rec)
+      if ((r >> 32) & kPairLeaf) r = (r >> 32 << 32) | row++;
+  }
+  return true;
+}
+
 // Vector leaves: the K class values of every leaf (rows of vec_stride(K) floats), numbered as
 // each kernel family finds its leaves (PERFECT: kernel tree x 2^D + leaf slot; RAGGED and
 // DIRECT: record index); zeros for internal and filler records and for the padding.
@@ -497,6 +575,14 @@ void build_vector_leaves(bridger_forest *h, const int64_t *offs, const int32_t *
     for (int64_t i = 0; i < n; ++i)
       put(h->vec_direct, h->direct_root[k] + i, t, h->direct_rec_node[h->direct_root[k] + i]);
   }
+  if (h->pair_ok)  // the leaves' rows alone, in record order
+    for (int32_t k = 0; k < h->n_trees; ++k)
+      for (int64_t r = h->direct_root[k],
+                   e = r + offs[h->tree_order[k] + 1] - offs[h->tree_order[k]]; r < e; ++r)
+        if ((h->pair_rec[r] >> 32) & kPairLeaf) {
+          const float *v = &h->vec_direct[(size_t)(h->direct_root[k] + h->pair_node[r]) * KS];
+          h->vec_pair.insert(h->vec_pair.end(), v, v + KS);
+        }
 }
 
 // -------------------------------------------------------------- Eq. 1 planner
@@ -1245,6 +1331,30 @@ Plan choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
   return best;
 }
 
+// Launch plan of the DIRECT tile kernel (waves == 0: does not fit): W waves that share 64 rows and
+// a batch of W * kDirectBatch trees; the W that puts the most waves on the chip.  A wave beyond
+// the trees of one batch would stay idle.
+Plan choose_direct_plan(const bridger_forest *h, int64_t n_rows) {
+  Plan best{};
+  const int64_t n_wg = (std::max<int64_t>(n_rows, 1) + 63) / 64;
+  int64_t most = 0;
+  for (int W : {1, 2, 4, 8, 16}) {
+    if (W > 1 && (W / 2) * kDirectBatch >= h->n_trees) continue;
+    const int64_t lds = (int64_t)h->F * 64 * 4 + (int64_t)2 * W * kDirectBatch * 64 * 4 + (int64_t)h->K * 64 * 8;
+    if (lds > kLdsBytesPerCU) continue;
+    const int m = (int)std::min<int64_t>(kLdsBytesPerCU / lds, kMaxWavesPerCU / W);
+    const int64_t active = std::min<int64_t>(n_wg, (int64_t)kNumCUs * m) * W;
+    if (active <= most) continue;
+    most = active;
+    best = Plan{};
+    best.waves = best.groups = W;
+    best.rows_per_wg = 64;
+    best.lds_bytes = (int32_t)lds;
+    best.waves_per_cu = m * W;
+  }
+  return best;
+}
+
 // RAGGED records for bins: an internal record's threshold becomes its rank.
 void build_ragged_brec(bridger_forest *h) {
   h->ragged_brec = h->ragged_rec;
@@ -1330,7 +1440,7 @@ void free_all(bridger_forest *h) {
       free_dev(c.d_roots);
     }
   for (void **q : {&h->heap.d_tops, &h->heap.d_blocks, &h->bheap.d_tops, &h->bheap.d_blocks,
-                   &h->d_heap_leaf, &h->d_vec_heap, &h->d_perfect_deep, &h->d_perfect_bdeep, &h->d_ragged_tops,
+                   &h->d_heap_leaf, &h->d_vec_heap, &h->d_vec_pair, &h->d_perfect_deep, &h->d_perfect_bdeep, &h->d_ragged_tops,
                    &h->d_ragged_btops, &h->d_q_values, &h->d_q_off,
                    &h->d_perfect_btrav, &h->d_ragged_brec,
                    &h->d_ragged_bchunk_first, &h->d_ragged_bchunk_rec, &h->d_pre_a, &h->d_pre_b,
@@ -1406,16 +1516,26 @@ bridger_status upload_all(bridger_forest *h) {
       return s;
     }
   }
-  if ((s = upload(&h->d_direct.nodes, h->direct_rec)) != BRIDGER_OK) return s;
-  if ((s = upload(&h->d_direct.tree_start, h->direct_root)) != BRIDGER_OK) return s;
-  if ((s = upload(&h->d_direct.leaf_map, h->direct_rec_node)) != BRIDGER_OK) return s;
+  if (h->pair_ok) {
+    if ((s = upload(&h->d_direct.nodes, h->pair_rec)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_direct.tree_start, h->pair_start)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_direct.leaf_map, h->pair_node)) != BRIDGER_OK) return s;
+  } else {
+    if ((s = upload(&h->d_direct.nodes, h->direct_rec)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_direct.tree_start, h->direct_root)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_direct.leaf_map, h->direct_rec_node)) != BRIDGER_OK) return s;
+  }
   if (h->vec) {
     if (!h->vec_perfect.empty() && (s = upload(&h->d_vec_perfect, h->vec_perfect)) != BRIDGER_OK)
       return s;
     if (!h->vec_ragged.empty() && (s = upload(&h->d_vec_ragged, h->vec_ragged)) != BRIDGER_OK)
       return s;
     if (!h->vec_heap.empty() && (s = upload(&h->d_vec_heap, h->vec_heap)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_vec_direct, h->vec_direct)) != BRIDGER_OK) return s;
+    if (h->pair_ok) {
+      if ((s = upload(&h->d_vec_pair, h->vec_pair)) != BRIDGER_OK) return s;
+    } else if ((s = upload(&h->d_vec_direct, h->vec_direct)) != BRIDGER_OK) {
+      return s;
+    }
   }
   return BRIDGER_OK;
 }
@@ -1665,9 +1785,17 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
     a.tree_start = (const int32_t *)h->d_direct.tree_start;
     a.leaf_map = (const int32_t *)h->d_direct.leaf_map;
     a.vec = h->vec ? 1 : 0;
-    a.leaf_vec = (const float *)h->d_vec_direct;
-    const int64_t n_wg = (n_rows + 255) / 256;
-    err = launch_direct(a, n_wg, stream);
+    a.leaf_vec = (const float *)(h->pair_ok ? h->d_vec_pair : h->d_vec_direct);
+    if (h->pair_ok) {
+      const Plan p = choose_direct_plan(h, n_rows);
+      a.rows_per_wg = 64;
+      a.groups = p.groups;
+      a.lds_top_off = h->F * 64 * 4;
+      a.lds_acc_off = a.lds_top_off + 2 * p.waves * kDirectBatch * 64 * 4;
+      err = launch_direct_tile(a, p.waves, (n_rows + 63) / 64, p.lds_bytes, stream);
+    } else {
+      err = launch_direct(a, (n_rows + 255) / 256, stream);
+    }
   }
   if (err != 0)
     return fail(BRIDGER_ERR_DEVICE, std::string("kernel launch failed: ") +
@@ -1941,6 +2069,11 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
         }
       }
     }
+    // the forests that only DIRECT can take (BRIDGER_DIRECT_TILE=1: any; 0: none)
+    const int pairs = env_int("BRIDGER_DIRECT_TILE", -1);
+    if ((pairs == 1 || (pairs != 0 && resolve_auto(h) == kDirect)) &&
+        choose_direct_plan(h, 1 << 20).waves > 0)
+      h->pair_ok = make_pair_records(h);
     if (vec) build_vector_leaves(h, tree_offsets, left, value_vec);
     if (env_int("BRIDGER_LOG", 0)) {
       auto show = [](const char *what, const Plan &p) {
@@ -2242,9 +2375,13 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
     p.waves = 4;
     forest_bytes = (double)h->perfect_blob.size();
   } else {
-    p.rows_per_wg = 256;
-    p.waves = 4;
-    forest_bytes = 16.0 * h->n_nodes;
+    if (h->pair_ok) {
+      p = choose_direct_plan(h, n_rows);
+    } else {
+      p.rows_per_wg = 256;
+      p.waves = 4;
+    }
+    forest_bytes = (h->pair_ok ? 8.0 : 16.0) * h->n_nodes;
   }
   const double n = (double)n_rows;
   const double n_wg = std::ceil(n / std::max(p.rows_per_wg, 1));

@@ -35,6 +35,12 @@
 //
 // DIRECT (any forest): 16-byte records {float w; int32 feature (-1 at a leaf); int32 left;
 //   int32 right} with absolute record indices; kernel tree t starts at record root[t].
+//   The tile kernel reads pair records instead (trees below 2^21 records, feature indices below
+//   kDeepMaxFeatures): 8 bytes {w, feature | leaf << 10 | left_rel << 11}, the left child left_rel
+//   records further on, the right one next to it; w is the threshold, or at a leaf its value or
+//   (vector leaves) its row of the class values.  A tree starts with its nodes of more than 32
+//   descendants' records and their children, breadth-first; then each subtree below those, whole
+//   and breadth-first.
 #pragma once
 #include <stdint.h>
 
@@ -109,6 +115,11 @@ constexpr int deep_tree_bytes(int D, int TL) {
 }
 constexpr int kMaxGemmDepth = 4;
 constexpr int kMaxGemmFeatures = 64;
+
+constexpr int kDirectBatch = 4;       // DIRECT tile kernel: trees a wave walks at once
+constexpr uint32_t kPairLeaf = 1024u;
+constexpr int kPairRelShift = 11;
+constexpr int kPairCluster = 32;      // records of a subtree kept together
 
 // Launch plan (host side), chosen by the data-movement model of Eq. 1.
 struct Plan {
@@ -220,6 +231,7 @@ int launch_ragged_top(const LaunchArgs &a, int waves, int64_t n_wg, int lds_byte
 int launch_ragged_heap5(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
 int launch_ragged_heap6(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
 int launch_ragged_heap7(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
+int launch_direct_tile(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
 int launch_direct(const LaunchArgs &a, int64_t n_wg, void *stream);
 int launch_gemm(int depth, const LaunchArgs &a, int64_t n_wg, void *stream);
 

@@ -4,319 +4,201 @@
 // (-0.0 and +0.0 are one threshold; a NaN feature gets the table's size, above every rank,
 // so it goes right at every split as the fp32 compare sends it).
 //
-// Two kernels; launch_bin (at the end) picks one by how many LDS loads of tables a group of 32
-// features needs.
+// A value is looked up in two steps (layout in internal.h: bin tables): a uniform grid over the
+// feature's thresholds, one cell per threshold, gives the number of thresholds in lower cells, and
+// a search over power-of-two steps counts those of its own cell, as many steps as the fullest cell
+// of the run of features needs (3 or 4 where thresholds are drawn from the data, against 10 to 12
+// for the whole table).  A cell is the truncated product fl(fl(x - lo) * scale), which never
+// decreases with x, so thresholds in lower cells are below x and those in higher ones are not.
 //
-// Row kernel: a workgroup owns 512 rows and one group of 32 features (one 128-byte line of an
-// fp32 row): every thread holds its row's 32 values of the group in registers, read once.  The
-// group's features are then taken in runs whose threshold tables fit the workgroup's LDS
-// buffer: stage the run's tables, then each thread binary-searches its values of the run's
-// features, four features at a time (four independent chains of LDS reads).  The bins stay in
-// registers until every run is done and are written once, whole (16-byte stores where the
-// layout allows).  X is read once and the bins written once whatever the tables' size; what
-// grows with the tables is the L2->LDS staging (the tables, a few MB at most, stay in L2).  A
-// single table larger than the buffer is searched in global memory instead.
+// What bounds it: the LDS gathers and the instructions around them, no longer the chain of a
+// whole binary search.  A thread keeps one column, four features where rows and bins are
+// aligned for it, so the features' parameters stay in registers, the loads and stores of a
+// wave are consecutive, and no index is divided.
+// Measured against the binary search over whole tables (32-feature groups, one element a lane):
+// 1M x 28 rows, 910 thresholds a feature, 135 -> 44 us; 100k x 784, 325: 343 -> 134 us; 4M x 256, 2,750
+// (16 runs of features, whose partial lines are what is left): 8.6 -> 4.0 ms.
 #include "kernel_common.h"
 
 namespace bridger {
 
-constexpr int kBinThreads = 512;  // rows per workgroup, one per thread; two workgroups a CU
-constexpr int kBinGroup = 32;     // features per workgroup
-constexpr int kBinIlp = 4;        // searches in flight per thread
+constexpr int kBinThreads = 1024;
 
-// Number of the n[j] ascending values at t[j] strictly below x[j] (x not NaN), for N tables at
-// once, by a binary search over power-of-two steps: lo only grows, by `step` when the step's
-// last element is below x.  The same trip count (floor(log2 max_n) + 1 steps) for every lane
-// searching the same tables.  LDS: t holds element offsets into the staged (padded) run; else
-// global element offsets into g.
-// In LDS the staged tables keep one unused float after every 32 (element e at e + e / 32): a
-// search's lanes sit at positions that differ by multiples of its step, and without the pad
-// every step of 32 or more would send all of them to one bank.
-__device__ __forceinline__ uint32_t padded(uint32_t e) { return e + (e >> 5); }
-
-template <int N, bool LDS>
-__device__ __forceinline__ void count_below(const float *g, const uint32_t (&t)[N],
-                                            const int (&n)[N], const float (&x)[N], int max_n,
-                                            int (&lo)[N]) {
-#pragma unroll
-  for (int j = 0; j < N; ++j) lo[j] = 0;
-  if (max_n <= 0) return;
-  for (int step = 1 << (31 - __builtin_clz((unsigned)max_n)); step > 0; step >>= 1) {
-    float v[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const int i = lo[j] + step - 1;
-      const uint32_t k = (uint32_t)(i < n[j] ? i : (n[j] > 0 ? n[j] - 1 : 0));
-      v[j] = LDS ? lds_f32(nullptr, 4u * padded(t[j] + k)) : g[t[j] + k];
-    }
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-      if (lo[j] + step <= n[j] && v[j] < x[j]) lo[j] += step;
-  }
-}
-
-template <int XB>
-__global__ __launch_bounds__(kBinThreads, 4) void bin_rows_kernel(LaunchArgs a) {  // 2 per CU
+// LDS: the run's part of the image is staged and searched there; else it is searched in place.
+template <int XB, int V, bool LDS>
+__global__ __launch_bounds__(kBinThreads) void bin_kernel(LaunchArgs a, BinTables bt,
+                                                          int64_t rows_per_block) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  // floats of tables the LDS buffer holds: padded, with up to 3 leading and 3 trailing slack
-  const int cap = (a.chunk_bytes / 4) * 32 / 33 - 8;
+  constexpr int kIlp = V == 4 ? 2 : 4;  // rows in flight per thread
   const int tid = threadIdx.x;
-  const int n_groups = a.groups;
-  const int grp = (int)(blockIdx.x % (uint32_t)n_groups);
-  // this block's rows: trees_per_chunk chunks of kBinThreads rows (the host's choice)
-  const int chunks = a.trees_per_chunk;
-  const int64_t rb = (int64_t)(blockIdx.x / (uint32_t)n_groups) * chunks * kBinThreads;
-  const int F = a.F;
-  const int f0 = grp * kBinGroup;
-  const int nf = F - f0 < kBinGroup ? F - f0 : kBinGroup;
-  const int f_end = f0 + nf;
-  int staged = -1, staged_end = -1;  // the run whose tables the buffer holds
-
-  for (int c = 0; c < chunks; ++c) {
-    const int64_t row = rb + (int64_t)c * kBinThreads + tid;
-    if (__builtin_amdgcn_readfirstlane((int)(rb + (int64_t)c * kBinThreads < a.n_rows)) == 0)
-      break;  // uniform: no row of this chunk exists
-    const bool row_ok = row < a.n_rows;
-
-    // the row's values of the group (zeros past the row's end or the last feature)
-    float x[kBinGroup];
-    const float *xr = a.X + (row_ok ? row : 0) * (int64_t)F + f0;
-    if (a.x_vec4 && nf == kBinGroup) {
-      const float4 *x4 = reinterpret_cast<const float4 *>(xr);
-#pragma unroll
-      for (int k = 0; k < kBinGroup / 4; ++k) {
-        const float4 v = row_ok ? x4[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-        x[4 * k] = v.x;
-        x[4 * k + 1] = v.y;
-        x[4 * k + 2] = v.z;
-        x[4 * k + 3] = v.w;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kBinGroup; ++j) x[j] = (row_ok && j < nf) ? xr[j] : 0.0f;
+  const BinRun run = bt.runs[blockIdx.x % (uint32_t)bt.n_runs];
+  const int64_t r0 = (int64_t)(blockIdx.x / (uint32_t)bt.n_runs) * rows_per_block;
+  const int64_t r1 = r0 + rows_per_block < a.n_rows ? r0 + rows_per_block : a.n_rows;
+  const bool staged = LDS && run.staged;
+  if (staged) {
+    const uint4 *src = reinterpret_cast<const uint4 *>(bt.image + run.word0);
+    for (int i = tid; i < (run.words >> 2); i += kBinThreads) {
+      const uint4 v = src[i];
+      *(__attribute__((address_space(3))) uint64_t *)(uintptr_t)(16 * i) = v.x | (uint64_t)v.y << 32;
+      *(__attribute__((address_space(3))) uint64_t *)(uintptr_t)(16 * i + 8) = v.z | (uint64_t)v.w << 32;
     }
-    if (a.pre_kind && row_ok) {
+    __syncthreads();
+  }
+  const int units = (run.f1 - run.f0 + V - 1) / V;   // columns of the run
+  const int rpi = (int)blockDim.x / units;           // rows per pass of the workgroup
+  const int rr = tid / units, f = run.f0 + (tid - rr * units) * V;
+  if (rr >= rpi) return;
+  float lo[V], scale[V], top[V];
+  uint32_t start[V], tab[V];  // byte offsets into the run's image
+  int n[V];
 #pragma unroll
-      for (int j = 0; j < kBinGroup; ++j)
-        if (j < nf) x[j] = preprocess(a, f0 + j, row, x[j]);
-    }
+  for (int v = 0; v < V; ++v) {
+    const BinFeature p = bt.features[f + v];
+    lo[v] = p.lo;
+    scale[v] = p.scale;
+    top[v] = p.top;
+    n[v] = p.n;
+    start[v] = 2u * (uint32_t)(p.start - 2 * run.word0);
+    tab[v] = 4u * (uint32_t)(p.tab - run.word0);
+  }
+  const int steps = __builtin_amdgcn_readfirstlane(run.steps);
+  const uint8_t *img = reinterpret_cast<const uint8_t *>(bt.image + run.word0);
 
-    uint32_t bin[kBinGroup];
+  auto rows = [&](auto lds_tag) {
+    constexpr bool IN_LDS = decltype(lds_tag)::value;
+    auto below = [&](uint32_t at, float x) {  // the table's element at byte `at`
+      return (IN_LDS ? lds_f32(smem, at) : *reinterpret_cast<const float *>(img + at)) < x;
+    };
+    for (int64_t row = r0 + rr; row < r1; row += (int64_t)rpi * kIlp) {
+      float x[kIlp][V];
 #pragma unroll
-    for (int j = 0; j < kBinGroup; ++j) bin[j] = 0;
-    int f = f0;
-    while (f < f_end) {  // runs of features whose tables fit the buffer (uniform control flow)
-      const int base = a.q_off[f];
-      int fe = f;
-      while (fe < f_end && a.q_off[fe + 1] - base <= cap) ++fe;
-      const bool in_lds = fe > f;
-      if (!in_lds) fe = f + 1;  // one table too large for the buffer: search it in place
-      // the run's tables, copied in 16-byte pieces from the aligned global offset abase <= base
-      // into the padded layout; a group with one run stages it once for all its chunks
-      const int abase = base & ~3;
-      if (in_lds && !(staged == base && staged_end == fe)) {
-        __syncthreads();  // the previous run's searches are done with the buffer
-        const int n4 = (a.q_off[fe] - abase + 3) >> 2;  // 16-byte pieces
-        const float4 *src4 = reinterpret_cast<const float4 *>(a.q_values + abase);
-        for (int i = tid; i < n4; i += kBinThreads) {
-          const float4 v = src4[i];
-          const uint32_t p = 4u * padded(4u * (uint32_t)i);  // four elements of one 32-row
-          *(__attribute__((address_space(3))) float *)(uintptr_t)(p) = v.x;
-          *(__attribute__((address_space(3))) float *)(uintptr_t)(p + 4) = v.y;
-          *(__attribute__((address_space(3))) float *)(uintptr_t)(p + 8) = v.z;
-          *(__attribute__((address_space(3))) float *)(uintptr_t)(p + 12) = v.w;
-        }
-        __syncthreads();
-        staged = base;
-        staged_end = fe;
-      }
-#pragma unroll
-      for (int j0 = 0; j0 < kBinGroup; j0 += kBinIlp) {
-        if (f0 + j0 + kBinIlp <= f || f0 + j0 >= fe) continue;  // no feature of the run here
-        uint32_t t[kBinIlp];
-        int n[kBinIlp], lo[kBinIlp];
-        float xv[kBinIlp];
-        int max_n = 0;
-#pragma unroll
-        for (int j = 0; j < kBinIlp; ++j) {
-          const int ff = f0 + j0 + j;
-          const bool in_run = ff >= f && ff < fe;
-          const int o = in_run ? a.q_off[ff] : base;
-          n[j] = in_run ? a.q_off[ff + 1] - o : 0;
-          // the table's element offset in the staged run (the buffer starts at LDS 0), or in
-          // the global array
-          t[j] = in_lds ? (uint32_t)(o - abase) : (uint32_t)o;
-          xv[j] = x[j0 + j];
-          max_n = n[j] > max_n ? n[j] : max_n;
-        }
-        if (in_lds) count_below<kBinIlp, true>(a.q_values, t, n, xv, max_n, lo);
-        else count_below<kBinIlp, false>(a.q_values, t, n, xv, max_n, lo);
-#pragma unroll
-        for (int j = 0; j < kBinIlp; ++j) {
-          const int ff = f0 + j0 + j;
-          if (ff >= f && ff < fe)
-            bin[j0 + j] = (xv[j] == xv[j]) ? (uint32_t)lo[j] : (uint32_t)n[j];
+      for (int i = 0; i < kIlp; ++i) {
+        const int64_t r = row + (int64_t)i * rpi;
+        const float *p = a.X + (r < r1 ? r : row) * (int64_t)a.F + f;
+        if constexpr (V == 4) {
+          const float4 q = *reinterpret_cast<const float4 *>(p);
+          x[i][0] = q.x;
+          x[i][1] = q.y;
+          x[i][2] = q.z;
+          x[i][3] = q.w;
+        } else {
+          x[i][0] = *p;
         }
       }
-      f = fe;
-    }
-
-    if (row_ok) {
-      uint8_t *q = reinterpret_cast<uint8_t *>(a.xq) + (row * (int64_t)F + f0) * XB;
-      constexpr int kBytes = kBinGroup * XB;  // one row's bins of the group
-      if (nf == kBinGroup && ((uintptr_t)q & 15) == 0) {
-        uint32_t w[kBytes / 4];
+      if (a.pre_kind) {
 #pragma unroll
-        for (int i = 0; i < kBytes / 4; ++i) {
-          if (XB == 2)
-            w[i] = bin[2 * i] | (bin[2 * i + 1] << 16);
-          else
-            w[i] = bin[4 * i] | (bin[4 * i + 1] << 8) | (bin[4 * i + 2] << 16) |
-                   (bin[4 * i + 3] << 24);
+        for (int i = 0; i < kIlp; ++i) {
+          const int64_t r = row + (int64_t)i * rpi;
+#pragma unroll
+          for (int v = 0; v < V; ++v) x[i][v] = preprocess(a, f + v, r < r1 ? r : row, x[i][v]);
         }
-        uint4 *q4 = reinterpret_cast<uint4 *>(q);
+      }
+      uint32_t at[kIlp][V];  // byte offset of the element the count stands at
 #pragma unroll
-        for (int i = 0; i < kBytes / 16; ++i)
-          q4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
-      } else {
+      for (int i = 0; i < kIlp; ++i)
 #pragma unroll
-        for (int j = 0; j < kBinGroup; ++j) {
-          if (j < nf) {
-            if (XB == 2) reinterpret_cast<uint16_t *>(q)[j] = (uint16_t)bin[j];
-            else q[j] = (uint8_t)bin[j];
+        for (int v = 0; v < V; ++v) {
+          const float c = fminf(fmaxf((x[i][v] - lo[v]) * scale[v], 0.0f), top[v]);
+          const uint32_t s = start[v] + 2u * (uint32_t)c;
+          at[i][v] = tab[v] + 4u * (IN_LDS ? lds_u16(smem, s)
+                                           : (uint32_t)*reinterpret_cast<const uint16_t *>(img + s));
+        }
+      // an element past the cell is not below x, and +inf elements follow the table: 8 of them
+      // for the last steps, one that the larger steps are clamped to
+      for (int st = steps; st >= 16; st >>= 1) {
+#pragma unroll
+        for (int i = 0; i < kIlp; ++i)
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const uint32_t e = min(at[i][v] + 4u * (uint32_t)(st - 1), tab[v] + 4u * (uint32_t)n[v]);
+            at[i][v] += below(e, x[i][v]) ? 4u * (uint32_t)st : 0u;
           }
-        }
+      }
+      auto step = [&](auto st_tag) {
+        constexpr uint32_t ST = decltype(st_tag)::value;
+#pragma unroll
+        for (int i = 0; i < kIlp; ++i)
+#pragma unroll
+          for (int v = 0; v < V; ++v)
+            at[i][v] += below(at[i][v] + 4u * (ST - 1), x[i][v]) ? 4u * ST : 0u;
+      };
+      if (steps >= 8) step(std::integral_constant<uint32_t, 8>{});
+      if (steps >= 4) step(std::integral_constant<uint32_t, 4>{});
+      if (steps >= 2) step(std::integral_constant<uint32_t, 2>{});
+      if (steps >= 1) step(std::integral_constant<uint32_t, 1>{});
+#pragma unroll
+      for (int i = 0; i < kIlp; ++i) {
+        const int64_t r = row + (int64_t)i * rpi;
+        if (r >= r1) break;
+        uint32_t b[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+          b[v] = x[i][v] == x[i][v] ? (at[i][v] - tab[v]) >> 2 : (uint32_t)n[v];
+        uint8_t *q = reinterpret_cast<uint8_t *>(a.xq) + (r * (int64_t)a.F + f) * XB;
+        if constexpr (V == 4 && XB == 2)
+          *reinterpret_cast<uint2 *>(q) = make_uint2(b[0] | b[1] << 16, b[2] | b[3] << 16);
+        else if constexpr (V == 4)
+          *reinterpret_cast<uint32_t *>(q) = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
+        else if constexpr (XB == 2)
+          *reinterpret_cast<uint16_t *>(q) = (uint16_t)b[0];
+        else
+          *q = (uint8_t)b[0];
       }
     }
-  }
+  };
+  if (staged) rows(std::true_type{});
+  else rows(std::false_type{});
 }
 
-static int launch_bin_rows(const LaunchArgs &a0, void *stream) {
-  LaunchArgs a = a0;
-  const int64_t groups = (a.F + kBinGroup - 1) / kBinGroup;
-  a.groups = (int32_t)groups;
-  if (a.chunk_bytes <= 0) a.chunk_bytes = 64 * 1024;  // two workgroups per CU
-  // chunks of kBinThreads rows per block: about two blocks per CU slot while that keeps a
-  // feature group's tables staged once for several chunks, at most 8
-  const int64_t n_chunks = (a.n_rows + kBinThreads - 1) / kBinThreads;
-  int64_t per = (n_chunks * groups) / 2048;
-  per = per < 1 ? 1 : (per > 8 ? 8 : per);
-  if (a0.trees_per_chunk > 0) per = a0.trees_per_chunk;  // tuning override
-  a.trees_per_chunk = (int32_t)per;
-  const int64_t blocks = (n_chunks + per - 1) / per * groups;
-  if (a.x_bytes == 2) return launch_common(bin_rows_kernel<2>, kBinThreads, blocks, a.chunk_bytes, stream, a);
-  if (a.x_bytes == 1) return launch_common(bin_rows_kernel<1>, kBinThreads, blocks, a.chunk_bytes, stream, a);
+template <int XB, int V>
+static int launch_bin_xv(const LaunchArgs &a, const BinTables &bt, bool lds, int threads,
+                         int64_t blocks, int64_t rows, void *stream) {
+  const auto k = lds ? bin_kernel<XB, V, true> : bin_kernel<XB, V, false>;
+  const int bytes = lds ? bt.lds_bytes : 0;
+  const int e = ensure_lds_limit((const void *)k, bytes);
+  if (e != 0) return e;
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), bytes, (hipStream_t)stream, a, bt,
+                     rows);
+  return (int)hipGetLastError();
+}
+
+int launch_bin(const LaunchArgs &a, const BinTables &bt, bool lds, void *stream) {
+  const uintptr_t q = (uintptr_t)a.xq;
+  const bool v4 = a.x_vec4 && q % (4 * (uintptr_t)a.x_bytes) == 0;
+  int threads = kBinThreads;
+  int64_t blocks, rows;
+  if (lds) {
+    // Whole rounds of resident workgroups: every workgroup has the same work, so a last round with
+    // few of them costs as much as a full one.  Few rounds, since each stages its tables.
+    const int64_t slots = (int64_t)256 * (bt.lds_bytes <= kLdsBytesPerCU / 2 ? 2 : 1);
+    int64_t per_run = 1;
+    double best = 0.0;
+    for (int k = 1; k <= 4; ++k) {
+      const int64_t p = std::max<int64_t>(1, k * slots / bt.n_runs), wg = p * bt.n_runs;
+      const double used = (double)wg / (double)((wg + slots - 1) / slots * slots);
+      if (used > best + 0.03) {
+        best = used;
+        per_run = p;
+      }
+    }
+    rows = std::max<int64_t>(64, (a.n_rows + per_run - 1) / per_run);
+  } else {
+    // tables in L2: a thread per column and four or two rows, in workgroups that a row fits
+    if (!v4 ? bt.max_features <= 256 : bt.max_features <= 1024) threads = 256;
+    const int64_t units = v4 ? (bt.max_features + 3) / 4 : bt.max_features;
+    const int64_t pass = threads / units * (v4 ? 2 : 4);
+    // at most 2^20 workgroups
+    const int64_t passes = (a.n_rows * bt.n_runs + pass * (int64_t(1) << 20) - 1) / (pass * (int64_t(1) << 20));
+    rows = pass * std::max<int64_t>(1, passes);
+  }
+  blocks = (a.n_rows + rows - 1) / rows * bt.n_runs;
+  if (a.x_bytes == 2)
+    return v4 ? launch_bin_xv<2, 4>(a, bt, lds, threads, blocks, rows, stream)
+              : launch_bin_xv<2, 1>(a, bt, lds, threads, blocks, rows, stream);
+  if (a.x_bytes == 1)
+    return v4 ? launch_bin_xv<1, 4>(a, bt, lds, threads, blocks, rows, stream)
+              : launch_bin_xv<1, 1>(a, bt, lds, threads, blocks, rows, stream);
   return (int)hipErrorInvalidValue;
-}
-
-// ====================================================== stream kernel
-// A workgroup owns a block of rows and one group of 32 features and walks the group's runs of
-// features whose tables fit its LDS buffer: stage the run's tables, then every (row, feature)
-// of the run binary-searches its feature's table, one element per lane at a time, writing its
-// bin at once.  The block re-reads its rows' 128-byte line once per run (from L2 while it
-// holds them), and the blocks of one group (one in every n_groups, dispatched round-robin
-// over the XCDs) share the group's tables in L2.  16 waves per workgroup: each lane's binary
-// search is a chain of dependent LDS reads, so the pass needs many waves in flight per CU (two
-// 64 KB workgroups fit a CU).
-constexpr int kBinStreamThreads = 1024;
-
-__device__ __forceinline__ int lower_bound_f32(const float *t, int n, float x) {
-  int lo = 0, len = n;
-  while (len > 0) {
-    const int half = len >> 1;
-    if (t[lo + half] < x) {
-      lo += half + 1;
-      len -= half + 1;
-    } else {
-      len = half;
-    }
-  }
-  return lo;
-}
-
-template <int XB>
-__global__ __launch_bounds__(kBinStreamThreads) void bin_stream_kernel(LaunchArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  const float *tab = reinterpret_cast<const float *>(smem);
-  const int cap = a.chunk_bytes / 4;  // floats the LDS buffer holds
-  const int tid = threadIdx.x;
-  // block = (row block, group of kBinGroup features); consecutive blocks take consecutive groups
-  const int n_groups = a.groups;
-  const int grp = (int)(blockIdx.x % (uint32_t)n_groups);
-  const int64_t r0 = (int64_t)(blockIdx.x / (uint32_t)n_groups) * a.rows_per_wg;
-  const int64_t r1 = (r0 + a.rows_per_wg < a.n_rows) ? r0 + a.rows_per_wg : a.n_rows;
-  const int F = a.F;
-  const int f_end = (grp + 1) * kBinGroup < F ? (grp + 1) * kBinGroup : F;
-  int f = grp * kBinGroup;
-  while (f < f_end) {
-    const int base = a.q_off[f];
-    int fe = f;
-    while (fe < f_end && a.q_off[fe + 1] - base <= cap) ++fe;
-    const bool in_lds = fe > f;
-    if (!in_lds) fe = f + 1;  // one table too large for the buffer: search it in place
-    const int nf = fe - f;
-    if (in_lds) {
-      __syncthreads();  // the previous run's searches are done with the buffer
-      const int n = a.q_off[fe] - base;
-      for (int i = tid; i < n; i += kBinStreamThreads) reinterpret_cast<float *>(smem)[i] = a.q_values[base + i];
-      __syncthreads();
-    }
-    // a block's rows x the run's features stays below 2^31 (launch_bin): 32-bit indices
-    const uint32_t total = (uint32_t)(r1 - r0) * (uint32_t)nf;
-    for (uint32_t i = tid; i < total; i += kBinStreamThreads) {
-      const uint32_t rq = i / (uint32_t)nf;
-      const int64_t row = r0 + rq;
-      const int ff = f + (int)(i - rq * (uint32_t)nf);
-      const int64_t e = row * F + ff;
-      const float x = a.pre_kind ? preprocess(a, ff, row, a.X[e]) : a.X[e];
-      const int o = a.q_off[ff] - base, cnt = a.q_off[ff + 1] - a.q_off[ff];
-      int b = cnt;
-      if (x == x) b = in_lds ? lower_bound_f32(tab + o, cnt, x)
-                             : lower_bound_f32(a.q_values + a.q_off[ff], cnt, x);
-      if (XB == 2) reinterpret_cast<uint16_t *>(a.xq)[e] = (uint16_t)b;
-      else reinterpret_cast<uint8_t *>(a.xq)[e] = (uint8_t)b;
-    }
-    f = fe;
-  }
-}
-
-static int launch_bin_stream(const LaunchArgs &a0, void *stream) {
-  LaunchArgs a = a0;
-  // About one block per resident workgroup (two per CU): each block restages its tables once
-  // per run of features, and longer blocks re-read lines that L2 no longer holds; at most
-  // 2,048 rows, 1,024 with several feature groups (measured: 1M x 28 rows 0.146 -> 0.138 ms
-  // against n / 1024 rows per block and no groups, 100k x 784 0.546 -> 0.33 ms, 4M x 256
-  // 13.0 -> 9.4 ms).
-  const int64_t groups = (a.F + kBinGroup - 1) / kBinGroup;
-  int64_t rows = (a.n_rows * groups + 511) / 512;
-  const int64_t max_rows = groups > 1 ? 1024 : 2048;
-  rows = rows < 64 ? 64 : (rows > max_rows ? max_rows : rows);
-  if (a0.rows_per_wg > 0) rows = a0.rows_per_wg;
-  // at most 2^21 blocks (2^31 work-items), and a run's (row, feature) pairs fit 32 bits
-  const int64_t min_rows = (a.n_rows * groups + (int64_t(1) << 21) - 1) >> 21;
-  rows = rows < min_rows ? min_rows : rows;
-  const int64_t cap = INT32_MAX / kBinGroup;
-  rows = rows > cap ? cap : rows;
-  a.rows_per_wg = (int32_t)rows;
-  a.groups = (int32_t)groups;
-  if (a.chunk_bytes <= 0) a.chunk_bytes = 64 * 1024;
-  const int64_t blocks = (a.n_rows + rows - 1) / rows * groups;
-  if (a.x_bytes == 2) return launch_common(bin_stream_kernel<2>, kBinStreamThreads, blocks, a.chunk_bytes, stream, a);
-  if (a.x_bytes == 1) return launch_common(bin_stream_kernel<1>, kBinStreamThreads, blocks, a.chunk_bytes, stream, a);
-  return (int)hipErrorInvalidValue;
-}
-
-// Runs of table staging per feature group decide the kernel: with one or two runs the stream
-// kernel (1,024 lanes, many searches in flight, a second read of the rows from L2) is the
-// faster (16-bit bins of 1M x 28 rows: 0.138 against 0.276 ms), and so it is with more runs
-// while the rows fit the last-level cache that serves its re-reads (1M x 28 rows, five runs:
-// 0.167 against 0.323 ms); with more runs over larger rows its re-reads of X go to memory (7.3x
-// the rows' bytes read and 4.0x the bins written for 4M x 256 rows with seven runs a group),
-// and the row kernel, which reads X and writes the bins once, is the faster (8.7 against
-// 9.5 ms).  The host passes a.n_chunks = the largest number of runs of any group when it
-// wants the row kernel, else 1.
-int launch_bin(const LaunchArgs &a, void *stream) {
-  return a.n_chunks > 2 ? launch_bin_rows(a, stream) : launch_bin_stream(a, stream);
 }
 
 }  // namespace bridger

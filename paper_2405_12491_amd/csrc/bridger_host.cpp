@@ -47,7 +47,9 @@ constexpr int kMaxWavesPerCU = 32;
 constexpr double kL2BytesPerXcd = 4.0 * 1024 * 1024;
 constexpr int kMinWavesPerCU = 8;
 constexpr int kNumCUs = 256;
-constexpr int64_t kLastLevelCacheBytes = int64_t(256) << 20;  // MI355X Infinity Cache
+// Values from which binning stages its tables (28 features of 910 thresholds: 140k values 8.5 us
+// staged, 7.6 in place; 560k values 8.9 against 14).
+constexpr int64_t kBinStagedValues = int64_t(1) << 18;
 // Latency terms for small batches, where a workgroup's walk over its share of the trees, not
 // the throughput of the LDS, sets the time: one dependent LDS gather (two per level, and the
 // leaf), and the barrier and L2 round trip of a chunk.  Fitted by least squares to batches
@@ -122,6 +124,13 @@ struct bridger_forest {
   int32_t bin_bytes = 0;                // 2 or 1; 0: some feature has 2^16 or more thresholds
   std::vector<float> q_values;
   std::vector<int32_t> q_off;           // [F + 1]
+  // bin tables (layout in internal.h): runs staged to LDS, and whole-row runs searched in place
+  std::vector<uint32_t> bin_image;
+  std::vector<BinFeature> bin_features;
+  std::vector<BinRun> bin_runs, bin_runs_in_place;
+  int32_t bin_lds_bytes = 0;
+  void *d_bin_image = nullptr, *d_bin_features = nullptr, *d_bin_runs = nullptr,
+       *d_bin_runs_in_place = nullptr;
   Plan perfect_bplan{}, ragged_bplan{};
   bool perfect_bok = false, ragged_bok = false;
   std::vector<uint8_t> perfect_btrav;   // PERFECT traversal copy for bins: {rank, f * R * bytes}
@@ -199,7 +208,7 @@ struct bridger_forest {
        *d_tree_order = nullptr;
   DevArrays d_perfect, d_ragged, d_direct;
   void *d_perfect_trav = nullptr, *d_perfect_roots = nullptr, *d_perfect_broots = nullptr;
-  void *d_q_values = nullptr, *d_q_off = nullptr, *d_perfect_btrav = nullptr,
+  void *d_perfect_btrav = nullptr,
        *d_ragged_brec = nullptr, *d_ragged_bchunk_first = nullptr, *d_ragged_tops = nullptr,
        *d_ragged_btops = nullptr,
        *d_ragged_bchunk_rec = nullptr;
@@ -958,6 +967,96 @@ bool build_quantization(bridger_forest *h, const int32_t *feat, const float *thr
   return h->bin_bytes != 0;
 }
 
+// Bin tables of the quantization (layout in internal.h).  A grid cell per threshold: more cells
+// make the fullest ones smaller but take LDS from the tables (6 bytes a threshold in all).
+void make_bin_tables(bridger_forest *h) {
+  const int32_t F = h->F;
+  std::vector<int32_t> fullest(F, 0), word0(F + 1, 0);  // fullest cell; first word of a feature
+  h->bin_features.assign(F, BinFeature{});
+  h->bin_image.clear();
+  h->bin_image.reserve(h->q_values.size() * 3 / 2 + (size_t)12 * F);
+  std::vector<uint32_t> count;
+  for (int32_t f = 0; f < F; ++f) {
+    while (f % 4 == 0 && h->bin_image.size() % 4) h->bin_image.push_back(0);
+    word0[f] = (int32_t)h->bin_image.size();
+    const float *v = h->q_values.data() + h->q_off[f];
+    const int32_t n = h->q_off[f + 1] - h->q_off[f], cells = std::max(n, 1);
+    const float *b = v, *e = v + n;  // the finite thresholds
+    while (b < e && std::isinf(*b)) ++b;
+    while (e > b && std::isinf(e[-1])) --e;
+    BinFeature &p = h->bin_features[f];
+    p.n = n;
+    p.top = (float)(cells - 1);
+    p.lo = b < e ? *b : 0.0f;
+    const float width = b < e ? e[-1] - *b : 0.0f;
+    p.scale = (float)cells / width;
+    if (!std::isfinite(p.scale)) p.scale = 0.0f;  // one value, or a range beyond fp32: one cell
+    p.tab = (int32_t)h->bin_image.size();
+    for (int32_t i = 0; i < n; ++i) {
+      uint32_t w;
+      std::memcpy(&w, &v[i], 4);
+      h->bin_image.push_back(w);
+    }
+    for (int i = 0; i < 8; ++i) h->bin_image.push_back(0x7f800000u);
+    p.start = 2 * (int32_t)h->bin_image.size();
+    count.assign(cells, 0);
+    for (int32_t i = 0; i < n; ++i) {
+      const float c = std::fmin(std::fmax((v[i] - p.lo) * p.scale, 0.0f), p.top);
+      fullest[f] = std::max<int32_t>(fullest[f], (int32_t)++count[(uint32_t)c]);
+    }
+    uint32_t lower = 0;
+    for (int32_t c = 0; c < cells; c += 2) {
+      const uint32_t first = lower;
+      lower += count[c];
+      const uint32_t second = lower;
+      if (c + 1 < cells) lower += count[c + 1];
+      h->bin_image.push_back(first | second << 16);
+    }
+  }
+  while (h->bin_image.size() % 4) h->bin_image.push_back(0);
+  word0[F] = (int32_t)h->bin_image.size();
+
+  auto run = [&](int32_t f0, int32_t f1, bool staged) {
+    BinRun r{f0, f1, word0[f0], word0[f1] - word0[f0], staged ? 1 : 0, 0};
+    const int32_t most = *std::max_element(fullest.begin() + f0, fullest.begin() + f1);
+    if (most > 0) r.steps = 1 << ilog2(most);
+    return r;
+  };
+  // staged runs: as few as fit a CU's LDS whole, or half of it where that takes no more of them
+  auto staged_runs = [&](int64_t cap, std::vector<BinRun> &runs) {
+    runs.clear();
+    int64_t most = 0;
+    for (int32_t f = 0; f < F;) {
+      int32_t fe = f;
+      while (fe < F && fe - f < 1024) {
+        const int32_t next = std::min(F, fe + 4);
+        if (4 * (int64_t)(word0[next] - word0[f]) > cap) break;
+        fe = next;
+      }
+      const bool fits = fe > f;
+      if (!fits) fe = std::min(F, f + 4);
+      runs.push_back(run(f, fe, fits));
+      if (fits) most = std::max(most, 4 * (int64_t)runs.back().words);
+      f = fe;
+    }
+    return most;
+  };
+  const int kb = env_int("BRIDGER_BIN_LDS_KB", 0);  // tuning override of the LDS taken
+  if (kb > 0) {
+    h->bin_lds_bytes = (int32_t)staged_runs(std::min<int64_t>((int64_t)kb * 1024, kLdsBytesPerCU), h->bin_runs);
+  } else {
+    h->bin_lds_bytes = (int32_t)staged_runs(kLdsBytesPerCU / 2, h->bin_runs);
+    std::vector<BinRun> whole;
+    const int64_t bytes = staged_runs(kLdsBytesPerCU, whole);
+    if (whole.size() < h->bin_runs.size()) {
+      h->bin_runs = whole;
+      h->bin_lds_bytes = (int32_t)bytes;
+    }
+  }
+  h->bin_runs_in_place.clear();
+  for (int32_t f = 0; f < F; f += 1024) h->bin_runs_in_place.push_back(run(f, std::min(F, f + 1024), false));
+}
+
 uint32_t rank_of(const bridger_forest *h, int32_t f, float t) {
   const float *b = h->q_values.data() + h->q_off[f];
   const float *e = h->q_values.data() + h->q_off[f + 1];
@@ -1441,7 +1540,8 @@ void free_all(bridger_forest *h) {
     }
   for (void **q : {&h->heap.d_tops, &h->heap.d_blocks, &h->bheap.d_tops, &h->bheap.d_blocks,
                    &h->d_heap_leaf, &h->d_vec_heap, &h->d_vec_pair, &h->d_perfect_deep, &h->d_perfect_bdeep, &h->d_ragged_tops,
-                   &h->d_ragged_btops, &h->d_q_values, &h->d_q_off,
+                   &h->d_ragged_btops, &h->d_bin_image, &h->d_bin_features,
+                   &h->d_bin_runs, &h->d_bin_runs_in_place,
                    &h->d_perfect_btrav, &h->d_ragged_brec,
                    &h->d_ragged_bchunk_first, &h->d_ragged_bchunk_rec, &h->d_pre_a, &h->d_pre_b,
                    &h->d_vec_perfect, &h->d_vec_ragged, &h->d_vec_direct})
@@ -1490,8 +1590,10 @@ bridger_status upload_all(bridger_forest *h) {
     }
   }
   if (h->bin_bytes) {
-    if ((s = upload(&h->d_q_values, h->q_values)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_q_off, h->q_off)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_bin_image, h->bin_image)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_bin_features, h->bin_features)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_bin_runs, h->bin_runs)) != BRIDGER_OK) return s;
+    if ((s = upload(&h->d_bin_runs_in_place, h->bin_runs_in_place)) != BRIDGER_OK) return s;
   }
   if (h->perfect_bok) {
     if ((s = upload(&h->d_perfect_btrav, h->perfect_btrav, 1024)) != BRIDGER_OK) return s;
@@ -2034,6 +2136,7 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
     }
     // binned variants of the same layouts (used by bridger_forest_predict_binned)
     if (build_quantization(h, feature, threshold, left)) {
+      make_bin_tables(h);
       if (h->perfect_ok) {
         PlanInput pin{1 << 20, n_features, n_classes, n_trees, (double)h->perfect_blob.size(),
                       h->perfect_tree_bytes, true, visits, h->bin_bytes};
@@ -2217,43 +2320,23 @@ bridger_status bridger_forest_bin(bridger_forest_t h, const float *X, int64_t n_
     a.n_rows = nr;
     a.F = h->F;
     a.x_bytes = h->bin_bytes;
-    a.q_values = (const float *)h->d_q_values;
-    a.q_off = (const int32_t *)h->d_q_off;
     a.xq = (uint8_t *)Xq + r0 * (int64_t)h->F * h->bin_bytes;
     a.x_vec4 = ((uintptr_t)a.X % 16 == 0) && (h->F % 4 == 0);
-    a.rows_per_wg = env_int("BRIDGER_BIN_ROWS", 0);  // tuning overrides: stream kernel's rows
-    a.trees_per_chunk = env_int("BRIDGER_BIN_CHUNKS", 0);  // and row kernel's 512-row chunks
-    {  // tuning override of the LDS table buffer
-      const int kb = env_int("BRIDGER_BIN_LDS_KB", 0);
-      if (kb > 0) a.chunk_bytes = (int32_t)std::min<int64_t>((int64_t)kb * 1024, kLdsBytesPerCU);
-    }
-    // the largest number of LDS loads of tables (runs of whole tables within 64 KB, or the
-    // override) any group of 32 features needs; it picks the binning kernel
-    {
-      const int cap = (a.chunk_bytes > 0 ? a.chunk_bytes : 65536) / 4;
-      int max_runs = 0;
-      for (int f0 = 0; f0 < h->F; f0 += 32) {
-        const int f1 = std::min(h->F, f0 + 32);
-        int runs = 0;
-        for (int f = f0; f < f1;) {
-          int fe = f;
-          while (fe < f1 && h->q_off[fe + 1] - h->q_off[f] <= cap) ++fe;
-          f = fe > f ? fe : f + 1;
-          ++runs;
-        }
-        max_runs = std::max(max_runs, runs);
-      }
-      // the row kernel when the stream kernel's re-reads of the rows (one per run) would miss
-      // the last-level cache: more than two runs and more row bytes than the cache holds
-      const bool rows_kernel = max_runs > 2 && nr * (int64_t)h->F * 4 > kLastLevelCacheBytes;
-      const int force = env_int("BRIDGER_BIN_KERNEL", 0);
-      a.n_chunks = force == 1 ? std::max(max_runs, 3)
-                   : force == 2 ? 1 : rows_kernel ? max_runs : 1;
-    }
+    // (the tuning override takes one way or the other)
+    const int force = env_int("BRIDGER_BIN_KERNEL", 0);
+    const bool lds = force == 1 || (force != 2 && nr * (int64_t)h->F >= kBinStagedValues);
+    const auto &runs = lds ? h->bin_runs : h->bin_runs_in_place;
+    BinTables bt{};
+    bt.image = (const uint32_t *)h->d_bin_image;
+    bt.features = (const BinFeature *)h->d_bin_features;
+    bt.runs = (const BinRun *)(lds ? h->d_bin_runs : h->d_bin_runs_in_place);
+    bt.n_runs = (int32_t)runs.size();
+    bt.lds_bytes = h->bin_lds_bytes;
+    bt.max_features = std::min(h->F, 1024);
     set_preprocess_args(h, a);
     RowNorms norms;
     if ((s = prepare_row_norms(h, a, stream, norms)) != BRIDGER_OK) return s;
-    const int err = launch_bin(a, stream);
+    const int err = launch_bin(a, bt, lds, stream);
     if (err != 0)
       return fail(BRIDGER_ERR_DEVICE, std::string("kernel launch failed: ") +
                                           hipGetErrorString((hipError_t)err));

@@ -183,8 +183,6 @@ struct LaunchArgs {
   int32_t finite_thresholds;   // PERFECT: every threshold is finite (sign-of-difference step)
   const uint32_t *roots;       // PERFECT: per kernel tree the root's traversal record (2 words)
   int32_t x_bytes;             // element of X and of the LDS tile: 4 (fp32) or 2 / 1 (bins)
-  const float *q_values;       // binning: sorted distinct thresholds of every feature
-  const int32_t *q_off;        // binning: [F + 1] offsets into q_values
   void *xq;                    // binning: output bins [n_rows, F] of x_bytes each
   int32_t csr;                 // rows in CSR form: X = values, plus the two arrays below
   const int64_t *csr_indptr;   // [n_rows + 1]
@@ -215,7 +213,33 @@ int launch_perfect(int depth, const LaunchArgs &a, int waves, int64_t n_wg, int 
                    void *stream);
 int launch_perfect_binned(int depth, const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes,
                           void *stream);
-int launch_bin(const LaunchArgs &a, void *stream);
+// Binning tables: an image of 32-bit words holding, feature after feature, its distinct thresholds
+// ascending, 8 words of +inf, and (16 bits each) for every cell of a grid over them the number of
+// thresholds in lower cells; x lies in cell (uint)min(max((x - lo) * scale, 0), top), in fp32.
+struct BinFeature {
+  float lo, scale, top;  // top: cells - 1
+  int32_t n;             // thresholds
+  int32_t tab;           // first word of the thresholds
+  int32_t start;         // first 16-bit word of the cells' counts
+  int32_t unused[2];
+};
+// A run of features that one workgroup looks up; a multiple of 4 features unless it ends the row.
+struct BinRun {
+  int32_t f0, f1;        // at most 1024 features
+  int32_t word0, words;  // their part of the image (multiples of 4 words)
+  int32_t staged;        // it is copied to LDS (a table too large for it is searched in place)
+  int32_t steps;         // largest power of two in the fullest cell's count
+};
+struct BinTables {
+  const uint32_t *image;
+  const BinFeature *features;
+  const BinRun *runs;
+  int32_t n_runs;
+  int32_t lds_bytes;     // of the largest staged run
+  int32_t max_features;  // of any run
+};
+// lds: stage the runs' tables (bt: the staged runs), else search them in place (bt: whole rows).
+int launch_bin(const LaunchArgs &a, const BinTables &bt, bool lds, void *stream);
 int launch_row_norm(const LaunchArgs &a, double *norm, void *stream);
 // Device address of the allocation-free predict's row-norm scratch on the current device
 // (kNoAllocMaxRows doubles); looked up once per device.  Returns a hipError_t as int.

@@ -60,7 +60,8 @@ enum { BRIDGER_XFORM_IDENTITY = 0, BRIDGER_XFORM_SIGMOID = 1, BRIDGER_XFORM_SOFT
 
 /* Kernel families.  AUTO picks PERFECT when every tree is a perfect binary tree of
  * one common depth (1..10), else RAGGED when every tree fits an LDS chunk, else
- * DIRECT.  PERFECT and RAGGED stage the trees through LDS (the data-movement
+ * DIRECT.  (Under AUTO a perfect forest's batches of up to 131,072 rows take the ragged
+ * walk, which fills the chip with fewer rows; the family reported stays PERFECT.)  PERFECT and RAGGED stage the trees through LDS (the data-movement
  * model of Eq. 1 sizes the row tile and the tree chunks); DIRECT reads nodes
  * from global memory and handles any forest.  GEMM is the matrix-multiply
  * lowering (Table 4's matmul and one_hot on the matrix cores) for perfect trees
@@ -305,7 +306,8 @@ bridger_status bridger_forest_get_kernel(bridger_forest_t h, int32_t *kernel);
 
 /*
  * The launch plan predict would use for n_rows rows (the Eq. 1 choice):
- * rows per workgroup, bytes of one LDS tree-chunk buffer, trees per chunk (0 when
+ * rows per workgroup (columns of its LDS tile: the ragged walk of a small batch holds a row in
+ * several), bytes of one LDS tree-chunk buffer, trees per chunk (0 when
  * chunks hold a varying number of trees), number of chunks, LDS bytes per
  * workgroup, and the modelled bytes moved per level (HBM, L2->LDS staging, LDS
  * reads).  Any output pointer may be NULL.  Works on host-only handles.

@@ -91,6 +91,8 @@ struct bridger_forest {
   bool host_only = false;
   int device = -1;
   int32_t kernel_active = kDirect;
+  bool kernel_auto = true;    // chosen by AUTO
+  bool perfect_heap = false;  // AUTO may take the padded-heap walk for a perfect forest
 
   std::vector<int32_t> tree_order;   // kernel position -> caller tree
   std::vector<int32_t> class_begin;  // [K+1]
@@ -171,7 +173,8 @@ struct bridger_forest {
   int32_t heap_levels = 0;  // L
   bool heap_flat = false;   // no tree deeper than L
   int32_t heap_waves = 0;   // BRIDGER_WAVES at create
-  int32_t heap_span[5] = {};  // most classes a lane group's trees span, of 1, 2, 4, 8, 16 groups
+  int32_t heap_rows = 0;    // BRIDGER_HEAP_ROWS at create
+  int32_t heap_span[7] = {};  // most classes a lane group's trees span, of 1, 2, 4 .. 64 groups
   RaggedHeaps heap, bheap;
   std::vector<int32_t> heap_leaf;  // leaf ids: two per block, or one per leaf word (flat)
   std::vector<float> vec_heap;     // vector leaves: class rows of the leaves, in record order
@@ -203,7 +206,8 @@ struct bridger_forest {
   std::vector<float> vec_pair;                 // vector leaves: the leaves' class rows
   void *d_vec_pair = nullptr;
 
-  // device copies
+  // device copies, all in the allocation d_arena
+  void *d_arena = nullptr;
   void *d_class_begin = nullptr, *d_class_count = nullptr, *d_base = nullptr,
        *d_tree_order = nullptr;
   DevArrays d_perfect, d_ragged, d_direct;
@@ -1392,42 +1396,92 @@ bool heaps_wanted(const bridger_forest *h) {
          env_int("BRIDGER_ROWS", 0) == 0 && h->F <= kDeepMaxFeatures;
 }
 
-// Launch plan of the padded-heap kernel for n_rows rows (waves == 0: does not fit): W waves, one
-// lane group of the 64 rows each, that split the trees.  Takes the W that puts the most waves on
-// the chip: large batches fill it with any W that keeps 32 waves on a CU, small ones need W = 16
-// to use more than a wave per 64 rows (100 trees, 3,001 rows of 28 features: one 512-row tile per
-// workgroup took 66 us).
+// One shape of the padded-heap kernel: W waves that share R rows, 64 / R lane groups in each.
+Plan heap_plan(const bridger_forest *h, int R, int W, bool binned) {
+  Plan p{};
+  const int groups = W * (64 / R);
+  const int64_t sums = (int64_t)h->K * W * 64 * 8;
+  // sums kept in LDS during the walk, or written over the tile after it
+  const bool regs = h->vec ? h->K <= 8 : h->K == 1 || h->heap_span[ilog2(groups)] <= kHeapClassRegs;
+  const int64_t walk = (int64_t)h->F * 64 * (binned ? 2 : 4) + (int64_t)groups * heap_wave_bytes(h->heap_levels);
+  const int64_t lds = regs ? std::max(walk, sums) : walk + sums;
+  if (lds > kLdsBytesPerCU) return p;
+  p.waves = W;
+  p.groups = groups;
+  p.rows_per_wg = R;
+  p.lds_bytes = (int32_t)lds;
+  p.acc_in_lds = 1;
+  p.acc_alias = regs ? 1 : 0;
+  p.global_nodes = 1;
+  p.tops = h->heap_levels;
+  p.ilp = heap_batch(h->heap_levels);
+  p.waves_per_cu = W * (int)std::min<int64_t>(kLdsBytesPerCU / lds, kMaxWavesPerCU / W);
+  return p;
+}
+
+// Launch plan of the padded-heap kernel for n_rows rows (waves == 0: does not fit).
+//   * Batches whose 16- or 32-row tiles leave a CU at most one: lane groups of that many rows, and
+//     the fewest waves with which a group has the fewest batches of trees, since what such a batch
+//     waits for is one group's chain (500 trees of depth 6, 1,000 rows: 9.8 us with 16-row groups,
+//     10.8 with 32, 14.1 with 64; 100 trees of depth 12, 3,001 rows: 7.3, 8.6, 9.7).  With more
+//     tiles than CUs the wave-uniform groups of 64 rows win (10,000 rows: 14.3 us, 16.9 with 32).
+//   * Else groups of 64 rows, and the W that puts the most waves on the chip; the fewest of equals
+//     (1M x 28 rows, 100 trees of depth 12: W = 2 0.225 ms, 4 0.236, 8 0.261).
 Plan choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
+  const int U = heap_batch(h->heap_levels);
+  n_rows = std::max<int64_t>(n_rows, 1);
+  for (int R : {16, 32}) {
+    const int gpw = 64 / R;
+    if (h->heap_rows ? R != h->heap_rows : n_rows > (int64_t)R * kNumCUs || h->n_trees < gpw * U) continue;
+    Plan best{};
+    int fewest = INT32_MAX;
+    for (int W : {1, 2, 4, 8, 16}) {
+      if (h->heap_waves && W != h->heap_waves) continue;
+      const int groups = W * gpw, batches = ((h->n_trees + groups - 1) / groups + U - 1) / U;
+      const Plan p = heap_plan(h, R, W, binned);
+      if (!p.waves || batches >= fewest) continue;
+      fewest = batches;
+      best = p;
+    }
+    if (best.waves) return best;
+  }
   Plan best{};
-  const int64_t n_wg = (std::max<int64_t>(n_rows, 1) + 63) / 64;
-  const int64_t tile = (int64_t)h->F * 64 * (binned ? 2 : 4);
   int64_t most = 0;
-  for (int i = 0; i < 5; ++i) {
-    const int W = 1 << i;
-    if (h->heap_waves && W != h->heap_waves) continue;
-    if (W > h->n_trees) continue;
-    const int64_t sums = (int64_t)h->K * W * 64 * 8;
-    // sums kept in LDS during the walk, or written over the tile after it
-    const bool regs = h->vec ? h->K <= 8 : h->K == 1 || h->heap_span[i] <= kHeapClassRegs;
-    const int64_t walk = tile + (int64_t)W * heap_wave_bytes(h->heap_levels);
-    const int64_t lds = regs ? std::max(walk, sums) : walk + sums;
-    if (lds > kLdsBytesPerCU) continue;
-    const int m = (int)std::min<int64_t>(kLdsBytesPerCU / lds, kMaxWavesPerCU / W);
-    const int64_t active = std::min<int64_t>(n_wg, (int64_t)kNumCUs * m) * W;
+  for (int W : {1, 2, 4, 8, 16}) {
+    if (h->heap_waves ? W != h->heap_waves : W > h->n_trees) continue;
+    const Plan p = heap_plan(h, 64, W, binned);
+    if (!p.waves) continue;
+    const int64_t active = std::min<int64_t>((n_rows + 63) / 64 * W, (int64_t)kNumCUs * p.waves_per_cu);
     if (active <= most) continue;
     most = active;
-    best = Plan{};
-    best.waves = best.groups = W;
-    best.rows_per_wg = 64;
-    best.lds_bytes = (int32_t)lds;
-    best.acc_in_lds = 1;
-    best.acc_alias = regs ? 1 : 0;
-    best.global_nodes = 1;
-    best.tops = h->heap_levels;
-    best.ilp = heap_batch(h->heap_levels);
-    best.waves_per_cu = m * W;
+    best = p;
   }
   return best;
+}
+
+// Perfect forests under AUTO: batches of up to this many rows take the padded-heap walk of their
+// ragged layout, whose waves need no chunk barriers and split the trees 16 to 64 ways; larger ones
+// fill the chip with one lane group per row and PERFECT's cheaper steps.  Measured (us, heap walk
+// against PERFECT): 500 trees of depth 6, 28 features: 1,000 rows 9.8 / 17.9, 10,000 14.3 / 20.1,
+// 100,000 68 / 74, 200,000 122 / 112; 100 trees of depth 8: 1,000 rows 7.0 / 15.4, 100,000
+// 24.6 / 24.1; 300 trees, 5 classes, 90 features, 51,630 rows 36.9 / 43.5.
+constexpr int64_t kHeapPerfectRows = int64_t(1) << 17;
+
+bool perfect_heap_wanted() {
+  for (const char *v : {"BRIDGER_SIZED_PLANS", "BRIDGER_DEEP", "BRIDGER_PERFECT_TOP_LEVELS",
+                        "BRIDGER_TOP_GROUP_KB", "BRIDGER_REG_SUMS", "BRIDGER_CHUNK_TREES",
+                        "BRIDGER_WG_PER_CU", "BRIDGER_NO_FIXED", "BRIDGER_NO_SIGN_STEP"}) {
+    const char *e = std::getenv(v);
+    if (e && *e) return false;  // the PERFECT kernels' tuning overrides
+  }
+  return true;
+}
+
+// Whether a prediction of n_rows rows takes the padded-heap kernel.
+bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned) {
+  if (!(binned ? h->heap_bok : h->heap_ok)) return false;
+  return h->kernel_active == kRagged ||
+         (h->kernel_active == kPerfect && h->kernel_auto && h->perfect_heap && n_rows <= kHeapPerfectRows);
 }
 
 // Launch plan of the DIRECT tile kernel (waves == 0: does not fit): W waves that share 64 rows and
@@ -1506,15 +1560,13 @@ bool alloc_refused(size_t bytes) {
 }
 
 template <class T>
-bridger_status upload(void **dst, const std::vector<T> &src, size_t pad = 0) {
+bridger_status upload(void **dst, const std::vector<T> &src) {
   const size_t bytes = src.size() * sizeof(T);
-  if (alloc_refused(bytes + pad + 16) || hipMalloc(dst, bytes + pad + 16) != hipSuccess) {
+  if (alloc_refused(bytes + 16) || hipMalloc(dst, bytes + 16) != hipSuccess) {
     *dst = nullptr;
     (void)hipGetLastError();
     return fail(BRIDGER_ERR_OUT_OF_MEMORY, "device allocation failed");
   }
-  if (pad && hipMemset(*dst, 0, bytes + pad + 16) != hipSuccess)
-    return fail(BRIDGER_ERR_DEVICE, "hipMemset failed");
   if (bytes && hipMemcpy(*dst, src.data(), bytes, hipMemcpyHostToDevice) != hipSuccess)
     return fail(BRIDGER_ERR_DEVICE, "hipMemcpy to device failed");
   return BRIDGER_OK;
@@ -1526,120 +1578,129 @@ void free_dev(void *&p) {
 }
 
 void free_all(bridger_forest *h) {
-  free_dev(h->d_class_begin);
-  free_dev(h->d_class_count);
-  free_dev(h->d_base);
-  free_dev(h->d_tree_order);
-  free_dev(h->d_perfect_trav);
-  free_dev(h->d_perfect_roots);
-  free_dev(h->d_perfect_broots);
-  for (auto *cs : {&h->perfect_copies, &h->perfect_bcopies})
-    for (auto &c : *cs) {
-      free_dev(c.d_trav);
-      free_dev(c.d_roots);
-    }
-  for (void **q : {&h->heap.d_tops, &h->heap.d_blocks, &h->bheap.d_tops, &h->bheap.d_blocks,
-                   &h->d_heap_leaf, &h->d_vec_heap, &h->d_vec_pair, &h->d_perfect_deep, &h->d_perfect_bdeep, &h->d_ragged_tops,
-                   &h->d_ragged_btops, &h->d_bin_image, &h->d_bin_features,
-                   &h->d_bin_runs, &h->d_bin_runs_in_place,
-                   &h->d_perfect_btrav, &h->d_ragged_brec,
-                   &h->d_ragged_bchunk_first, &h->d_ragged_bchunk_rec, &h->d_pre_a, &h->d_pre_b,
-                   &h->d_vec_perfect, &h->d_vec_ragged, &h->d_vec_direct})
-    free_dev(*q);
-  for (DevArrays *d : {&h->d_perfect, &h->d_ragged, &h->d_direct}) {
-    free_dev(d->nodes);
-    free_dev(d->tree_start);
-    free_dev(d->chunk_first);
-    free_dev(d->chunk_rec);
-    free_dev(d->leaf_map);
-  }
+  for (void **q : {&h->d_arena, &h->d_pre_a, &h->d_pre_b}) free_dev(*q);
 }
 
-bridger_status upload_all(bridger_forest *h) {
-  bridger_status s;
-  if ((s = upload(&h->d_class_begin, h->class_begin)) != BRIDGER_OK) return s;
-  if ((s = upload(&h->d_class_count, h->class_count)) != BRIDGER_OK) return s;
-  if ((s = upload(&h->d_base, h->base)) != BRIDGER_OK) return s;
-  if ((s = upload(&h->d_tree_order, h->tree_order)) != BRIDGER_OK) return s;
-  if (h->perfect_ok) {
-    if ((s = upload(&h->d_perfect.nodes, h->perfect_blob, 1024)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_perfect_trav, h->perfect_trav, 1024)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_perfect_roots, h->perfect_roots)) != BRIDGER_OK) return s;
-    for (auto &c : h->perfect_copies) {
-      if ((s = upload(&c.d_trav, c.trav, 1024)) != BRIDGER_OK) return s;
-      if ((s = upload(&c.d_roots, c.roots)) != BRIDGER_OK) return s;
+// The forest's device arrays in one allocation (h->d_arena): the small ones gathered into one copy.
+// Forty allocations and copies of their own were most of a small forest's create.
+struct Uploads {
+  struct Item {
+    void **dst;
+    const void *src;
+    size_t bytes, room;  // room: the bytes, zero padding and slack
+  };
+  std::vector<Item> items;
+  template <class T>
+  void add(void **dst, const std::vector<T> &src, size_t pad = 0) {
+    const size_t bytes = src.size() * sizeof(T);
+    items.push_back({dst, src.data(), bytes, (bytes + pad + 16 + 255) & ~size_t(255)});
+  }
+  bridger_status commit(void **arena) {
+    constexpr size_t kSmall = size_t(256) << 10;
+    std::stable_partition(items.begin(), items.end(), [](const Item &i) { return i.room <= kSmall; });
+    size_t total = 0, small = 0;
+    for (const Item &i : items) {
+      total += i.room;
+      if (i.room <= kSmall) small += i.room;
     }
-    if ((s = upload(&h->d_perfect.leaf_map, h->perfect_leaf_map)) != BRIDGER_OK) return s;
-    if (!h->perfect_deep.empty() &&
-        (s = upload(&h->d_perfect_deep, h->perfect_deep, 1024)) != BRIDGER_OK)
-      return s;
+    std::vector<uint8_t> staging(small, 0);
+    if (alloc_refused(total) || hipMalloc(arena, total) != hipSuccess) {
+      *arena = nullptr;
+      (void)hipGetLastError();
+      return fail(BRIDGER_ERR_OUT_OF_MEMORY, "device allocation failed");
+    }
+    size_t at = 0;
+    bool ok = true;
+    for (const Item &i : items) {
+      uint8_t *d = (uint8_t *)*arena + at;
+      *i.dst = d;
+      if (i.room <= kSmall) {
+        if (i.bytes) std::memcpy(&staging[at], i.src, i.bytes);
+      } else {
+        ok = ok && hipMemcpy(d, i.src, i.bytes, hipMemcpyHostToDevice) == hipSuccess &&
+             hipMemset(d + i.bytes, 0, i.room - i.bytes) == hipSuccess;
+      }
+      at += i.room;
+    }
+    ok = ok && hipMemcpy(*arena, staging.data(), small, hipMemcpyHostToDevice) == hipSuccess;
+    return ok ? BRIDGER_OK : fail(BRIDGER_ERR_DEVICE, "hipMemcpy to device failed");
+  }
+};
+
+bridger_status upload_all(bridger_forest *h) {
+  Uploads up;
+  up.add(&h->d_class_begin, h->class_begin);
+  up.add(&h->d_class_count, h->class_count);
+  up.add(&h->d_base, h->base);
+  up.add(&h->d_tree_order, h->tree_order);
+  if (h->perfect_ok) {
+    up.add(&h->d_perfect.nodes, h->perfect_blob, 1024);
+    up.add(&h->d_perfect_trav, h->perfect_trav, 1024);
+    up.add(&h->d_perfect_roots, h->perfect_roots);
+    for (auto &c : h->perfect_copies) {
+      up.add(&c.d_trav, c.trav, 1024);
+      up.add(&c.d_roots, c.roots);
+    }
+    up.add(&h->d_perfect.leaf_map, h->perfect_leaf_map);
+    if (!h->perfect_deep.empty()) up.add(&h->d_perfect_deep, h->perfect_deep, 1024);
   }
   if (h->ragged_ok) {
-    if ((s = upload(&h->d_ragged.nodes, h->ragged_rec, 1024)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_ragged.tree_start, h->ragged_tree_start)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_ragged.chunk_first, h->ragged_chunk_first)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_ragged.chunk_rec, h->ragged_chunk_rec)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_ragged.leaf_map, h->ragged_rec_node)) != BRIDGER_OK) return s;
+    up.add(&h->d_ragged.nodes, h->ragged_rec, 1024);
+    up.add(&h->d_ragged.tree_start, h->ragged_tree_start);
+    up.add(&h->d_ragged.chunk_first, h->ragged_chunk_first);
+    up.add(&h->d_ragged.chunk_rec, h->ragged_chunk_rec);
+    up.add(&h->d_ragged.leaf_map, h->ragged_rec_node);
     if (h->heap_ok) {
-      if ((s = upload(&h->heap.d_tops, h->heap.tops)) != BRIDGER_OK) return s;
-      if ((s = upload(&h->heap.d_blocks, h->heap.blocks)) != BRIDGER_OK) return s;
-      if ((s = upload(&h->d_heap_leaf, h->heap_leaf)) != BRIDGER_OK) return s;
-    } else if (!h->ragged_tops.empty() &&
-               (s = upload(&h->d_ragged_tops, h->ragged_tops)) != BRIDGER_OK) {
-      return s;
+      up.add(&h->heap.d_tops, h->heap.tops);
+      up.add(&h->heap.d_blocks, h->heap.blocks);
+      up.add(&h->d_heap_leaf, h->heap_leaf);
+    } else if (!h->ragged_tops.empty()) {
+      up.add(&h->d_ragged_tops, h->ragged_tops);
     }
   }
   if (h->bin_bytes) {
-    if ((s = upload(&h->d_bin_image, h->bin_image)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_bin_features, h->bin_features)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_bin_runs, h->bin_runs)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_bin_runs_in_place, h->bin_runs_in_place)) != BRIDGER_OK) return s;
+    up.add(&h->d_bin_image, h->bin_image);
+    up.add(&h->d_bin_features, h->bin_features);
+    up.add(&h->d_bin_runs, h->bin_runs);
+    up.add(&h->d_bin_runs_in_place, h->bin_runs_in_place);
   }
   if (h->perfect_bok) {
-    if ((s = upload(&h->d_perfect_btrav, h->perfect_btrav, 1024)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_perfect_broots, h->perfect_broots)) != BRIDGER_OK) return s;
+    up.add(&h->d_perfect_btrav, h->perfect_btrav, 1024);
+    up.add(&h->d_perfect_broots, h->perfect_broots);
     for (auto &c : h->perfect_bcopies) {
-      if ((s = upload(&c.d_trav, c.trav, 1024)) != BRIDGER_OK) return s;
-      if ((s = upload(&c.d_roots, c.roots)) != BRIDGER_OK) return s;
+      up.add(&c.d_trav, c.trav, 1024);
+      up.add(&c.d_roots, c.roots);
     }
-    if (!h->perfect_bdeep.empty() &&
-        (s = upload(&h->d_perfect_bdeep, h->perfect_bdeep, 1024)) != BRIDGER_OK)
-      return s;
+    if (!h->perfect_bdeep.empty()) up.add(&h->d_perfect_bdeep, h->perfect_bdeep, 1024);
   }
   if (h->ragged_bok) {
-    if ((s = upload(&h->d_ragged_brec, h->ragged_brec, 1024)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_ragged_bchunk_first, h->ragged_bchunk_first)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_ragged_bchunk_rec, h->ragged_bchunk_rec)) != BRIDGER_OK) return s;
+    up.add(&h->d_ragged_brec, h->ragged_brec, 1024);
+    up.add(&h->d_ragged_bchunk_first, h->ragged_bchunk_first);
+    up.add(&h->d_ragged_bchunk_rec, h->ragged_bchunk_rec);
     if (h->heap_bok) {
-      if ((s = upload(&h->bheap.d_tops, h->bheap.tops)) != BRIDGER_OK) return s;
-      if ((s = upload(&h->bheap.d_blocks, h->bheap.blocks)) != BRIDGER_OK) return s;
-    } else if (!h->ragged_btops.empty() &&
-               (s = upload(&h->d_ragged_btops, h->ragged_btops)) != BRIDGER_OK) {
-      return s;
+      up.add(&h->bheap.d_tops, h->bheap.tops);
+      up.add(&h->bheap.d_blocks, h->bheap.blocks);
+    } else if (!h->ragged_btops.empty()) {
+      up.add(&h->d_ragged_btops, h->ragged_btops);
     }
   }
   if (h->pair_ok) {
-    if ((s = upload(&h->d_direct.nodes, h->pair_rec)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_direct.tree_start, h->pair_start)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_direct.leaf_map, h->pair_node)) != BRIDGER_OK) return s;
+    up.add(&h->d_direct.nodes, h->pair_rec);
+    up.add(&h->d_direct.tree_start, h->pair_start);
+    up.add(&h->d_direct.leaf_map, h->pair_node);
   } else {
-    if ((s = upload(&h->d_direct.nodes, h->direct_rec)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_direct.tree_start, h->direct_root)) != BRIDGER_OK) return s;
-    if ((s = upload(&h->d_direct.leaf_map, h->direct_rec_node)) != BRIDGER_OK) return s;
+    up.add(&h->d_direct.nodes, h->direct_rec);
+    up.add(&h->d_direct.tree_start, h->direct_root);
+    up.add(&h->d_direct.leaf_map, h->direct_rec_node);
   }
   if (h->vec) {
-    if (!h->vec_perfect.empty() && (s = upload(&h->d_vec_perfect, h->vec_perfect)) != BRIDGER_OK)
-      return s;
-    if (!h->vec_ragged.empty() && (s = upload(&h->d_vec_ragged, h->vec_ragged)) != BRIDGER_OK)
-      return s;
-    if (!h->vec_heap.empty() && (s = upload(&h->d_vec_heap, h->vec_heap)) != BRIDGER_OK) return s;
-    if (h->pair_ok) {
-      if ((s = upload(&h->d_vec_pair, h->vec_pair)) != BRIDGER_OK) return s;
-    } else if ((s = upload(&h->d_vec_direct, h->vec_direct)) != BRIDGER_OK) {
-      return s;
-    }
+    if (!h->vec_perfect.empty()) up.add(&h->d_vec_perfect, h->vec_perfect);
+    if (!h->vec_ragged.empty()) up.add(&h->d_vec_ragged, h->vec_ragged);
+    if (!h->vec_heap.empty()) up.add(&h->d_vec_heap, h->vec_heap);
+    if (h->pair_ok) up.add(&h->d_vec_pair, h->vec_pair);
+    else up.add(&h->d_vec_direct, h->vec_direct);
   }
-  return BRIDGER_OK;
+  return up.commit(&h->d_arena);
 }
 
 // The Normalizer's row norms: n_rows doubles of stream-ordered scratch from the device's default
@@ -1774,9 +1835,9 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   }
   int err = 0;
   if (h->kernel_active == kPerfect || h->kernel_active == kRagged) {
-    const bool perfect = h->kernel_active == kPerfect;
+    const bool heaps = takes_heaps(h, n_rows, binned);
+    const bool perfect = h->kernel_active == kPerfect && !heaps;
     const bridger_forest::SizedPlan *sp = perfect ? sized_plan(h, n_rows, binned) : nullptr;
-    const bool heaps = !perfect && (binned ? h->heap_bok : h->heap_ok);
     const Plan p = sp ? sp->plan
                       : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
                       : heaps   ? choose_heap_plan(h, n_rows, binned)
@@ -1817,7 +1878,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
     const int64_t n_wg = (n_rows + p.rows_per_wg - 1) / p.rows_per_wg;
     // (bins compare exactly whatever the thresholds; fp32 needs them finite)
     // (leaf ids of any class count: no sums are kept)
-    const bool fixed = h->kernel_active == kPerfect &&
+    const bool fixed = perfect &&
                        (out_leaf ? h->perfect_tree_bytes == perfect_tree_bytes(h->perfect_depth)
                                  : h->K == 1 && !h->vec) &&
                        p.groups == 1 && p.waves <= 8 && (binned || h->finite_thresholds) &&
@@ -1825,7 +1886,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
                        perfect_fixed_ok(h->perfect_depth, p.trees_per_chunk) &&
                        p.chunk_bytes == p.trees_per_chunk * h->perfect_tree_bytes &&
                        h->fixed_chunks;
-    if (h->kernel_active == kPerfect && p.global_nodes) {
+    if (perfect && p.global_nodes) {
       if (p.tops) {  // after the row tile and the class sums
         a.top_levels = p.tops;
         a.top_group_bytes = p.top_group_bytes;
@@ -1848,7 +1909,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
     }
     else if (fixed)
       err = launch_perfect_fixed(h->perfect_depth, a, p.waves, n_wg, p.lds_bytes, stream);
-    else if (h->kernel_active == kPerfect)
+    else if (perfect)
       err = launch_perfect(h->perfect_depth, a, p.waves, n_wg, p.lds_bytes, stream);
     else if (heaps) {
       const auto &hp = binned ? h->bheap : h->heap;
@@ -1862,7 +1923,9 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
       // class sums over the tile after the walk, or behind the copies during it
       a.acc_alias = p.acc_alias;
       a.lds_acc_off =
-          p.acc_alias ? 0 : a.lds_top_off + p.waves * heap_wave_bytes(h->heap_levels);
+          p.acc_alias ? 0 : a.lds_top_off + p.groups * heap_wave_bytes(h->heap_levels);
+      a.heap_rows = p.rows_per_wg;
+      a.rows_per_wg = 64;  // columns of the tile
       err = (h->heap_levels == 5   ? launch_ragged_heap5
              : h->heap_levels == 6 ? launch_ragged_heap6
                                    : launch_ragged_heap7)(a, p.waves, n_wg, p.lds_bytes, stream);
@@ -2129,7 +2192,8 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
         h->heap_levels = heap_top_levels(h->max_depth);
         h->heap_flat = h->max_depth <= h->heap_levels;
         h->heap_waves = env_int("BRIDGER_WAVES", 0);
-        for (int i = 0; i < 5; ++i) h->heap_span[i] = class_span(h, 1 << i);
+        h->heap_rows = env_int("BRIDGER_HEAP_ROWS", 0);
+        for (int i = 0; i < 7; ++i) h->heap_span[i] = class_span(h, 1 << i);
         h->heap_ok = choose_heap_plan(h, pin.n_rows, false).waves > 0 &&
                      make_ragged_heaps(h, h->ragged_rec, false, h->heap, &h->heap_leaf);
       }
@@ -2201,7 +2265,9 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
       }
     }
     h->kernel_active = resolve_auto(h);
+    h->perfect_heap = perfect_heap_wanted();
     const int forced = env_int("BRIDGER_KERNEL", 0);
+    if (forced) h->kernel_auto = false;
     if (forced == kPerfect && h->perfect_ok) h->kernel_active = kPerfect;
     if (forced == kRagged && h->ragged_ok) h->kernel_active = kRagged;
     if (forced == kDirect) h->kernel_active = kDirect;
@@ -2407,24 +2473,33 @@ bridger_status bridger_forest_set_kernel(bridger_forest_t h, int32_t kernel) {
   g_last_error.clear();
   if (!h) return fail(BRIDGER_ERR_INVALID_ARGUMENT, "null handle");
   switch (kernel) {
-    case BRIDGER_KERNEL_AUTO: h->kernel_active = resolve_auto(h); return BRIDGER_OK;
+    case BRIDGER_KERNEL_AUTO:
+      h->kernel_active = resolve_auto(h);
+      h->kernel_auto = true;
+      return BRIDGER_OK;
     case BRIDGER_KERNEL_PERFECT:
       if (!h->perfect_ok)
         return fail(BRIDGER_ERR_UNSUPPORTED, "forest is not all perfect trees of one depth 1..10");
       h->kernel_active = kPerfect;
+      h->kernel_auto = false;
       return BRIDGER_OK;
     case BRIDGER_KERNEL_RAGGED:
       if (!h->ragged_ok)
         return fail(BRIDGER_ERR_UNSUPPORTED, "a tree does not fit the LDS-chunked layout");
       h->kernel_active = kRagged;
+      h->kernel_auto = false;
       return BRIDGER_OK;
-    case BRIDGER_KERNEL_DIRECT: h->kernel_active = kDirect; return BRIDGER_OK;
+    case BRIDGER_KERNEL_DIRECT:
+      h->kernel_active = kDirect;
+      h->kernel_auto = false;
+      return BRIDGER_OK;
     case BRIDGER_KERNEL_GEMM:
       if (!gemm_ok(h))
         return fail(BRIDGER_ERR_UNSUPPORTED,
                     "the matrix lowering needs perfect trees of depth 1..4, one class and at "
                     "most 64 features");
       h->kernel_active = kGemm;
+      h->kernel_auto = false;
       return BRIDGER_OK;
     default: return fail(BRIDGER_ERR_INVALID_ARGUMENT, "unknown kernel");
   }
@@ -2446,12 +2521,16 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
   if (n_rows < 0) return fail(BRIDGER_ERR_INVALID_ARGUMENT, "n_rows < 0");
   Plan p{};
   double forest_bytes = 0;
-  if (h->kernel_active == kPerfect) {
+  if (takes_heaps(h, n_rows, false)) {
+    p = choose_heap_plan(h, n_rows, false);
+    p.rows_per_wg = 64;  // the tile's columns; a small batch holds a row in several of them
+    forest_bytes = 8.0 * h->ragged_rec.size();
+  } else if (h->kernel_active == kPerfect) {
     const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, false);
     p = sp ? sp->plan : h->perfect_plan;
     forest_bytes = (double)h->perfect_blob.size();
   } else if (h->kernel_active == kRagged) {
-    p = h->heap_ok ? choose_heap_plan(h, n_rows, false) : h->ragged_plan;
+    p = h->ragged_plan;
     forest_bytes = 8.0 * h->ragged_rec.size();
   } else if (h->kernel_active == kGemm) {
     p.rows_per_wg = 64;

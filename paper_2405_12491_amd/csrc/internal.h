@@ -202,6 +202,7 @@ struct LaunchArgs {
   int32_t tile_coalesced;      // global-node RAGGED kernels: the row tile read 8 rows x 128 B a load
   int32_t trees_in_order;      // kernel tree order is the caller's
   int32_t leaf_bfs;            // PERFECT: the caller numbers every tree's nodes breadth-first
+  int32_t heap_rows;           // RAGGED heaps: rows of a lane group (the tile has 64 columns)
   int32_t flat;                // RAGGED heaps: no tree deeper than the heaps, leaf words only
 };
 

@@ -55,14 +55,19 @@ __device__ __forceinline__ void load_row_bins16(const LaunchArgs &a, uint32_t la
   }
 }
 
-// One wave is one lane group of 64 rows; the G waves of a workgroup share a 64-row tile and walk
-// contiguous ranges of the trees, U trees at a time, all lanes of a wave on the same trees.
+// A lane group is R = 64 / GPW rows (heap_rows); a wave holds GPW groups (1, 2 or 4), the G waves of
+// a workgroup share R rows, and the G * GPW groups walk contiguous ranges of the trees, U trees at a
+// time.  With one group per wave (MULTI false) all lanes of a wave are on the same trees and the
+// tree addresses are wave-uniform; small batches take more groups per wave instead, so that a
+// group's chain of batches is shorter (each group then has its own copies of the heaps).  The tile
+// has 64 columns whatever R: every lane has its own, a row in several of them, so the gathers meet
+// no bank conflicts.
 // XB: bytes of an element of X (4; 2 or 1: the tile then holds 16-bit bins).  FIN: fp32 with
 // finite thresholds (bins: always).  VK: 0 scalar leaves; 4 or 8 (K <= VK) or 64 vector leaves,
 // class sums in registers / LDS (a leaf's word is then its row of leaf_vec).  KS: scalar leaves
 // of several classes: -1 class sums in LDS slots, else the sums of the (at most KS) classes that
 // a group's trees span in registers until the walk is done; 0: one class.
-template <int L, int U, bool LEAVES, int XB, bool FIN, int VK, int KS>
+template <int L, int U, bool LEAVES, int XB, bool FIN, int VK, int KS, bool MULTI>
 __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int XL = XB == 4 ? 4 : 2;              // bytes of an element of the tile
@@ -75,26 +80,39 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   static_assert((U * TB) % 1024 == 0, "a batch is whole 1 KB copies");
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63;
-  const int G = a.groups, T = a.n_trees;
-  const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t row = (int64_t)blockIdx.x * 64 + lane;
+  const int T = a.n_trees;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = MULTI ? a.heap_rows : 64, GPW = MULTI ? 64 / R : 1;
+  const int GT = a.groups;                         // lane groups of the workgroup
+  const int gi = MULTI ? lane / R : 0;             // this lane's group within the wave
+  const int g = wave * GPW + gi;
+  const int64_t row = (int64_t)blockIdx.x * R + (MULTI ? (lane & (R - 1)) : lane);
   const bool row_ok = row < a.n_rows;
   const uint32_t lane_off = tile_row_off<XL>(lane);
-  const uint32_t buf = (uint32_t)a.lds_top_off + (uint32_t)g * (U * TB);
-  const int ga = (int)(((int64_t)T * g) / G), gb = (int)(((int64_t)T * (g + 1)) / G);
+  const uint32_t wbuf = (uint32_t)a.lds_top_off + (uint32_t)(wave * GPW) * (U * TB);
+  const uint32_t buf = wbuf + (uint32_t)gi * (U * TB);
+  const int ga = (int)(((int64_t)T * g) / GT), gb = (int)(((int64_t)T * (g + 1)) / GT);
+  const int NB = MULTI ? ((T + GT - 1) / GT + U - 1) / U : (gb - ga + U - 1) / U;  // batches
 
-  // the heaps of trees q .. q + U - 1 into this wave's buffer (U empty heaps follow the last)
-  auto copy_tops = [&](int q) {
+  // the heaps of batch j of the wave's groups into their buffers (U empty heaps follow the last)
+  auto copy_tops = [&](int j) {
+    for (int i = 0; i < GPW; ++i) {
+      const int q = min((int)(((int64_t)T * (wave * GPW + i)) / GT) + j * U, T);
 #pragma unroll
-    for (uint32_t k = 0; k < U * TB / 1024; ++k)
-      __builtin_amdgcn_global_load_lds(
-          (const void *)(reinterpret_cast<const uint8_t *>(a.tops) + (size_t)q * TB + k * 1024 +
-                         (size_t)lane * 16),
-          (__attribute__((address_space(3))) void *)((lds_byte *)smem + buf + k * 1024), 16, 0, 0);
+      for (uint32_t k = 0; k < U * TB / 1024; ++k)
+        __builtin_amdgcn_global_load_lds(
+            (const void *)(reinterpret_cast<const uint8_t *>(a.tops) + (size_t)q * TB + k * 1024 +
+                           (size_t)lane * 16),
+            (__attribute__((address_space(3))) void *)((lds_byte *)smem + wbuf +
+                                                       (uint32_t)i * (U * TB) + k * 1024),
+            16, 0, 0);
+    }
   };
-  if (ga < gb) copy_tops(ga);
-  if constexpr (XB == 4) load_tile_all<4, FIN>(smem, a, lane, row, row_ok, g, G);
-  else load_row_bins16<XB>(a, lane_off, row, row_ok, g, G);
+  if (NB > 0) copy_tops(0);
+  const int waves = (int)(blockDim.x >> 6);
+  if constexpr (XB != 4) load_row_bins16<XB>(a, lane_off, row, row_ok, wave, waves);
+  else if constexpr (MULTI) load_tile_any<4, FIN>(smem, a, lane, row, row_ok, wave, waves);
+  else load_tile_all<4, FIN>(smem, a, lane, row, row_ok, wave, waves);
   __syncthreads();
 
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -102,7 +120,7 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   const bool flat = a.flat != 0;  // no tree is deeper than L: a leaf word per slot, no blocks
 
   double *acc_lds = reinterpret_cast<double *>(smem + a.lds_acc_off) + tid;
-  const int slot_stride = G * 64;
+  const int slot_stride = (int)blockDim.x;
   int k0 = 0;  // KS > 0: the class of the group's first tree
   if (KS > 0)
     while (k0 + 1 < a.K && ga >= a.class_begin[k0 + 1]) ++k0;
@@ -127,13 +145,15 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
     }
   };
 
-  for (int q = ga; q < gb; q += U) {
-    const int nvalid = gb - q < U ? gb - q : U;
+  for (int j = 0; j < NB; ++j) {
+    const int q = ga + j * U;
+    const int nvalid = gb - q < U ? gb - q : U;  // (MULTI: per lane, and 0 or less past its trees)
     wait_stage();  // this batch's heaps have landed
     uint32_t m[U], base[U], res[U], oi[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      base[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_u64(smem, buf + u * TB).x);
+      const uint32_t first = lds_u64(smem, buf + u * TB).x;
+      base[u] = MULTI ? first : (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
       m[u] = 1u;
     }
 #pragma unroll
@@ -148,7 +168,7 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
       for (int u = 0; u < U; ++u) m[u] = step_slot<FIN, XL>(m[u], rec[u].x, xv[u]);
     }
     // the heaps are read: the next batch's can land while the deep blocks are walked
-    if (q + U < gb) copy_tops(q + U);
+    if (j + 1 < NB) copy_tops(j + 1);
     if (flat) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -165,9 +185,9 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
         blk[u] = u32x4{0u, 0u, 0u, 0u};
         res[u] = oi[u] = 0u;
       }
-      // slot m of block level j (2^L 4^j <= m < 2^(L+1) 4^j) is block base + m + off
+      // slot m of block level lv (2^L 4^lv <= m < 2^(L+1) 4^lv) is block base + m + off
       uint32_t off = 0u - (1u << L), width = 1u << L;
-      for (int j = 0; j < 32; ++j) {  // trees are at most 64 levels deep
+      for (int lv = 0; lv < 32; ++lv) {  // trees are at most 64 levels deep
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (live[u])
@@ -274,16 +294,16 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
     acc_lds[0] = ca.acc;
   }
   __syncthreads();
-  groups_finalize_store(a, reinterpret_cast<double *>(smem + a.lds_acc_off), 64, G, slot_stride,
+  groups_finalize_store(a, reinterpret_cast<double *>(smem + a.lds_acc_off), R, GT, slot_stride,
                         tid, row, row_ok);
 }
 
 // ---------------------------------------------------------------------- launchers
-template <int L, int U, int XB, bool FIN>
-static int launch_heap_luxf(const LaunchArgs &a, int threads, int64_t n_wg, int lds_bytes,
+template <int L, int U, int XB, bool FIN, bool MULTI>
+static int launch_heap_luxfm(const LaunchArgs &a, int threads, int64_t n_wg, int lds_bytes,
                             void *stream) {
 #define BRIDGER_HEAP(LEAVES, VK, KS) \
-  launch_common(ragged_heap_kernel<L, U, LEAVES, XB, FIN, VK, KS>, threads, n_wg, lds_bytes, stream, a)
+  launch_common(ragged_heap_kernel<L, U, LEAVES, XB, FIN, VK, KS, MULTI>, threads, n_wg, lds_bytes, stream, a)
   if (a.out_leaf) return BRIDGER_HEAP(true, 0, 0);
   if (a.vec && a.K <= 4) return BRIDGER_HEAP(false, 4, 0);
   if (a.vec && a.K <= 8) return BRIDGER_HEAP(false, 8, 0);
@@ -292,6 +312,13 @@ static int launch_heap_luxf(const LaunchArgs &a, int threads, int64_t n_wg, int 
   if (a.acc_alias) return BRIDGER_HEAP(false, 0, kHeapClassRegs);
   return BRIDGER_HEAP(false, 0, -1);
 #undef BRIDGER_HEAP
+}
+
+template <int L, int U, int XB, bool FIN>
+static int launch_heap_luxf(const LaunchArgs &a, int threads, int64_t n_wg, int lds_bytes,
+                            void *stream) {
+  return a.heap_rows < 64 ? launch_heap_luxfm<L, U, XB, FIN, true>(a, threads, n_wg, lds_bytes, stream)
+                          : launch_heap_luxfm<L, U, XB, FIN, false>(a, threads, n_wg, lds_bytes, stream);
 }
 
 template <int L, int U>

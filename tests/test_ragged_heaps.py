@@ -7,8 +7,8 @@ import oracle
 import paper_2405_12491_amd as B
 from oracle import binning
 from parity_util import assert_scores
-from synth import (AGG_MEAN, AGG_SUM, XFORM_IDENTITY, XFORM_SIGMOID, XFORM_SOFTMAX, permute_nodes,
-                   random_tiny_forest, with_vector_leaves)
+from synth import (AGG_MEAN, AGG_SUM, XFORM_IDENTITY, XFORM_SIGMOID, XFORM_SOFTMAX, concat_trees,
+                   perfect_tree_arrays, permute_nodes, random_tiny_forest, with_vector_leaves)
 
 GRID = [-1.0, -0.0, 0.0, 0.5, 1.0]
 VALUES = np.array([-1.0, -0.0, 0.0, 0.5, 1.0, 2.0, np.nan, np.inf, -np.inf], np.float32)
@@ -111,20 +111,48 @@ def test_heap_layout_vector_leaves():
 @pytest.mark.parametrize("n_rows,features,bytes_", [(1, 28, 4), (3001, 28, 4), (10**6, 28, 4), (10**6, 256, 4),
                                                     (5000, 600, 4)])
 def test_heap_plan_fits(n_rows, features, bytes_):
-    """Every batch size gets a 64-row plan within a CU's LDS."""
+    """Every batch size gets a plan within a CU's LDS: a 64-column tile and a heap copy per lane group."""
     rng = np.random.default_rng(3)
     model = random_tiny_forest(rng, 40, features, max_depth=9)
     with B.Forest(model, host_only=True) as f:
         p = f.plan(n_rows)
         assert p["rows_per_wg"] == 64 and 0 < p["lds_bytes"] <= 163840
-        waves = (p["lds_bytes"] - features * 64 * bytes_) // 2048  # 6 top levels: 2 KB a wave
-        assert waves in (1, 2, 4, 8, 16)
+        groups = (p["lds_bytes"] - features * 64 * bytes_) // 2048  # 6 top levels: 2 KB a group
+        assert groups in (1, 2, 4, 8, 16, 32, 64)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("waves", [0, 1, 2, 8, 16])
+@pytest.mark.parametrize("n_rows", [1, 17, 4096, 4097, 8193, 131072, 131073])
+def test_perfect_small_batches(n_rows):
+    """AUTO on perfect forests around the rows where the shape of the walk changes (16-, 32- and
+    64-row groups, then the PERFECT kernels): the explicit PERFECT kernel's outputs."""
+    import torch
+    rng = np.random.default_rng(n_rows)
+    for D, K, T in ((3, 1, 9), (6, 3, 70), (8, 1, 40)):
+        trees = [perfect_tree_arrays(D, rng.integers(0, 10, (1 << D) - 1),
+                                     rng.standard_normal((1 << D) - 1).astype(np.float32),
+                                     rng.standard_normal(1 << D).astype(np.float32)) for _ in range(T)]
+        model = concat_trees(trees, 10, K, None if K == 1 else np.arange(T) % K, AGG_SUM,
+                             XFORM_SIGMOID if K == 1 else XFORM_SOFTMAX)
+        X = torch.from_numpy(rng.standard_normal((n_rows, 10)).astype(np.float32)).cuda()
+        with B.Forest(model) as f:
+            assert f.kernel == B.BRIDGER_KERNEL_PERFECT
+            q = f.bin(X)
+            got = [f.predict(X), f.predict_binned(q), f.predict_labels(X), f.predict_leaves(X)]
+            assert (f.plan(n_rows)["chunk_bytes"] == 0) == (n_rows <= 131072)
+            f.kernel = B.BRIDGER_KERNEL_PERFECT
+            ref = [f.predict(X), f.predict_binned(q), f.predict_labels(X), f.predict_leaves(X)]
+            assert f.plan(n_rows)["chunk_bytes"] > 0
+        for g, r in zip(got[:2], ref[:2]):  # double sums in another order, rounded once
+            assert torch.allclose(g, r, rtol=2.4e-7, atol=1e-7)
+        assert torch.equal(got[2], ref[2]) and torch.equal(got[3], ref[3])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [64, 32, 16])
+@pytest.mark.parametrize("waves", [1, 2, 8, 16])
 @pytest.mark.parametrize("depth", [3, 6, 7, 8, 9, 12])
-def test_heap_kernel(depth, waves, monkeypatch):
+def test_heap_kernel(depth, waves, rows, monkeypatch):
     """Scores, labels, leaf ids, bins and CSR rows around the tile's edges, for every number of
     lane groups, scalar leaves of 1, 3 and 13 classes and vector leaves of 2, 7 and 9."""
     import dataclasses
@@ -132,11 +160,11 @@ def test_heap_kernel(depth, waves, monkeypatch):
     import torch
 
     from oracle import vector
-    if waves:
-        monkeypatch.setenv("BRIDGER_WAVES", str(waves))
+    monkeypatch.setenv("BRIDGER_WAVES", str(waves))
+    monkeypatch.setenv("BRIDGER_HEAP_ROWS", str(rows))
     rng = np.random.default_rng(900 + depth)
     F = 7 if depth % 2 else 12
-    T = 17 if depth != 8 else 43
+    T = 17 if depth != 8 else 71
     grid = GRID if depth != 9 else None
     base = random_tiny_forest(rng, T, F, max_depth=depth, p_split=0.9, thr_grid=grid)
     models = [dataclasses.replace(base, transform=XFORM_SIGMOID)]
@@ -146,9 +174,9 @@ def test_heap_kernel(depth, waves, monkeypatch):
     models += [with_vector_leaves(base, 2, rng), with_vector_leaves(base, 7, rng),
                with_vector_leaves(base, 9, rng, AGG_SUM, XFORM_IDENTITY)]
     for model in models:
-        for n in (1, 63, 64, 65, 130):
+        for n in (1, 63, 65):
             X = rng.choice(VALUES[:7], (n, F)) if grid else rng.standard_normal((n, F)).astype(np.float32)
-            what = f"depth {depth} waves {waves} K {model.n_classes} rows {n}"
+            what = f"depth {depth} waves {waves}x{rows} K {model.n_classes} rows {n}"
             print(what, flush=True)
             if model.value.ndim == 2:
                 ref, ref_lv = vector.predict(model, X)

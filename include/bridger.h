@@ -60,7 +60,7 @@ enum { BRIDGER_XFORM_IDENTITY = 0, BRIDGER_XFORM_SIGMOID = 1, BRIDGER_XFORM_SOFT
 
 /* Kernel families.  AUTO picks PERFECT when every tree is a perfect binary tree of
  * one common depth (1..10), else RAGGED when every tree fits an LDS chunk, else
- * DIRECT.  (Under AUTO a perfect forest's batches of up to 131,072 rows take the ragged
+ * DIRECT.  (Under AUTO a perfect forest's smaller batches, and wide rows, take the ragged
  * walk, which fills the chip with fewer rows; the family reported stays PERFECT.)  PERFECT and RAGGED stage the trees through LDS (the data-movement
  * model of Eq. 1 sizes the row tile and the tree chunks); DIRECT reads nodes
  * from global memory and handles any forest.  GEMM is the matrix-multiply
@@ -347,7 +347,7 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
  * = f(n) << 8 | rotl(c0, 10) | rotl(c1, 21) with c = (f(c) | leaf(c) << 10) << 8; a leaf word is
  * the value's bits or, with vector leaves, the leaf's place among the leaf records; 16 the leaf id
  * of each leaf word, or of each block's two children, 17 and 18 as 14 and 15 for bins (ranks, and
- * 7 in place of 8).  *ptr stays valid until destroy or set_kernel.
+ * 7 in place of 8; 7 in 14 and 15 too above 576 features).  *ptr stays valid until destroy or set_kernel.
  */
 bridger_status bridger_forest_packed(bridger_forest_t h, int32_t which, const void **ptr,
                                      int64_t *bytes);

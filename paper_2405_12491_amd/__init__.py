@@ -304,15 +304,18 @@ class Forest:
             raise TypeError("X must be a float32 CUDA tensor")
         if X.dim() != 2 or X.shape[1] != self.n_features or not X.is_contiguous():
             raise ValueError("X must be contiguous [n_rows, n_features]")
+        return X.shape[0]
 
     def predict(self, X, out=None):
-        import torch
-        self._check_x(X)
+        # a small batch is bound by this call: no argument objects, and new_empty (X's dtype and
+        # device are the output's) in place of torch.empty (one 10k-row tree 6.8 -> 5.7 us)
+        n = self._check_x(X)
         if out is None:
-            out = torch.empty((X.shape[0], self.n_classes), dtype=torch.float32, device=X.device)
-        stream = _launch_stream(X.device)
-        bridger_forest_predict(self._h, X.data_ptr(), X.shape[0], self.n_features, out.data_ptr(),
-                               stream)
+            out = X.new_empty((n, self.n_classes))
+        st = _lib.bridger_forest_predict(self._h, X.data_ptr(), n, self.n_features, out.data_ptr(),
+                                         _launch_stream(X.device))
+        if st != BRIDGER_OK:
+            _check(st, "bridger_forest_predict")
         return out
 
     def predict_csr(self, indptr, indices, values, n_rows: int, out=None, leaves: bool = False):

@@ -92,6 +92,7 @@ struct bridger_forest {
   int device = -1;
   int32_t kernel_active = kDirect;
   bool kernel_auto = true;    // chosen by AUTO
+  bool tile_coalesced = true; // BRIDGER_COALESCED_TILE at create
   bool perfect_heap = false;  // AUTO may take the padded-heap walk for a perfect forest
 
   std::vector<int32_t> tree_order;   // kernel position -> caller tree
@@ -174,6 +175,7 @@ struct bridger_forest {
   bool heap_flat = false;   // no tree deeper than L
   int32_t heap_waves = 0;   // BRIDGER_WAVES at create
   int32_t heap_rows = 0;    // BRIDGER_HEAP_ROWS at create
+  Plan heap_plans[2][3][5] = {};  // [binned][64, 32 or 16 rows][1, 2, 4, 8 or 16 waves]; waves 0: none
   int32_t heap_span[7] = {};  // most classes a lane group's trees span, of 1, 2, 4 .. 64 groups
   RaggedHeaps heap, bheap;
   std::vector<int32_t> heap_leaf;  // leaf ids: two per block, or one per leaf word (flat)
@@ -1288,13 +1290,21 @@ int heap_top_levels(int max_depth) {
   return max_depth % 2 == 0 ? 5 : 6;
 }
 
+// Columns of the padded-heap kernel's tile, and bytes of a feature's row of it.
+int heap_columns(const bridger_forest *h, bool binned) {
+  return !binned && h->F > kHeapWideFeatures ? 32 : 64;
+}
+int heap_row_bytes(const bridger_forest *h, bool binned) {
+  return heap_columns(h, binned) * (binned ? 2 : 4);
+}
+
 // RAGGED heaps (layout in internal.h) of the packed records `rec` (fp32 thresholds, or ranks when
 // `binned`); leaf_ids as the layout's leaf_map, when wanted.  False when they would take more
 // than heap_bytes_limit.
 bool make_ragged_heaps(const bridger_forest *h, const std::vector<uint64_t> &rec, bool binned,
                        bridger_forest::RaggedHeaps &out, std::vector<int32_t> *leaf_ids) {
   const int L = h->heap_levels;
-  const uint32_t s = binned ? 7 : 8;
+  const uint32_t s = (uint32_t)ilog2(heap_row_bytes(h, binned));
   const int64_t slots = int64_t(1) << L;
   // vector leaves: a leaf's word is its row of class values, the leaf records in order
   std::vector<int32_t> leaf_row;
@@ -1400,10 +1410,11 @@ bool heaps_wanted(const bridger_forest *h) {
 Plan heap_plan(const bridger_forest *h, int R, int W, bool binned) {
   Plan p{};
   const int groups = W * (64 / R);
+  if (R > heap_columns(h, binned)) return p;
   const int64_t sums = (int64_t)h->K * W * 64 * 8;
   // sums kept in LDS during the walk, or written over the tile after it
   const bool regs = h->vec ? h->K <= 8 : h->K == 1 || h->heap_span[ilog2(groups)] <= kHeapClassRegs;
-  const int64_t walk = (int64_t)h->F * 64 * (binned ? 2 : 4) + (int64_t)groups * heap_wave_bytes(h->heap_levels);
+  const int64_t walk = (int64_t)h->F * heap_row_bytes(h, binned) + (int64_t)groups * heap_wave_bytes(h->heap_levels);
   const int64_t lds = regs ? std::max(walk, sums) : walk + sums;
   if (lds > kLdsBytesPerCU) return p;
   p.waves = W;
@@ -1425,47 +1436,58 @@ Plan heap_plan(const bridger_forest *h, int R, int W, bool binned) {
 //     waits for is one group's chain (500 trees of depth 6, 1,000 rows: 9.8 us with 16-row groups,
 //     10.8 with 32, 14.1 with 64; 100 trees of depth 12, 3,001 rows: 7.3, 8.6, 9.7).  With more
 //     tiles than CUs the wave-uniform groups of 64 rows win (10,000 rows: 14.3 us, 16.9 with 32).
-//   * Else groups of 64 rows, and the W that puts the most waves on the chip; the fewest of equals
+//   * Else groups of 64 rows (32 in a 32-column tile), and the W that puts the most waves on the chip; the fewest of equals
 //     (1M x 28 rows, 100 trees of depth 12: W = 2 0.225 ms, 4 0.236, 8 0.261).
-Plan choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
+const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
   const int U = heap_batch(h->heap_levels);
   n_rows = std::max<int64_t>(n_rows, 1);
   for (int R : {16, 32}) {
     const int gpw = 64 / R;
     if (h->heap_rows ? R != h->heap_rows : n_rows > (int64_t)R * kNumCUs || h->n_trees < gpw * U) continue;
-    Plan best{};
+    const Plan *best = nullptr;
     int fewest = INT32_MAX;
     for (int W : {1, 2, 4, 8, 16}) {
       if (h->heap_waves && W != h->heap_waves) continue;
       const int groups = W * gpw, batches = ((h->n_trees + groups - 1) / groups + U - 1) / U;
-      const Plan p = heap_plan(h, R, W, binned);
+      const Plan &p = h->heap_plans[binned][ilog2(gpw)][ilog2(W)];
       if (!p.waves || batches >= fewest) continue;
       fewest = batches;
-      best = p;
+      best = &p;
     }
-    if (best.waves) return best;
+    if (best) return *best;
   }
-  Plan best{};
+  static const Plan none{};
+  const Plan *best = &none;
+  const int R = heap_columns(h, binned);
   int64_t most = 0;
   for (int W : {1, 2, 4, 8, 16}) {
-    if (h->heap_waves ? W != h->heap_waves : W > h->n_trees) continue;
-    const Plan p = heap_plan(h, 64, W, binned);
+    if (h->heap_waves ? W != h->heap_waves : W * (64 / R) > h->n_trees && W > 1) continue;
+    const Plan &p = h->heap_plans[binned][ilog2(64 / R)][ilog2(W)];
     if (!p.waves) continue;
-    const int64_t active = std::min<int64_t>((n_rows + 63) / 64 * W, (int64_t)kNumCUs * p.waves_per_cu);
+    const int64_t active = std::min<int64_t>((n_rows + R - 1) / R * W, (int64_t)kNumCUs * p.waves_per_cu);
     if (active <= most) continue;
     most = active;
-    best = p;
+    best = &p;
   }
-  return best;
+  return *best;
 }
 
-// Perfect forests under AUTO: batches of up to this many rows take the padded-heap walk of their
-// ragged layout, whose waves need no chunk barriers and split the trees 16 to 64 ways; larger ones
-// fill the chip with one lane group per row and PERFECT's cheaper steps.  Measured (us, heap walk
-// against PERFECT): 500 trees of depth 6, 28 features: 1,000 rows 9.8 / 17.9, 10,000 14.3 / 20.1,
-// 100,000 68 / 74, 200,000 122 / 112; 100 trees of depth 8: 1,000 rows 7.0 / 15.4, 100,000
-// 24.6 / 24.1; 300 trees, 5 classes, 90 features, 51,630 rows 36.9 / 43.5.
-constexpr int64_t kHeapPerfectRows = int64_t(1) << 17;
+// Perfect forests under AUTO.  Batches that do not fill the chip with one lane group per row take
+// the padded-heap walk of their ragged layout, whose waves need no chunk barriers and split the
+// trees 16 to 64 ways; larger ones PERFECT's cheaper steps.  Measured (us, heap walk / PERFECT): 500
+// trees of depth 6, 28 features: 1,000 rows 9.8 / 17.9, 10,000 14.3 / 20.1, 100,000 68 / 74,
+// 200,000 122 / 112; 100 trees of depth 8: 1,000 rows 7.0 / 15.4, 100,000 24.6 / 24.1; 300 trees, 5
+// classes, 90 features, 51,630 rows 36.9 / 43.5.  Vector leaves: 100 trees of depth 8, 7 classes: 10,000
+// rows 11.5 / 20.3, 30,000 20.6 / 20.4, 60,000 38 / 32.  Leaf ids (a table gather per leaf against
+// none): 500 trees of depth 6: 5,000 rows 12.3 / 18.0, 10,000 22.5 / 24.5, 20,000 54 / 28.
+constexpr int64_t kHeapPerfectRows = int64_t(1) << 17, kHeapVectorRows = int64_t(1) << 14,
+                  kHeapLeafRows = int64_t(1) << 13;
+// Rows whose tile leaves PERFECT several lane groups a tile and few waves, or its records to be
+// read from global memory, take the heap walk in batches of any size (400,000 rows, 300 trees of
+// depth 6: 60 features 150 / 148, 90 159 / 206, 128 166 / 191, 300 319 / 567; 100 trees of depth
+// 8: 60 features (8 waves a CU) 79 / 130, 90 126 / 263, 128 97 / 218; 1000 trees of depth 8, 784
+// features, 10 classes: 100,000 rows 409 / 425, 300,000 1,158 / 1,202).
+constexpr int kHeapTileRowBytes = 256;  // of one row of the tile, from which that holds
 
 bool perfect_heap_wanted() {
   for (const char *v : {"BRIDGER_SIZED_PLANS", "BRIDGER_DEEP", "BRIDGER_PERFECT_TOP_LEVELS",
@@ -1478,10 +1500,16 @@ bool perfect_heap_wanted() {
 }
 
 // Whether a prediction of n_rows rows takes the padded-heap kernel.
-bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned) {
+bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves) {
   if (!(binned ? h->heap_bok : h->heap_ok)) return false;
-  return h->kernel_active == kRagged ||
-         (h->kernel_active == kPerfect && h->kernel_auto && h->perfect_heap && n_rows <= kHeapPerfectRows);
+  if (h->kernel_active == kRagged) return true;
+  if (h->kernel_active != kPerfect || !h->kernel_auto || !h->perfect_heap) return false;
+  if (leaves) return n_rows <= kHeapLeafRows;
+  const Plan &p = binned ? h->perfect_bplan : h->perfect_plan;
+  const int row_bytes = h->F * (binned ? h->bin_bytes : 4);
+  if (p.global_nodes || (p.groups > 1 && (row_bytes >= kHeapTileRowBytes || p.waves_per_cu < 16)))
+    return true;
+  return n_rows <= (h->vec ? kHeapVectorRows : kHeapPerfectRows);
 }
 
 // Launch plan of the DIRECT tile kernel (waves == 0: does not fit): W waves that share 64 rows and
@@ -1827,7 +1855,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   a.K = h->K;
   a.aggregate = h->aggregate;
   a.transform = h->transform;
-  a.tile_coalesced = env_int("BRIDGER_COALESCED_TILE", 1) != 0 ? 1 : 0;
+  a.tile_coalesced = h->tile_coalesced ? 1 : 0;
   RowNorms norms;
   if (!binned) {
     set_preprocess_args(h, a);
@@ -1835,13 +1863,13 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   }
   int err = 0;
   if (h->kernel_active == kPerfect || h->kernel_active == kRagged) {
-    const bool heaps = takes_heaps(h, n_rows, binned);
+    const bool heaps = takes_heaps(h, n_rows, binned, out_leaf != nullptr);
     const bool perfect = h->kernel_active == kPerfect && !heaps;
     const bridger_forest::SizedPlan *sp = perfect ? sized_plan(h, n_rows, binned) : nullptr;
-    const Plan p = sp ? sp->plan
-                      : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
-                      : heaps   ? choose_heap_plan(h, n_rows, binned)
-                                : (binned ? h->ragged_bplan : h->ragged_plan);
+    const Plan &p = sp ? sp->plan
+                       : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
+                       : heaps   ? choose_heap_plan(h, n_rows, binned)
+                                 : (binned ? h->ragged_bplan : h->ragged_plan);
     const DevArrays &d = perfect ? h->d_perfect : h->d_ragged;
     if (perfect)
       a.nodes = (const uint8_t *)(binned ? h->d_perfect_btrav : h->d_perfect_trav);
@@ -1919,13 +1947,13 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
       a.flat = h->heap_flat ? 1 : 0;
       a.leaf_map = (const int32_t *)h->d_heap_leaf;
       a.leaf_vec = (const float *)h->d_vec_heap;
-      a.lds_top_off = h->F * 64 * (binned ? 2 : 4);
+      a.lds_top_off = h->F * heap_row_bytes(h, binned);
       // class sums over the tile after the walk, or behind the copies during it
       a.acc_alias = p.acc_alias;
       a.lds_acc_off =
           p.acc_alias ? 0 : a.lds_top_off + p.groups * heap_wave_bytes(h->heap_levels);
       a.heap_rows = p.rows_per_wg;
-      a.rows_per_wg = 64;  // columns of the tile
+      a.rows_per_wg = heap_columns(h, binned);
       err = (h->heap_levels == 5   ? launch_ragged_heap5
              : h->heap_levels == 6 ? launch_ragged_heap6
                                    : launch_ragged_heap7)(a, p.waves, n_wg, p.lds_bytes, stream);
@@ -2194,6 +2222,9 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
         h->heap_waves = env_int("BRIDGER_WAVES", 0);
         h->heap_rows = env_int("BRIDGER_HEAP_ROWS", 0);
         for (int i = 0; i < 7; ++i) h->heap_span[i] = class_span(h, 1 << i);
+        for (int b = 0; b < 2; ++b)
+          for (int r = 0; r < 3; ++r)
+            for (int w = 0; w < 5; ++w) h->heap_plans[b][r][w] = heap_plan(h, 64 >> r, 1 << w, b != 0);
         h->heap_ok = choose_heap_plan(h, pin.n_rows, false).waves > 0 &&
                      make_ragged_heaps(h, h->ragged_rec, false, h->heap, &h->heap_leaf);
       }
@@ -2266,6 +2297,7 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
     }
     h->kernel_active = resolve_auto(h);
     h->perfect_heap = perfect_heap_wanted();
+    h->tile_coalesced = env_int("BRIDGER_COALESCED_TILE", 1) != 0;
     const int forced = env_int("BRIDGER_KERNEL", 0);
     if (forced) h->kernel_auto = false;
     if (forced == kPerfect && h->perfect_ok) h->kernel_active = kPerfect;
@@ -2521,9 +2553,9 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
   if (n_rows < 0) return fail(BRIDGER_ERR_INVALID_ARGUMENT, "n_rows < 0");
   Plan p{};
   double forest_bytes = 0;
-  if (takes_heaps(h, n_rows, false)) {
+  if (takes_heaps(h, n_rows, false, false)) {
     p = choose_heap_plan(h, n_rows, false);
-    p.rows_per_wg = 64;  // the tile's columns; a small batch holds a row in several of them
+    p.rows_per_wg = heap_columns(h, false);  // the tile's columns; a small batch holds a row in several of them
     forest_bytes = 8.0 * h->ragged_rec.size();
   } else if (h->kernel_active == kPerfect) {
     const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, false);

@@ -67,11 +67,15 @@ __device__ __forceinline__ void load_row_bins16(const LaunchArgs &a, uint32_t la
 // class sums in registers / LDS (a leaf's word is then its row of leaf_vec).  KS: scalar leaves
 // of several classes: -1 class sums in LDS slots, else the sums of the (at most KS) classes that
 // a group's trees span in registers until the walk is done; 0: one class.
-template <int L, int U, bool LEAVES, int XB, bool FIN, int VK, int KS, bool MULTI>
+// C: columns of the tile.  Rows too wide for 64 fp32 columns (above kHeapWideFeatures features) take
+// 32, with groups of 32 or 16 rows: the halves of a wave then read the same columns.
+template <int L, int U, bool LEAVES, int XB, bool FIN, int VK, int KS, bool MULTI, int C>
 __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int XL = XB == 4 ? 4 : 2;              // bytes of an element of the tile
-  constexpr uint32_t kShift = XL == 4 ? 8u : 7u;   // log2 of a feature's row of the tile
+  constexpr uint32_t kShift = XL * C == 256 ? 8u : 7u;  // log2 of a feature's row of the tile
+  static_assert(XL * C == 128 || XL * C == 256, "a feature's row is 128 or 256 bytes");
+  static_assert(C == 64 || (C == 32 && XB == 4 && MULTI), "32 columns: fp32 rows, several groups");
   constexpr uint32_t kField = 1023u << kShift;     // a feature field in place: its row's offset
   constexpr uint32_t kLeaf = 1024u << kShift;      // a rotated child's leaf flag
   constexpr uint32_t TB = 8u << L;                 // bytes of one tree's heap
@@ -88,7 +92,7 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   const int g = wave * GPW + gi;
   const int64_t row = (int64_t)blockIdx.x * R + (MULTI ? (lane & (R - 1)) : lane);
   const bool row_ok = row < a.n_rows;
-  const uint32_t lane_off = tile_row_off<XL>(lane);
+  const uint32_t lane_off = tile_row_off<XL>(lane & (C - 1));
   const uint32_t wbuf = (uint32_t)a.lds_top_off + (uint32_t)(wave * GPW) * (U * TB);
   const uint32_t buf = wbuf + (uint32_t)gi * (U * TB);
   const int ga = (int)(((int64_t)T * g) / GT), gb = (int)(((int64_t)T * (g + 1)) / GT);
@@ -111,6 +115,8 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   if (NB > 0) copy_tops(0);
   const int waves = (int)(blockDim.x >> 6);
   if constexpr (XB != 4) load_row_bins16<XB>(a, lane_off, row, row_ok, wave, waves);
+  else if constexpr (C == 32)  // each half of a wave a part of its own
+    load_tile_any<4, FIN>(smem, a, lane & 31, row, row_ok, 2 * wave + (lane >> 5), 2 * waves);
   else if constexpr (MULTI) load_tile_any<4, FIN>(smem, a, lane, row, row_ok, wave, waves);
   else load_tile_all<4, FIN>(smem, a, lane, row, row_ok, wave, waves);
   __syncthreads();
@@ -299,11 +305,11 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
 }
 
 // ---------------------------------------------------------------------- launchers
-template <int L, int U, int XB, bool FIN, bool MULTI>
+template <int L, int U, int XB, bool FIN, bool MULTI, int C>
 static int launch_heap_luxfm(const LaunchArgs &a, int threads, int64_t n_wg, int lds_bytes,
                             void *stream) {
 #define BRIDGER_HEAP(LEAVES, VK, KS) \
-  launch_common(ragged_heap_kernel<L, U, LEAVES, XB, FIN, VK, KS, MULTI>, threads, n_wg, lds_bytes, stream, a)
+  launch_common(ragged_heap_kernel<L, U, LEAVES, XB, FIN, VK, KS, MULTI, C>, threads, n_wg, lds_bytes, stream, a)
   if (a.out_leaf) return BRIDGER_HEAP(true, 0, 0);
   if (a.vec && a.K <= 4) return BRIDGER_HEAP(false, 4, 0);
   if (a.vec && a.K <= 8) return BRIDGER_HEAP(false, 8, 0);
@@ -317,8 +323,11 @@ static int launch_heap_luxfm(const LaunchArgs &a, int threads, int64_t n_wg, int
 template <int L, int U, int XB, bool FIN>
 static int launch_heap_luxf(const LaunchArgs &a, int threads, int64_t n_wg, int lds_bytes,
                             void *stream) {
-  return a.heap_rows < 64 ? launch_heap_luxfm<L, U, XB, FIN, true>(a, threads, n_wg, lds_bytes, stream)
-                          : launch_heap_luxfm<L, U, XB, FIN, false>(a, threads, n_wg, lds_bytes, stream);
+  if constexpr (XB == 4)
+    if (a.rows_per_wg == 32)
+      return launch_heap_luxfm<L, U, XB, FIN, true, 32>(a, threads, n_wg, lds_bytes, stream);
+  return a.heap_rows < 64 ? launch_heap_luxfm<L, U, XB, FIN, true, 64>(a, threads, n_wg, lds_bytes, stream)
+                          : launch_heap_luxfm<L, U, XB, FIN, false, 64>(a, threads, n_wg, lds_bytes, stream);
 }
 
 template <int L, int U>

@@ -32,7 +32,7 @@ def walk_heaps(f, X, bins=None):
     top = top.reshape(-1, 1 << L, 2)
     assert not top[T:].any()
     flat = f.info()["max_depth"] <= L
-    s = 7 if binned else 8
+    s = 7 if binned or f.n_features > 576 else 8
     V = bins if binned else X
     rows = np.arange(n)
 
@@ -116,9 +116,50 @@ def test_heap_plan_fits(n_rows, features, bytes_):
     model = random_tiny_forest(rng, 40, features, max_depth=9)
     with B.Forest(model, host_only=True) as f:
         p = f.plan(n_rows)
-        assert p["rows_per_wg"] == 64 and 0 < p["lds_bytes"] <= 163840
-        groups = (p["lds_bytes"] - features * 64 * bytes_) // 2048  # 6 top levels: 2 KB a group
+        columns = 64 if features <= 576 else 32
+        assert p["rows_per_wg"] == columns and 0 < p["lds_bytes"] <= 163840
+        groups = (p["lds_bytes"] - features * columns * bytes_) // 2048  # 6 top levels: 2 KB a group
         assert groups in (1, 2, 4, 8, 16, 32, 64)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("F", [576, 577, 784, 1023])
+@pytest.mark.parametrize("waves,rows", [(0, 0), (1, 32), (8, 32), (4, 16), (8, 16)])
+def test_wide_rows(F, waves, rows, monkeypatch):
+    """Tiles of 64 and of 32 columns (above 576 features): dense rows, CSR rows, a scaler, leaf ids,
+    several classes and vector leaves."""
+    import dataclasses
+
+    import torch
+
+    from oracle import vector
+    if waves:
+        monkeypatch.setenv("BRIDGER_WAVES", str(waves))
+        monkeypatch.setenv("BRIDGER_HEAP_ROWS", str(rows))
+    rng = np.random.default_rng(F)
+    base = random_tiny_forest(rng, 70, F, max_depth=8, p_split=0.9)
+    models = [base, dataclasses.replace(base, n_classes=5, transform=XFORM_SOFTMAX), with_vector_leaves(base, 3, rng)]
+    n = 70
+    X = rng.standard_normal((n, F)).astype(np.float32)
+    X[rng.random((n, F)) < 0.5] = 0.0
+    mean, scale = rng.normal(0, 0.2, F), rng.uniform(0.8, 1.2, F)
+    Xs = ((X.astype(np.float64) - mean).astype(np.float32).astype(np.float64) / scale).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    nz = (Xd != 0)
+    csr = (torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), nz.sum(1).cumsum(0)]),
+           nz.nonzero()[:, 1].to(torch.int32), Xd[nz])
+    for model in models:
+        predict = vector.predict if model.value.ndim == 2 else \
+            (lambda m, x: oracle.predict(m, x, want_leaves=True)[:2])
+        ref, ref_lv = predict(model, X)
+        refs, _ = predict(model, Xs)
+        with B.Forest(model) as f:
+            print(f"F={F} {waves}x{rows} K={model.n_classes} plan {f.plan(n)}", flush=True)
+            assert_scores(f.predict(Xd).cpu().numpy(), ref, "dense")
+            assert_scores(f.predict_csr(*csr, n).cpu().numpy(), ref, "csr")
+            assert np.array_equal(f.predict_leaves(Xd).cpu().numpy(), ref_lv)
+            f.set_preprocess(B.BRIDGER_PRE_CENTER_SCALE, mean, scale)
+            assert_scores(f.predict(Xd).cpu().numpy(), refs, "scaled")
 
 
 @pytest.mark.gpu

@@ -242,7 +242,8 @@ bridger_status bridger_forest_predict_binned_leaves(bridger_forest_t h, const vo
  * every later predict, predict_leaves, predict_csr, predict_labels and bin on the
  * handle.  Call it with no prediction in flight on the handle (synchronous
  * upload).  BRIDGER_ERR_INVALID_ARGUMENT on an unknown kind or a missing array.
- * NORMALIZE runs a row-norm pass before the fused kernel, with n_rows doubles of
+ * NORMALIZE (but for the dense rows of ragged forests, whose kernel takes the norms from
+ * its row tile) runs a row-norm pass before the fused kernel, with n_rows doubles of
  * scratch taken from the device's default stream-ordered memory pool and returned
  * to it on the same stream after the kernel (BRIDGER_ERR_OUT_OF_MEMORY if the pool
  * cannot supply them).
@@ -347,7 +348,7 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
  * = f(n) << 8 | rotl(c0, 10) | rotl(c1, 21) with c = (f(c) | leaf(c) << 10) << 8; a leaf word is
  * the value's bits or, with vector leaves, the leaf's place among the leaf records; 16 the leaf id
  * of each leaf word, or of each block's two children, 17 and 18 as 14 and 15 for bins (ranks, and
- * 7 in place of 8; 7 in 14 and 15 too above 576 features).  *ptr stays valid until destroy or set_kernel.
+ * 7 in place of 8; 7 in 14 and 15 too above 256 features).  *ptr stays valid until destroy or set_kernel.
  */
 bridger_status bridger_forest_packed(bridger_forest_t h, int32_t which, const void **ptr,
                                      int64_t *bytes);

@@ -1484,7 +1484,7 @@ constexpr int64_t kHeapPerfectRows = int64_t(1) << 17, kHeapVectorRows = int64_t
                   kHeapLeafRows = int64_t(1) << 13;
 // Rows whose tile leaves PERFECT several lane groups a tile and few waves, or its records to be
 // read from global memory, take the heap walk in batches of any size (400,000 rows, 300 trees of
-// depth 6: 60 features 150 / 148, 90 159 / 206, 128 166 / 191, 300 319 / 567; 100 trees of depth
+// depth 6: 60 features 150 / 148, 90 159 / 206, 128 166 / 191; 100,000 rows, 300 75 / 147; 100 trees of depth
 // 8: 60 features (8 waves a CU) 79 / 130, 90 126 / 263, 128 97 / 218; 1000 trees of depth 8, 784
 // features, 10 classes: 100,000 rows 409 / 425, 300,000 1,158 / 1,202).
 constexpr int kHeapTileRowBytes = 256;  // of one row of the tile, from which that holds
@@ -1856,14 +1856,18 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   a.aggregate = h->aggregate;
   a.transform = h->transform;
   a.tile_coalesced = h->tile_coalesced ? 1 : 0;
+  const bool heaps = takes_heaps(h, n_rows, binned, out_leaf != nullptr);
   RowNorms norms;
   if (!binned) {
     set_preprocess_args(h, a);
-    if ((s = prepare_row_norms(h, a, stream, norms, norm_scratch)) != BRIDGER_OK) return s;
+    // (ragged forests on the padded-heap kernel: dense rows' norms come from its tile; the other
+    // families' contract is a row-norm pass with scratch of the pool)
+    if (heaps && h->kernel_active == kRagged && !csr && a.pre_kind == BRIDGER_PRE_NORMALIZE)
+      a.tile_norm = 1;
+    else if ((s = prepare_row_norms(h, a, stream, norms, norm_scratch)) != BRIDGER_OK) return s;
   }
   int err = 0;
   if (h->kernel_active == kPerfect || h->kernel_active == kRagged) {
-    const bool heaps = takes_heaps(h, n_rows, binned, out_leaf != nullptr);
     const bool perfect = h->kernel_active == kPerfect && !heaps;
     const bridger_forest::SizedPlan *sp = perfect ? sized_plan(h, n_rows, binned) : nullptr;
     const Plan &p = sp ? sp->plan

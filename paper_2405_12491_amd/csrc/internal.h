@@ -99,10 +99,14 @@ constexpr int kDeepMaxFeatures = 1024;
 // fields}, the grandchild of steps b1, b2 in slot 4m + 2 b1 + b2 of the next level.  v(c) is a
 // child's w, or a leaf child's leaf word: its value's bits, or (vector leaves) its row of the
 // class values.  A leaf n takes {0, v(n), v(n), both leaf flags}; slots below a leaf are zero and
-// never read.  fields, with s = log2 of the bytes of a feature's row of the tile (fp32: 8; bins,
-// or rows of more than kHeapWideFeatures features: 7): f(n) << s, and the 11 bits {f(c), leaf(c) << 10} of child c << s, rotated left by 10 (c0) or
+// never read.  fields, with s = log2 of the bytes of a feature's row of the tile (fp32: 8; bins, or
+// rows of more than kHeapWideFeatures features: 7): f(n) << s, and the 11 bits {f(c), leaf(c) <<
+// 10} of child c << s, rotated left by 10 (c0) or
 // 21 (c1) bits.  Feature indices below kDeepMaxFeatures.
-constexpr int kHeapWideFeatures = 576;  // a 64-column fp32 tile and 16 KB of copies fill the LDS
+// fp32 rows wider than this take tiles of 32 columns: two 64-column tiles with the copies of 16 lane
+// groups no longer fit a CU's LDS (us, 64 / 32 columns, 200 trees of depth 12: 200 features, 100,000 rows
+// 76 / 96; 300 features 124 / 99, 3,000 rows 10.4 / 9.9; 500 features 138 / 137, 12.2 / 10.1).
+constexpr int kHeapWideFeatures = 256;
 constexpr int heap_batch(int L) { return L == 7 ? 2 : 4; }  // trees a wave walks at once
 constexpr int heap_wave_bytes(int L) { return heap_batch(L) * (8 << L); }
 constexpr int kHeapClassRegs = 4;  // class sums of a lane group that the kernel keeps in registers
@@ -204,6 +208,7 @@ struct LaunchArgs {
   int32_t trees_in_order;      // kernel tree order is the caller's
   int32_t leaf_bfs;            // PERFECT: the caller numbers every tree's nodes breadth-first
   int32_t heap_rows;           // RAGGED heaps: rows of a lane group (the tile has 64 columns)
+  int32_t tile_norm;           // RAGGED heaps: NORMALIZE from the tile, no row_norm
   int32_t flat;                // RAGGED heaps: no tree deeper than the heaps, leaf words only
 };
 

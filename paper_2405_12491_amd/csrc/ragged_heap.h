@@ -67,8 +67,8 @@ __device__ __forceinline__ void load_row_bins16(const LaunchArgs &a, uint32_t la
 // class sums in registers / LDS (a leaf's word is then its row of leaf_vec).  KS: scalar leaves
 // of several classes: -1 class sums in LDS slots, else the sums of the (at most KS) classes that
 // a group's trees span in registers until the walk is done; 0: one class.
-// C: columns of the tile.  Rows too wide for 64 fp32 columns (above kHeapWideFeatures features) take
-// 32, with groups of 32 or 16 rows: the halves of a wave then read the same columns.
+// C: columns of the tile.  fp32 rows of more than kHeapWideFeatures features take 32, with groups of
+// 32 or 16 rows: the halves of a wave then read the same columns.
 template <int L, int U, bool LEAVES, int XB, bool FIN, int VK, int KS, bool MULTI, int C>
 __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -112,13 +112,51 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
             16, 0, 0);
     }
   };
-  if (NB > 0) copy_tops(0);
   const int waves = (int)(blockDim.x >> 6);
-  if constexpr (XB != 4) load_row_bins16<XB>(a, lane_off, row, row_ok, wave, waves);
-  else if constexpr (C == 32)  // each half of a wave a part of its own
-    load_tile_any<4, FIN>(smem, a, lane & 31, row, row_ok, 2 * wave + (lane >> 5), 2 * waves);
-  else if constexpr (MULTI) load_tile_any<4, FIN>(smem, a, lane, row, row_ok, wave, waves);
-  else load_tile_all<4, FIN>(smem, a, lane, row, row_ok, wave, waves);
+  // the tile's part of this lane: column col, part `part` of `parts` of its features
+  const int col = lane & (C - 1);
+  const int part = C == 32 ? 2 * wave + (lane >> 5) : wave, parts = C == 32 ? 2 * waves : waves;
+  auto load_tile = [&](auto nan_tag) {
+    constexpr bool NAN_TO_INF = decltype(nan_tag)::value;
+    if constexpr (MULTI) load_tile_any<4, NAN_TO_INF>(smem, a, col, row, row_ok, part, parts);
+    else load_tile_all<4, NAN_TO_INF>(smem, a, lane, row, row_ok, wave, waves);
+  };
+  if constexpr (XB != 4) {
+    if (NB > 0) copy_tops(0);
+    load_row_bins16<XB>(a, lane_off, row, row_ok, wave, waves);
+  } else if (a.tile_norm) {
+    // Normalizer: the rows as they are, each column's norm (one lane adds its squares in feature
+    // order, as the row-norm pass does; a float's square is exact in double), then the division.
+    // That pass, its scratch and their allocation cost a small batch 25 us.  The norms pass
+    // through the first copy buffer.
+    a.pre_kind = 0;
+    load_tile(std::false_type{});
+    __syncthreads();
+    double *norm = reinterpret_cast<double *>(smem + a.lds_top_off) + col;
+    if (wave == 0) {
+      double s = 0.0;
+#pragma unroll 8
+      for (int f = 0; f < a.F; ++f) {
+        const double x = (double)lds_f32(smem, (uint32_t)f * (4u * C) + lane_off);
+        s = s + x * x;
+      }
+      *norm = s == 0.0 ? 1.0 : __builtin_sqrt(s);
+    }
+    __syncthreads();
+    const double rn = *norm;
+    __syncthreads();
+    if (NB > 0) copy_tops(0);
+    const int f1 = (a.F * (part + 1)) / parts;
+    for (int f = (a.F * part) / parts; f < f1; ++f) {
+      __attribute__((address_space(3))) float *x =
+          (__attribute__((address_space(3))) float *)(uintptr_t)((uint32_t)f * (4u * C) + lane_off);
+      const float v = (float)((double)*x / rn);
+      *x = FIN && v != v ? __builtin_inff() : v;
+    }
+  } else {
+    if (NB > 0) copy_tops(0);
+    load_tile(std::integral_constant<bool, FIN>{});
+  }
   __syncthreads();
 
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(

@@ -32,7 +32,7 @@ def walk_heaps(f, X, bins=None):
     top = top.reshape(-1, 1 << L, 2)
     assert not top[T:].any()
     flat = f.info()["max_depth"] <= L
-    s = 7 if binned or f.n_features > 576 else 8
+    s = 7 if binned or f.n_features > 256 else 8
     V = bins if binned else X
     rows = np.arange(n)
 
@@ -116,17 +116,17 @@ def test_heap_plan_fits(n_rows, features, bytes_):
     model = random_tiny_forest(rng, 40, features, max_depth=9)
     with B.Forest(model, host_only=True) as f:
         p = f.plan(n_rows)
-        columns = 64 if features <= 576 else 32
+        columns = 64 if features <= 256 else 32
         assert p["rows_per_wg"] == columns and 0 < p["lds_bytes"] <= 163840
         groups = (p["lds_bytes"] - features * columns * bytes_) // 2048  # 6 top levels: 2 KB a group
         assert groups in (1, 2, 4, 8, 16, 32, 64)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("F", [576, 577, 784, 1023])
+@pytest.mark.parametrize("F", [256, 257, 577, 1023])
 @pytest.mark.parametrize("waves,rows", [(0, 0), (1, 32), (8, 32), (4, 16), (8, 16)])
 def test_wide_rows(F, waves, rows, monkeypatch):
-    """Tiles of 64 and of 32 columns (above 576 features): dense rows, CSR rows, a scaler, leaf ids,
+    """Tiles of 64 and of 32 columns (above 256 features): dense rows, CSR rows, a scaler, leaf ids,
     several classes and vector leaves."""
     import dataclasses
 
@@ -160,6 +160,35 @@ def test_wide_rows(F, waves, rows, monkeypatch):
             assert np.array_equal(f.predict_leaves(Xd).cpu().numpy(), ref_lv)
             f.set_preprocess(B.BRIDGER_PRE_CENTER_SCALE, mean, scale)
             assert_scores(f.predict(Xd).cpu().numpy(), refs, "scaled")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [0, 16, 32])
+@pytest.mark.parametrize("F", [1, 7, 28, 256, 300, 784])
+def test_normalizer_from_the_tile(F, rows, monkeypatch):
+    """The Normalizer inside the walk: every threshold is some row's normalized value, so a last-bit
+    error anywhere changes a leaf; a zero row, a NaN row and an infinite one among them."""
+    import torch
+
+    from oracle import preprocess as P
+    if rows:
+        monkeypatch.setenv("BRIDGER_HEAP_ROWS", str(rows))
+    rng = np.random.default_rng(F)
+    n = 150
+    X = (rng.standard_normal((n, F)) * np.exp(rng.standard_normal((n, 1)))).astype(np.float32)
+    X[3], X[5, 0], X[7, F - 1] = 0.0, np.nan, np.inf
+    with np.errstate(invalid="ignore"):
+        Xn = P.apply(P.NORMALIZE, None, None, X)
+    model = random_tiny_forest(rng, 40, F, max_depth=9, p_split=0.9)
+    pool = Xn[rng.integers(8, n, model.n_nodes), np.maximum(model.feature, 0)]
+    model.threshold[:] = np.where(model.left >= 0, pool, 0.0)
+    ref, ref_lv, _ = oracle.predict(model, Xn, want_leaves=True)
+    Xd = torch.from_numpy(X).cuda()
+    with B.Forest(model) as f:
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
+        f.set_preprocess(B.BRIDGER_PRE_NORMALIZE)
+        assert np.array_equal(f.predict_leaves(Xd).cpu().numpy(), ref_lv)
+        assert_scores(f.predict(Xd).cpu().numpy(), ref, f"normalized F={F}")
 
 
 @pytest.mark.gpu

@@ -152,6 +152,7 @@ struct bridger_forest {
     int copy;
   };
   std::vector<SizedPlan> perfect_sized, perfect_bsized;
+  SizedPlan perfect_leaves{}, perfect_bleaves{};  // leaf ids of large batches (plan.waves == 0: none)
   std::deque<TravCopy> perfect_copies, perfect_bcopies;
   // PERFECT deep blocks (layout in internal.h) below deep_tl top levels: thresholds' bits,
   // and ranks for bins; empty when the forest has more than kDeepMaxFeatures features
@@ -619,6 +620,7 @@ struct PlanInput {
   bool vec = false;        // vector leaves
   int32_t depth = 0;       // PERFECT: the trees' depth
   bool deep = false;       // PERFECT: deep blocks exist (wide-row plans may use them)
+  int32_t waves = 0, rows = 0;  // of the chunked plan, when given
 };
 
 // Smallest tile: bins pack 4 / x_bytes rows per 32-bit word and a half-wave's 32 rows must
@@ -633,8 +635,8 @@ Plan choose_plan(const PlanInput &in) {
   if (force_ilp == 1 || force_ilp == 2 || force_ilp == 4) ilps = {force_ilp};
   else if (in.perfect) ilps = {4, 2, 1};
   else ilps = {4};
-  const int force_waves = env_int("BRIDGER_WAVES", 0);
-  const int force_rows = env_int("BRIDGER_ROWS", 0);
+  const int force_waves = in.waves ? in.waves : env_int("BRIDGER_WAVES", 0);
+  const int force_rows = in.rows ? in.rows : env_int("BRIDGER_ROWS", 0);
   const int force_ct = env_int("BRIDGER_CHUNK_TREES", 0);
   const int force_wg_per_cu = env_int("BRIDGER_WG_PER_CU", 0);
   const int64_t n = std::max<int64_t>(in.n_rows, 1);
@@ -1184,23 +1186,37 @@ void build_sized_plans(bridger_forest *h, PlanInput pin, const Plan &big, bool b
   sized.clear();
   copies.clear();
   if (env_int("BRIDGER_SIZED_PLANS", 1) == 0) return;
+  auto copy_for = [&](const Plan &p) {  // the traversal copy of a plan's row tile
+    if (p.rows_per_wg == big.rows_per_wg) return -1;
+    for (size_t i = 0; i < copies.size(); ++i)
+      if (copies[i].R == p.rows_per_wg) return (int)i;
+    copies.emplace_back();
+    copies.back().R = p.rows_per_wg;
+    if (binned) make_perfect_btrav(h, p.rows_per_wg, copies.back().trav, copies.back().roots);
+    else make_perfect_trav(h, p.rows_per_wg, copies.back().trav, copies.back().roots);
+    return (int)copies.size() - 1;
+  };
   for (const int64_t n : kSizeClasses) {
     pin.n_rows = n;
     const Plan p = pick_plan(pin);
     if (p.waves == 0 || same_plan(p, big)) continue;
-    int copy = -1;
-    if (p.rows_per_wg != big.rows_per_wg) {
-      for (size_t i = 0; i < copies.size(); ++i)
-        if (copies[i].R == p.rows_per_wg) copy = (int)i;
-      if (copy < 0) {
-        copies.emplace_back();
-        copies.back().R = p.rows_per_wg;
-        if (binned) make_perfect_btrav(h, p.rows_per_wg, copies.back().trav, copies.back().roots);
-        else make_perfect_trav(h, p.rows_per_wg, copies.back().trav, copies.back().roots);
-        copy = (int)copies.size() - 1;
-      }
-    }
+    const int copy = copy_for(p);
     sized.push_back({n, p, copy});
+  }
+  // Leaf ids of large batches, trees of at most 6 levels: with one lane group a row's ids come 16
+  // trees at a time and its lines reach memory in pieces (1.55x the bytes); four lane groups take
+  // consecutive trees of a chunk, so that a row's 64 bytes are written at once by four waves.  200k x
+  // 28 rows: 500 trees of depth 6 258 -> 207 us, 300 of depth 4 167 -> 86; with deeper trees the
+  // chunks that four groups need cost the walk more (100 of depth 8: 53 -> 77).
+  if (big.groups == 1 && pin.depth <= 6 && env_int("BRIDGER_WAVES", 0) == 0 && env_int("BRIDGER_ROWS", 0) == 0) {
+    pin.n_rows = int64_t(1) << 20;
+    pin.waves = 8;
+    pin.rows = 128;
+    const Plan p = choose_plan(pin);
+    if (p.waves && p.ilp == 4) {
+      const int copy = copy_for(p);
+      (binned ? h->perfect_bleaves : h->perfect_leaves) = {INT64_MAX, p, copy};
+    }
   }
 }
 
@@ -1870,6 +1886,8 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   if (h->kernel_active == kPerfect || h->kernel_active == kRagged) {
     const bool perfect = h->kernel_active == kPerfect && !heaps;
     const bridger_forest::SizedPlan *sp = perfect ? sized_plan(h, n_rows, binned) : nullptr;
+    const auto &leaves = binned ? h->perfect_bleaves : h->perfect_leaves;
+    if (perfect && out_leaf && leaves.plan.waves && (!sp || sp->plan.groups == 1)) sp = &leaves;
     const Plan &p = sp ? sp->plan
                        : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
                        : heaps   ? choose_heap_plan(h, n_rows, binned)

@@ -1206,7 +1206,7 @@ void build_sized_plans(bridger_forest *h, PlanInput pin, const Plan &big, bool b
   // Leaf ids of large batches, trees of at most 6 levels: with one lane group a row's ids come 16
   // trees at a time and its lines reach memory in pieces (1.55x the bytes); four lane groups take
   // consecutive trees of a chunk, so that a row's 64 bytes are written at once by four waves.  200k x
-  // 28 rows: 500 trees of depth 6 258 -> 207 us, 300 of depth 4 167 -> 86; with deeper trees the
+  // 28 rows: 500 trees of depth 6 258 -> 219 us, 300 of depth 4 167 -> 86; with deeper trees the
   // chunks that four groups need cost the walk more (100 of depth 8: 53 -> 77).
   if (big.groups == 1 && pin.depth <= 6 && env_int("BRIDGER_WAVES", 0) == 0 && env_int("BRIDGER_ROWS", 0) == 0) {
     pin.n_rows = int64_t(1) << 20;
@@ -1452,10 +1452,18 @@ Plan heap_plan(const bridger_forest *h, int R, int W, bool binned) {
 //     waits for is one group's chain (500 trees of depth 6, 1,000 rows: 9.8 us with 16-row groups,
 //     10.8 with 32, 14.1 with 64; 100 trees of depth 12, 3,001 rows: 7.3, 8.6, 9.7).  With more
 //     tiles than CUs the wave-uniform groups of 64 rows win (10,000 rows: 14.3 us, 16.9 with 32).
+//   * Waves without a tree still load their part of the row tile: 4 waves at least, 8 from
+//     kHeapLoadFeatures features (one tree of depth 6, us, 1 / 4 / 8 waves: 28 features, 10,000 rows 5.1 / 3.8
+//     / 3.9, 50,000 5.5 / 4.6 / 5.4; 90 features, 10,000 rows 12.8 / 5.5 / 5.1, 120,000 68 / 44 / 31; 8 trees, 90
+//     features, 1,000 rows 12.2 / 6.1 / 5.8).  On narrower rows waves beyond the trees of one batch only
+//     add to the launch (16 trees of depth 6, 28 features, 50,000 rows: 16 waves 10.6, 4 waves 5.2).
 //   * Else groups of 64 rows (32 in a 32-column tile), and the W that puts the most waves on the chip; the fewest of equals
 //     (1M x 28 rows, 100 trees of depth 12: W = 2 0.225 ms, 4 0.236, 8 0.261).
+constexpr int kHeapLoadFeatures = 64;
+
 const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
   const int U = heap_batch(h->heap_levels);
+  const int load_waves = h->F < kHeapLoadFeatures ? 4 : 8;
   n_rows = std::max<int64_t>(n_rows, 1);
   for (int R : {16, 32}) {
     const int gpw = 64 / R;
@@ -1463,7 +1471,7 @@ const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binne
     const Plan *best = nullptr;
     int fewest = INT32_MAX;
     for (int W : {1, 2, 4, 8, 16}) {
-      if (h->heap_waves && W != h->heap_waves) continue;
+      if (h->heap_waves ? W != h->heap_waves : W < 4) continue;
       const int groups = W * gpw, batches = ((h->n_trees + groups - 1) / groups + U - 1) / U;
       const Plan &p = h->heap_plans[binned][ilog2(gpw)][ilog2(W)];
       if (!p.waves || batches >= fewest) continue;
@@ -1477,7 +1485,11 @@ const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binne
   const int R = heap_columns(h, binned);
   int64_t most = 0;
   for (int W : {1, 2, 4, 8, 16}) {
-    if (h->heap_waves ? W != h->heap_waves : W * (64 / R) > h->n_trees && W > 1) continue;
+    const int gpw = 64 / R;
+    if (h->heap_waves ? W != h->heap_waves
+                      : W > load_waves && (W * gpw > h->n_trees ||
+                                           (h->F < kHeapLoadFeatures && W / 2 * gpw * U >= h->n_trees)))
+      continue;
     const Plan &p = h->heap_plans[binned][ilog2(64 / R)][ilog2(W)];
     if (!p.waves) continue;
     const int64_t active = std::min<int64_t>((n_rows + R - 1) / R * W, (int64_t)kNumCUs * p.waves_per_cu);
@@ -1503,6 +1515,11 @@ constexpr int64_t kHeapPerfectRows = int64_t(1) << 17, kHeapVectorRows = int64_t
 // depth 6: 60 features 150 / 148, 90 159 / 206, 128 166 / 191; 100,000 rows, 300 75 / 147; 100 trees of depth
 // 8: 60 features (8 waves a CU) 79 / 130, 90 126 / 263, 128 97 / 218; 1000 trees of depth 8, 784
 // features, 10 classes: 100,000 rows 409 / 425, 300,000 1,158 / 1,202).
+// Forests of few leaves stay with PERFECT, whose one or two chunks take no time to stage (us, heap walk with
+// its best waves / PERFECT, 28 features, 10,000 and 120,000 rows: 1 tree of depth 8 4.2 6.7 / 4.1 3.8; 8 of depth 6
+// 4.0 7.0 / 4.3 4.4; 16 of depth 6 4.0 7.0 / 4.4 5.7; 16 of depth 8 4.5 8.3 / 5.5 7.2; 90 features: 1 of depth 6 5.1 31
+// / 5.2 27, 16 of depth 8 6.1 34 / 6.6 46).
+constexpr int64_t kHeapLeaves = 1024;
 constexpr int kHeapTileRowBytes = 256;  // of one row of the tile, from which that holds
 
 bool perfect_heap_wanted() {
@@ -1520,6 +1537,7 @@ bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leav
   if (!(binned ? h->heap_bok : h->heap_ok)) return false;
   if (h->kernel_active == kRagged) return true;
   if (h->kernel_active != kPerfect || !h->kernel_auto || !h->perfect_heap) return false;
+  if ((int64_t)h->n_trees << h->perfect_depth <= kHeapLeaves) return false;
   if (leaves) return n_rows <= kHeapLeafRows;
   const Plan &p = binned ? h->perfect_bplan : h->perfect_plan;
   const int row_bytes = h->F * (binned ? h->bin_bytes : 4);

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void direct_kernel(LaunchArgs a) {
 // leaves in LDS and after the batch's barrier one wave adds the batch to the class sums, tree by
 // tree (vector leaves: one wave per four classes), while the others walk the next batch.
 // 64 trees grown on 20,000 rows, 51,630 x 90 rows: 655 us with one row and one tree per lane (three
-// waves a CU, 16-byte records, features from global memory); this kernel: 110 us.
+// waves a CU, 16-byte records, features from global memory); this kernel: 156 us.
 template <bool LEAVES, bool VEC>
 __global__ __launch_bounds__(1024) void direct_tile_kernel(LaunchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];

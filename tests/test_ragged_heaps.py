@@ -198,7 +198,7 @@ def test_perfect_small_batches(n_rows):
     64-row groups, then the PERFECT kernels): the explicit PERFECT kernel's outputs."""
     import torch
     rng = np.random.default_rng(n_rows)
-    for D, K, T in ((3, 1, 9), (6, 3, 70), (8, 1, 40)):
+    for D, K, T in ((3, 1, 129), (3, 1, 128), (6, 3, 70), (8, 1, 40)):  # above and at 1,024 leaves
         trees = [perfect_tree_arrays(D, rng.integers(0, 10, (1 << D) - 1),
                                      rng.standard_normal((1 << D) - 1).astype(np.float32),
                                      rng.standard_normal(1 << D).astype(np.float32)) for _ in range(T)]
@@ -209,13 +209,34 @@ def test_perfect_small_batches(n_rows):
             assert f.kernel == B.BRIDGER_KERNEL_PERFECT
             q = f.bin(X)
             got = [f.predict(X), f.predict_binned(q), f.predict_labels(X), f.predict_leaves(X)]
-            assert (f.plan(n_rows)["chunk_bytes"] == 0) == (n_rows <= 131072)
+            assert (f.plan(n_rows)["chunk_bytes"] == 0) == (n_rows <= 131072 and T << D > 1024)
             f.kernel = B.BRIDGER_KERNEL_PERFECT
             ref = [f.predict(X), f.predict_binned(q), f.predict_labels(X), f.predict_leaves(X)]
             assert f.plan(n_rows)["chunk_bytes"] > 0
         for g, r in zip(got[:2], ref[:2]):  # double sums in another order, rounded once
             assert torch.allclose(g, r, rtol=2.4e-7, atol=1e-7)
         assert torch.equal(got[2], ref[2]) and torch.equal(got[3], ref[3])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("F", [28, 63, 64, 300])
+@pytest.mark.parametrize("T", [1, 3, 16, 17])
+def test_few_trees(T, F):
+    """Ragged forests with fewer trees than waves that load the row tile, around the batch sizes where
+    the lane groups change, against the oracle."""
+    import torch
+    rng = np.random.default_rng(100 * T + F)
+    model = random_tiny_forest(rng, T, F, max_depth=9, p_split=0.9)
+    X = rng.standard_normal((8193, F)).astype(np.float32)
+    ref, ref_lv, _ = oracle.predict(model, X, want_leaves=True)
+    Xd = torch.from_numpy(X).cuda()
+    with B.Forest(model) as f:
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
+        for n in (1, 4097, 8193):
+            what = f"F={F} T={T} rows={n} plan {f.plan(n)}"
+            print(what, flush=True)
+            assert_scores(f.predict(Xd[:n]).cpu().numpy(), ref[:n], what)
+            assert np.array_equal(f.predict_leaves(Xd[:n]).cpu().numpy(), ref_lv[:n]), what
 
 
 @pytest.mark.gpu

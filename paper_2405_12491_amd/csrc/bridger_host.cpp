@@ -1519,7 +1519,10 @@ constexpr int64_t kHeapPerfectRows = int64_t(1) << 17, kHeapVectorRows = int64_t
 // its best waves / PERFECT, 28 features, 10,000 and 120,000 rows: 1 tree of depth 8 4.2 6.7 / 4.1 3.8; 8 of depth 6
 // 4.0 7.0 / 4.3 4.4; 16 of depth 6 4.0 7.0 / 4.4 5.7; 16 of depth 8 4.5 8.3 / 5.5 7.2; 90 features: 1 of depth 6 5.1 31
 // / 5.2 27, 16 of depth 8 6.1 34 / 6.6 46).
-constexpr int64_t kHeapLeaves = 1024;
+// On rows of kHeapLoadFeatures features or more a small batch waits for the tile, and the walk's many lane groups
+// each load their own: up to 4,096 leaves there (1,000 rows: 90 features, 32 trees of depth 6 6.3 / 4.9, 64
+// 6.3 / 5.5, 16 of depth 8 6.8 / 5.6, but 32 of depth 8 6.8 / 7.2; 10,000 rows, 16 of depth 8 6.1 / 6.6).
+constexpr int64_t kHeapLeaves = 1024, kHeapTileLeaves = 4096, kHeapTileRows = 4096;
 constexpr int kHeapTileRowBytes = 256;  // of one row of the tile, from which that holds
 
 bool perfect_heap_wanted() {
@@ -1537,7 +1540,8 @@ bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leav
   if (!(binned ? h->heap_bok : h->heap_ok)) return false;
   if (h->kernel_active == kRagged) return true;
   if (h->kernel_active != kPerfect || !h->kernel_auto || !h->perfect_heap) return false;
-  if ((int64_t)h->n_trees << h->perfect_depth <= kHeapLeaves) return false;
+  const bool few_rows = h->F >= kHeapLoadFeatures && n_rows <= kHeapTileRows;
+  if ((int64_t)h->n_trees << h->perfect_depth <= (few_rows ? kHeapTileLeaves : kHeapLeaves)) return false;
   if (leaves) return n_rows <= kHeapLeafRows;
   const Plan &p = binned ? h->perfect_bplan : h->perfect_plan;
   const int row_bytes = h->F * (binned ? h->bin_bytes : 4);

@@ -307,8 +307,7 @@ bridger_status bridger_forest_get_kernel(bridger_forest_t h, int32_t *kernel);
 
 /*
  * The launch plan predict would use for n_rows rows (the Eq. 1 choice):
- * rows per workgroup (columns of its LDS tile: the ragged walk of a small batch holds a row in
- * several), bytes of one LDS tree-chunk buffer, trees per chunk (0 when
+ * rows per workgroup, bytes of one LDS tree-chunk buffer, trees per chunk (0 when
  * chunks hold a varying number of trees), number of chunks, LDS bytes per
  * workgroup, and the modelled bytes moved per level (HBM, L2->LDS staging, LDS
  * reads).  Any output pointer may be NULL.  Works on host-only handles.

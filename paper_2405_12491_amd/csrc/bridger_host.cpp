@@ -2599,7 +2599,6 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
   double forest_bytes = 0;
   if (takes_heaps(h, n_rows, false, false)) {
     p = choose_heap_plan(h, n_rows, false);
-    p.rows_per_wg = heap_columns(h, false);  // the tile's columns; a small batch holds a row in several of them
     forest_bytes = 8.0 * h->ragged_rec.size();
   } else if (h->kernel_active == kPerfect) {
     const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, false);

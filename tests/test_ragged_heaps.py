@@ -108,18 +108,26 @@ def test_heap_layout_vector_leaves():
         assert np.array_equal(node[got], lv)
 
 
-@pytest.mark.parametrize("n_rows,features,bytes_", [(1, 28, 4), (3001, 28, 4), (10**6, 28, 4), (10**6, 256, 4),
-                                                    (5000, 600, 4)])
-def test_heap_plan_fits(n_rows, features, bytes_):
-    """Every batch size gets a plan within a CU's LDS: a 64-column tile and a heap copy per lane group."""
+@pytest.mark.parametrize("n_rows,features,rows", [(1, 28, 16), (3001, 28, 16), (4096, 28, 16), (4097, 28, 32),
+                                                  (8192, 28, 32), (8193, 28, 64), (10**6, 28, 64), (10**6, 256, 64),
+                                                  (3000, 600, 16), (5000, 600, 32), (10**6, 600, 32)])
+def test_heap_plan_fits(n_rows, features, rows):
+    """Every batch size gets a plan within a CU's LDS: a tile of 64 columns (32 above 256 features) and a
+    heap copy per lane group.  The rows of a workgroup reported are those it takes, 16 or 32 in a small
+    batch however many columns the tile has, and the bytes count its workgroups."""
     rng = np.random.default_rng(3)
     model = random_tiny_forest(rng, 40, features, max_depth=9)
     with B.Forest(model, host_only=True) as f:
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
         p = f.plan(n_rows)
         columns = 64 if features <= 256 else 32
-        assert p["rows_per_wg"] == columns and 0 < p["lds_bytes"] <= 163840
-        groups = (p["lds_bytes"] - features * columns * bytes_) // 2048  # 6 top levels: 2 KB a group
+        assert p["rows_per_wg"] == rows and 0 < p["lds_bytes"] <= 163840
+        groups = (p["lds_bytes"] - features * columns * 4) // 2048  # 6 top levels: 2 KB a group
         assert groups in (1, 2, 4, 8, 16, 32, 64)
+        staged = B.bridger_forest_packed(f.handle, 0, np.uint8).size / 4.0  # per workgroup
+        big = 1 << 20
+        walk = (f.plan(big)["lds_read_bytes"] - big // columns * staged) / big  # per row
+        assert p["lds_read_bytes"] == pytest.approx(n_rows * walk + -(-n_rows // rows) * staged)
 
 
 @pytest.mark.gpu

@@ -2675,8 +2675,10 @@ bridger_status bridger_forest_packed(bridger_forest_t h, int32_t which, const vo
           if (h->treelets.empty() && !make_treelets(h, h->ragged_rec, h->treelets, h->treelet_start,
                                                     &h->treelet_leaf))
             h->treelets.clear();
+          // (the slots are the same: the array handed out before is not written again)
+          std::vector<int32_t> start;
           if (which == 13 && h->heap_bok && h->btreelets.empty() &&
-              !make_treelets(h, h->ragged_brec, h->btreelets, h->treelet_start, nullptr))
+              !make_treelets(h, h->ragged_brec, h->btreelets, start, nullptr))
             h->btreelets.clear();
         } catch (const std::bad_alloc &) {
           return fail(BRIDGER_ERR_OUT_OF_MEMORY, "host allocation failed");

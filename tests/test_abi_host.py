@@ -641,3 +641,33 @@ def test_ragged_treelets(seed):
         lv, vals = walk_treelets(f, X, bins=bins)
         assert np.array_equal(lv, ref_lv)
         assert np.array_equal(vals, ref_val)
+
+
+def test_views_handed_out_stay_as_they_are():
+    """*ptr of a packed array stays valid until destroy or set_kernel: asking for the treelets of bins
+    (13) does not touch the slots (11) that another thread is reading."""
+    import threading
+    rng = np.random.default_rng(11)
+    model = random_tiny_forest(rng, 30_000, 5, max_depth=3, p_split=0.8)
+    with host(model) as f:
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
+        p, n = ctypes.c_void_p(), ctypes.c_int64()
+        lib = B.load_library()
+        assert lib.bridger_forest_packed(f.handle, 11, ctypes.byref(p), ctypes.byref(n)) == 0
+        view = np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_int32)), (n.value // 4,))
+        first, stop, changed = view.copy(), threading.Event(), []
+        started = threading.Event()
+
+        def read():
+            while not stop.is_set():
+                if not np.array_equal(view, first):
+                    changed.append(1)
+                started.set()
+
+        t = threading.Thread(target=read)
+        t.start()
+        started.wait()
+        assert lib.bridger_forest_packed(f.handle, 13, ctypes.byref(p), ctypes.byref(n)) == 0
+        stop.set()
+        t.join()
+        assert not changed and np.array_equal(view, first)

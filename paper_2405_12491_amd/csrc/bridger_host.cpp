@@ -174,7 +174,7 @@ struct bridger_forest {
   bool heap_ok = false, heap_bok = false;
   int32_t heap_levels = 0;  // L
   bool heap_flat = false;   // no tree deeper than L
-  int32_t heap_waves = 0;   // BRIDGER_WAVES at create
+  int32_t heap_waves = 0;   // BRIDGER_HEAP_WAVES (the padded-heap walk alone) or BRIDGER_WAVES at create
   int32_t heap_rows = 0;    // BRIDGER_HEAP_ROWS at create
   Plan heap_plans[2][3][5] = {};  // [binned][64, 32 or 16 rows][1, 2, 4, 8 or 16 waves]; waves 0: none
   int32_t heap_span[7] = {};  // most classes a lane group's trees span, of 1, 2, 4 .. 64 groups
@@ -2263,7 +2263,7 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
       if (h->ragged_ok && heaps_wanted(h)) {
         h->heap_levels = heap_top_levels(h->max_depth);
         h->heap_flat = h->max_depth <= h->heap_levels;
-        h->heap_waves = env_int("BRIDGER_WAVES", 0);
+        h->heap_waves = env_int("BRIDGER_HEAP_WAVES", env_int("BRIDGER_WAVES", 0));
         h->heap_rows = env_int("BRIDGER_HEAP_ROWS", 0);
         for (int i = 0; i < 7; ++i) h->heap_span[i] = class_span(h, 1 << i);
         for (int b = 0; b < 2; ++b)

@@ -259,7 +259,8 @@ def test_heap_kernel(depth, waves, rows, monkeypatch):
     import torch
 
     from oracle import vector
-    monkeypatch.setenv("BRIDGER_WAVES", str(waves))
+    # (this walk's waves alone: a record plan of one wave has no 128-row tile for 8-bit bins)
+    monkeypatch.setenv("BRIDGER_HEAP_WAVES", str(waves))
     monkeypatch.setenv("BRIDGER_HEAP_ROWS", str(rows))
     rng = np.random.default_rng(900 + depth)
     F = 7 if depth % 2 else 12
@@ -287,13 +288,42 @@ def test_heap_kernel(depth, waves, rows, monkeypatch):
                 q = f.bin(Xd)
                 idx = np.tile(np.arange(F, dtype=np.int32), n)
                 csr = (torch.arange(0, n * F + 1, F).cuda(), torch.from_numpy(idx).cuda(), Xd.reshape(-1))
-                outs = [f.predict(Xd), f.predict_csr(*csr, n)]
-                lvs = [f.predict_leaves(Xd), f.predict_csr(*csr, n, leaves=True)]
-                if waves != 1:  # a record plan of one wave has no 128-row tile for 8-bit bins
-                    outs.append(f.predict_binned(q))
-                    lvs.append(f.predict_binned_leaves(q))
+                outs = [f.predict(Xd), f.predict_csr(*csr, n), f.predict_binned(q)]
+                lvs = [f.predict_leaves(Xd), f.predict_csr(*csr, n, leaves=True), f.predict_binned_leaves(q)]
                 torch.cuda.synchronize()
             for o in outs:
                 assert_scores(o.cpu().numpy(), ref, what)
             for l in lvs:
                 assert np.array_equal(l.cpu().numpy(), ref_lv), what
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", [8, 16])
+@pytest.mark.parametrize("depth", [6, 9, 10])
+def test_binned_tables(depth, bits):
+    """Bins of a whole table of narrow rows, in the plan that the walk takes by itself there (one wave
+    of 64 rows a workgroup): scores and leaf ids, 8- and 16-bit bins, one class, several, vector leaves."""
+    import dataclasses
+
+    import torch
+
+    from oracle import vector
+    rng = np.random.default_rng(10 * depth + bits)
+    F, n = 3, (1 << 19) + 77
+    base = random_tiny_forest(rng, 12 if bits == 8 else 30, F, max_depth=depth, p_split=0.95,
+                              thr_grid=GRID if bits == 8 else None)
+    X = rng.choice(VALUES[:7], (n, F)) if bits == 8 else rng.standard_normal((n, F)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    for model in (base, dataclasses.replace(base, n_classes=3, transform=XFORM_SOFTMAX), with_vector_leaves(base, 7, rng)):
+        if model.value.ndim == 2:
+            ref, ref_lv = vector.predict(model, X, threads=8)
+        else:
+            ref, ref_lv, _ = oracle.predict(model, X, want_leaves=True, threads=8)
+        with B.Forest(model) as f:
+            f.kernel = B.BRIDGER_KERNEL_RAGGED
+            q = f.bin(Xd)
+            what = f"depth {depth} {q.dtype} K {model.n_classes}"
+            print(what, flush=True)
+            assert q.element_size() * 8 == bits
+            assert_scores(f.predict_binned(q).cpu().numpy(), ref, what)
+            assert np.array_equal(f.predict_binned_leaves(q).cpu().numpy(), ref_lv), what

@@ -204,6 +204,7 @@ struct bridger_forest {
   std::vector<int32_t> direct_rec_node;
   // its pair records (layout in internal.h), for the forests that the tile kernel serves
   bool pair_ok = false;
+  int32_t direct_tile = -1;  // BRIDGER_DIRECT_TILE at create: 0 no pair records, 1 always the tile, 2 never
   std::vector<uint64_t> pair_rec;
   std::vector<int32_t> pair_start, pair_node;  // per tree the first record; caller's node id
   std::vector<float> vec_pair;                 // vector leaves: the leaves' class rows
@@ -1574,6 +1575,24 @@ Plan choose_direct_plan(const bridger_forest *h, int64_t n_rows) {
   return best;
 }
 
+// Whether DIRECT walks pair records over an LDS tile, or row by row.  The tile pays where many trees
+// share it: it reads every feature of a row, row by row only those on the row's paths.  Trees grown on
+// 20,000 rows, us, tile / row by row / row by row on 16-byte records: 1 tree: 10,000 x 28 rows 11 / 8 / 9,
+// 10,000 x 256 26 / 9 / 9, 100,000 x 600 530 / 33 / 34; 3 trees, 100,000 rows: 63 features 40 / 58 / 64, 90 71 /
+// 48 / 58; 6 trees, 1,000 x 600 29 / 41 / 43; 8 trees, 100,000 rows: 256 features 115 / 176 / 199, 400 251 / 213
+// / 227.  From 12 trees the tile won everywhere (1.3 to 22 times).  Large tables: the limit is lower where one
+// tile fills a CU's LDS, and higher for rows of two lines that are read whole either way (1 tree, 300,000 x 48
+// 41 / 63 / 69, 300,000 x 28 32 / 30 / 37).  aligned: rows that the tile is filled from by whole lines.
+bool takes_direct_tile(const bridger_forest *h, int64_t n_rows, bool aligned) {
+  if (!h->pair_ok) return false;
+  if (h->direct_tile >= 0) return h->direct_tile == 1;
+  const int64_t T = h->n_trees, F = h->F, pairs = T * T - 1;
+  if (T >= 12) return true;
+  if (n_rows < 32768) return T >= 6 || F <= (aligned ? 20 : 12) * pairs;
+  if (aligned && T < 4 && F >= 32 && F <= 64 * T && n_rows * F * 4 > 56000000) return true;
+  return F <= (aligned ? std::min(20 * pairs, 48 * T) : std::min(9 * pairs, 36 * T));
+}
+
 // RAGGED records for bins: an internal record's threshold becomes its rank.
 void build_ragged_brec(bridger_forest *h) {
   h->ragged_brec = h->ragged_rec;
@@ -2023,7 +2042,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
     a.leaf_map = (const int32_t *)h->d_direct.leaf_map;
     a.vec = h->vec ? 1 : 0;
     a.leaf_vec = (const float *)(h->pair_ok ? h->d_vec_pair : h->d_vec_direct);
-    if (h->pair_ok) {
+    if (takes_direct_tile(h, n_rows, a.x_vec4 != 0)) {
       const Plan p = choose_direct_plan(h, n_rows);
       a.rows_per_wg = 64;
       a.groups = p.groups;
@@ -2031,7 +2050,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
       a.lds_acc_off = a.lds_top_off + 2 * p.waves * kDirectBatch * 64 * 4;
       err = launch_direct_tile(a, p.waves, (n_rows + 63) / 64, p.lds_bytes, stream);
     } else {
-      err = launch_direct(a, (n_rows + 255) / 256, stream);
+      err = launch_direct(a, h->pair_ok, (n_rows + 255) / 256, stream);
     }
   }
   if (err != 0)
@@ -2311,9 +2330,9 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
         }
       }
     }
-    // the forests that only DIRECT can take (BRIDGER_DIRECT_TILE=1: any; 0: none)
-    const int pairs = env_int("BRIDGER_DIRECT_TILE", -1);
-    if ((pairs == 1 || (pairs != 0 && resolve_auto(h) == kDirect)) &&
+    // the forests that only DIRECT can take (BRIDGER_DIRECT_TILE=1 or 2: any; 0: none)
+    h->direct_tile = env_int("BRIDGER_DIRECT_TILE", -1);
+    if ((h->direct_tile > 0 || (h->direct_tile != 0 && resolve_auto(h) == kDirect)) &&
         choose_direct_plan(h, 1 << 20).waves > 0)
       h->pair_ok = make_pair_records(h);
     if (vec) build_vector_leaves(h, tree_offsets, left, value_vec);
@@ -2612,7 +2631,7 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
     p.waves = 4;
     forest_bytes = (double)h->perfect_blob.size();
   } else {
-    if (h->pair_ok) {
+    if (takes_direct_tile(h, n_rows, h->F % 4 == 0)) {
       p = choose_direct_plan(h, n_rows);
     } else {
       p.rows_per_wg = 256;

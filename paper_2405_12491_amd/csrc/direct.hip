@@ -8,7 +8,8 @@ namespace bridger {
 // ======================================================================== DIRECT
 // Fallback for any forest: one row per lane, nodes and features read from global memory.
 // VK: 0 scalar leaves; 4 or 8 (K <= VK) or 64 vector leaves (class sums in registers / LDS).
-template <bool LEAVES, int VK = 0>
+// PAIR: pair records (layout in internal.h), else the 16-byte ones.
+template <bool LEAVES, int VK = 0, bool PAIR = false>
 __global__ __launch_bounds__(256) void direct_kernel(LaunchArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr bool VK_REG = VK == 4 || VK == 8;  // vector leaves, class sums in registers
@@ -17,7 +18,6 @@ __global__ __launch_bounds__(256) void direct_kernel(LaunchArgs a) {
   const bool row_ok = row < a.n_rows;
   const int64_t rr = row_ok ? row : 0;
   const float *xr = a.X + rr * (int64_t)a.F;
-  const int4 *recs = reinterpret_cast<const int4 *>(a.nodes);
   const int T = a.n_trees;
   double *acc_lds = reinterpret_cast<double *>(smem) + threadIdx.x;
   const int slot_stride = blockDim.x;
@@ -28,23 +28,38 @@ __global__ __launch_bounds__(256) void direct_kernel(LaunchArgs a) {
   double vacc[VR];
   if (VK_REG) vec_init_reg(a, vacc, true);
   if (VK == 64) vec_init(a, acc_lds, slot_stride, true);
+  auto feature = [&](int f) { return a.pre_kind ? preprocess(a, f, rr, xr[f]) : xr[f]; };
   for (int t = 0; t < T; ++t) {
-    int n = a.tree_start[t];
-    int4 rc = recs[n];
-    while (rc.y >= 0) {
-      const float xv = a.pre_kind ? preprocess(a, rc.y, rr, xr[rc.y]) : xr[rc.y];
-      n = (xv <= __int_as_float(rc.x)) ? rc.z : rc.w;
-      rc = recs[n];
+    int64_t n = a.tree_start[t];  // record of the leaf
+    uint32_t word;                // its value, or (PAIR, vector leaves) its row of class values
+    if constexpr (PAIR) {
+      const uint2 *recs = reinterpret_cast<const uint2 *>(a.nodes) + n;
+      uint32_t i = 0;
+      uint2 rc = recs[0];
+      while (!(rc.y & kPairLeaf)) {
+        i += (rc.y >> kPairRelShift) + (feature((int)(rc.y & 1023u)) <= __uint_as_float(rc.x) ? 0u : 1u);
+        rc = recs[i];
+      }
+      n += i;
+      word = rc.x;
+    } else {
+      const int4 *recs = reinterpret_cast<const int4 *>(a.nodes);
+      int4 rc = recs[n];
+      while (rc.y >= 0) {
+        n = (feature(rc.y) <= __int_as_float(rc.x)) ? rc.z : rc.w;
+        rc = recs[n];
+      }
+      word = (uint32_t)rc.x;
     }
     if (LEAVES) {
       if (row_ok) a.out_leaf[row * (int64_t)T + a.tree_order[t]] = a.leaf_map[n];
     } else if (VK) {
-      const int64_t leaf[1] = {n};
+      const int64_t leaf[1] = {PAIR ? (int64_t)word : n};
       if (VK_REG) vec_add_reg(a, vacc, leaf);
       else vec_add(a, acc_lds, slot_stride, leaf);
     } else {
       class_advance(a, ca, t, acc_lds, slot_stride, true);
-      ca.acc += (double)__int_as_float(rc.x);
+      ca.acc += (double)__uint_as_float(word);
     }
   }
   if (LEAVES) return;
@@ -190,15 +205,20 @@ int launch_direct_tile(const LaunchArgs &a, int waves, int64_t n_wg, int lds_byt
   return launch_common(direct_tile_kernel<false, false>, threads, n_wg, lds_bytes, stream, a);
 }
 
-int launch_direct(const LaunchArgs &a, int64_t n_wg, void *stream) {
+template <bool PAIR>
+static int launch_direct_p(const LaunchArgs &a, int64_t n_wg, void *stream) {
   const int lds = a.out_leaf ? 0 : 256 * 8 * a.K;
-  if (a.out_leaf) return launch_common(direct_kernel<true>, 256, n_wg, lds, stream, a);
+  if (a.out_leaf) return launch_common(direct_kernel<true, 0, PAIR>, 256, n_wg, lds, stream, a);
   if (a.vec && a.K <= 4)
-    return launch_common(direct_kernel<false, 4>, 256, n_wg, lds, stream, a);
+    return launch_common(direct_kernel<false, 4, PAIR>, 256, n_wg, lds, stream, a);
   if (a.vec && a.K <= 8)
-    return launch_common(direct_kernel<false, 8>, 256, n_wg, lds, stream, a);
-  if (a.vec) return launch_common(direct_kernel<false, 64>, 256, n_wg, lds, stream, a);
-  return launch_common(direct_kernel<false>, 256, n_wg, lds, stream, a);
+    return launch_common(direct_kernel<false, 8, PAIR>, 256, n_wg, lds, stream, a);
+  if (a.vec) return launch_common(direct_kernel<false, 64, PAIR>, 256, n_wg, lds, stream, a);
+  return launch_common(direct_kernel<false, 0, PAIR>, 256, n_wg, lds, stream, a);
+}
+
+int launch_direct(const LaunchArgs &a, bool pairs, int64_t n_wg, void *stream) {
+  return pairs ? launch_direct_p<true>(a, n_wg, stream) : launch_direct_p<false>(a, n_wg, stream);
 }
 
 }  // namespace bridger

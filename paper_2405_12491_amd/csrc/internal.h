@@ -263,7 +263,7 @@ int launch_ragged_heap5(const LaunchArgs &a, int waves, int64_t n_wg, int lds_by
 int launch_ragged_heap6(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
 int launch_ragged_heap7(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
 int launch_direct_tile(const LaunchArgs &a, int waves, int64_t n_wg, int lds_bytes, void *stream);
-int launch_direct(const LaunchArgs &a, int64_t n_wg, void *stream);
+int launch_direct(const LaunchArgs &a, bool pairs, int64_t n_wg, void *stream);
 int launch_gemm(int depth, const LaunchArgs &a, int64_t n_wg, void *stream);
 
 }  // namespace bridger

@@ -671,3 +671,17 @@ def test_views_handed_out_stay_as_they_are():
         stop.set()
         t.join()
         assert not changed and np.array_equal(view, first)
+
+
+@pytest.mark.parametrize("trees,F,n_rows,rows", [(1, 28, 10_000, 256), (1, 600, 100_000, 256), (1, 48, 300_000, 64),
+                                                 (3, 90, 100_000, 256), (3, 64, 100_000, 64), (4, 300, 1_000, 64),
+                                                 (4, 301, 1_000, 256), (6, 600, 1_000, 64), (12, 600, 100_000, 64)])
+def test_direct_few_large_trees(trees, F, n_rows, rows):
+    """Few large trees on wide rows are walked row by row (256 rows a workgroup): a tile would read
+    every feature of a row for the few that its paths meet."""
+    rng = np.random.default_rng(2)
+    big = random_tiny_forest(rng, 1, F, max_depth=15, p_split=0.99)
+    model = concat_trees([big.tree(0)] * trees, F)
+    with host(model) as f:
+        assert f.kernel == B.BRIDGER_KERNEL_DIRECT
+        assert f.plan(n_rows)["rows_per_wg"] == rows

@@ -17,7 +17,7 @@ GRID = [-1.0, -0.0, 0.0, 0.5, 1.0]
 VALUES = np.array([-1.0, -0.0, 0.0, 0.5, 1.0, 2.0, np.nan, np.inf, -np.inf], np.float32)
 
 
-def check(model, X, what, exact):
+def check(model, X, what, exact, rows=64):
     import torch
     print(what, flush=True)
     if model.value.ndim == 2:
@@ -27,7 +27,7 @@ def check(model, X, what, exact):
     Xd = torch.from_numpy(X).cuda()
     with B.Forest(model) as f:
         f.kernel = B.BRIDGER_KERNEL_DIRECT
-        assert f.plan(X.shape[0])["rows_per_wg"] == 64
+        assert f.plan(X.shape[0])["rows_per_wg"] == rows
         out = f.predict(Xd).cpu().numpy()
         lv = f.predict_leaves(Xd).cpu().numpy()
     assert np.array_equal(lv, ref_lv), what
@@ -36,9 +36,11 @@ def check(model, X, what, exact):
         assert np.array_equal(out, ref.astype(np.float32)), what
 
 
+@pytest.mark.parametrize("tile", ["1", "2"])
 @pytest.mark.parametrize("trees", [1, 3, 4, 5, 9, 33, 64, 65, 131])
-def test_direct_tile(trees, monkeypatch):
-    monkeypatch.setenv("BRIDGER_DIRECT_TILE", "1")
+def test_direct_tile(trees, tile, monkeypatch):
+    """The tile (1), and the same records row by row (2)."""
+    monkeypatch.setenv("BRIDGER_DIRECT_TILE", tile)
     rng = np.random.default_rng(40 + trees)
     F = 5 if trees % 2 else 8
     base = permute_nodes(random_tiny_forest(rng, trees, F, max_depth=9, p_split=0.85, thr_grid=GRID), rng)
@@ -50,21 +52,23 @@ def test_direct_tile(trees, monkeypatch):
         models.append((with_vector_leaves(base, K, rng), False))
     for model, exact in models:
         for n in (1, 64, 129):
-            check(model, rng.choice(VALUES, (n, F)), f"{trees} trees K {model.n_classes} rows {n}", exact)
+            check(model, rng.choice(VALUES, (n, F)), f"{trees} trees K {model.n_classes} rows {n}", exact,
+                  64 if tile == "1" else 256)
 
 
-def test_large_trees():
-    """Trees of more records than a RAGGED leaf can point over: the tile kernel by itself, with a
-    fused scaler too."""
+@pytest.mark.parametrize("trees,F", [(6, 9), (1, 9), (3, 100)])
+def test_large_trees(trees, F):
+    """Trees of more records than a RAGGED leaf can point over, in the way that the library takes by
+    itself (the tile; row by row for few trees), with a fused scaler too."""
     import torch
     rng = np.random.default_rng(4)
-    model = random_tiny_forest(rng, 6, 9, max_depth=17, p_split=0.97)
+    model = random_tiny_forest(rng, trees, F, max_depth=17, p_split=0.97)
     assert np.diff(model.tree_offsets).max() > 40000
-    X = rng.standard_normal((700, 9)).astype(np.float32)
+    X = rng.standard_normal((700, F)).astype(np.float32)
     with B.Forest(model, host_only=True) as f:
         assert f.kernel == B.BRIDGER_KERNEL_DIRECT
-    check(model, X, "large trees", True)
-    mean, scale = rng.normal(0, 0.2, 9), rng.uniform(0.8, 1.2, 9)
+    check(model, X, "large trees", True, 256 if trees == 1 else 64)
+    mean, scale = rng.normal(0, 0.2, F), rng.uniform(0.8, 1.2, F)
     Xs = ((X.astype(np.float64) - mean).astype(np.float32).astype(np.float64) / scale).astype(np.float32)
     with B.Forest(model) as f:
         f.set_preprocess(B.BRIDGER_PRE_CENTER_SCALE, mean, scale)

@@ -162,9 +162,7 @@ static int launch_bin_xv(const LaunchArgs &a, const BinTables &bt, bool lds, int
   return (int)hipGetLastError();
 }
 
-int launch_bin(const LaunchArgs &a, const BinTables &bt, bool lds, void *stream) {
-  const uintptr_t q = (uintptr_t)a.xq;
-  const bool v4 = a.x_vec4 && q % (4 * (uintptr_t)a.x_bytes) == 0;
+int launch_bin(const LaunchArgs &a, const BinTables &bt, bool lds, bool v4, void *stream) {
   int threads = kBinThreads;
   int64_t blocks, rows;
   if (lds) {

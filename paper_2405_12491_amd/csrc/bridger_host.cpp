@@ -129,11 +129,15 @@ struct bridger_forest {
   std::vector<int32_t> q_off;           // [F + 1]
   // bin tables (layout in internal.h): runs staged to LDS, and whole-row runs searched in place
   std::vector<uint32_t> bin_image;
-  std::vector<BinFeature> bin_features;
-  std::vector<BinRun> bin_runs, bin_runs_in_place;
-  int32_t bin_lds_bytes = 0;
-  void *d_bin_image = nullptr, *d_bin_features = nullptr, *d_bin_runs = nullptr,
-       *d_bin_runs_in_place = nullptr;
+  std::vector<BinFeature> bin_features, bin_features_in_place;
+  struct BinRuns {
+    std::vector<BinRun> runs;
+    int32_t lds_bytes = 0;  // of the largest staged run
+    int32_t in_place = 0;   // features not staged
+    void *d_runs = nullptr;
+  };
+  BinRuns bin_columns, bin_quads, bin_in_place;
+  void *d_bin_image = nullptr, *d_bin_features = nullptr, *d_bin_features_in_place = nullptr;
   Plan perfect_bplan{}, ragged_bplan{};
   bool perfect_bok = false, ragged_bok = false;
   std::vector<uint8_t> perfect_btrav;   // PERFECT traversal copy for bins: {rank, f * R * bytes}
@@ -976,42 +980,55 @@ bool build_quantization(bridger_forest *h, const int32_t *feat, const float *thr
   return h->bin_bytes != 0;
 }
 
-// Bin tables of the quantization (layout in internal.h).  A grid cell per threshold: more cells
-// make the fullest ones smaller but take LDS from the tables (6 bytes a threshold in all).
+// Bin tables of the quantization (layout in internal.h).  A grid cell per threshold, 6 bytes a
+// threshold in all, or (larger tables) per 2, 4, 8 or 16 thresholds, the fewest with which a column
+// (four adjacent ones, where the kernel takes four) fits a CU's LDS: a step more in LDS for each
+// doubling costs less than searching in L2 (1M x 28 rows, 7,204 thresholds a feature, a cell per 2: 181 us,
+// 426 in place, 368 by a binary search of staged tables; 9,000, a cell per 8: 182, 458, 733).
+constexpr int kBinCoarsest = 4;
+
+int32_t bin_words(int32_t n, int coarse) {  // words of a feature of the image
+  const int32_t cells = std::max((n + (1 << coarse) - 1) >> coarse, 1);
+  return (n + 8 + (cells + 1) / 2 + 3) & ~3;
+}
+
 void make_bin_tables(bridger_forest *h) {
   const int32_t F = h->F;
-  std::vector<int32_t> fullest(F, 0), word0(F + 1, 0);  // fullest cell; first word of a feature
+  const int kb = env_int("BRIDGER_BIN_LDS_KB", 0);  // tuning override of the LDS taken
+  const int64_t cap = kb > 0 ? std::min<int64_t>((int64_t)kb * 1024, kLdsBytesPerCU) : kLdsBytesPerCU;
+  auto table = [&](int32_t f) { return h->q_off[f + 1] - h->q_off[f]; };
+  // the fewest thresholds a cell with which features [f0, f1) fit; kBinCoarsest + 1: none
+  auto coarseness = [&](int32_t f0, int32_t f1) {
+    int c = 0;
+    for (; c <= kBinCoarsest; ++c) {
+      int64_t bytes = 0;
+      for (int32_t f = f0; f < f1; ++f) bytes += 4 * (int64_t)bin_words(table(f), c);
+      if (bytes <= cap) break;
+    }
+    return c;
+  };
   h->bin_features.assign(F, BinFeature{});
   h->bin_image.clear();
-  h->bin_image.reserve(h->q_values.size() * 3 / 2 + (size_t)12 * F);
+  h->bin_image.reserve(h->q_values.size() * 3 / 2 + (size_t)16 * F);
   std::vector<uint32_t> count;
-  for (int32_t f = 0; f < F; ++f) {
-    while (f % 4 == 0 && h->bin_image.size() % 4) h->bin_image.push_back(0);
-    word0[f] = (int32_t)h->bin_image.size();
-    const float *v = h->q_values.data() + h->q_off[f];
-    const int32_t n = h->q_off[f + 1] - h->q_off[f], cells = std::max(n, 1);
+  // the cells of a feature whose thresholds are in the image: parameters, counts; the fullest cell
+  auto make_grid = [&](BinFeature &p, const float *v, int32_t n, int coarse) {
+    const int32_t cells = std::max((n + (1 << coarse) - 1) >> coarse, 1);
     const float *b = v, *e = v + n;  // the finite thresholds
     while (b < e && std::isinf(*b)) ++b;
     while (e > b && std::isinf(e[-1])) --e;
-    BinFeature &p = h->bin_features[f];
     p.n = n;
     p.top = (float)(cells - 1);
     p.lo = b < e ? *b : 0.0f;
     const float width = b < e ? e[-1] - *b : 0.0f;
     p.scale = (float)cells / width;
     if (!std::isfinite(p.scale)) p.scale = 0.0f;  // one value, or a range beyond fp32: one cell
-    p.tab = (int32_t)h->bin_image.size();
-    for (int32_t i = 0; i < n; ++i) {
-      uint32_t w;
-      std::memcpy(&w, &v[i], 4);
-      h->bin_image.push_back(w);
-    }
-    for (int i = 0; i < 8; ++i) h->bin_image.push_back(0x7f800000u);
     p.start = 2 * (int32_t)h->bin_image.size();
     count.assign(cells, 0);
+    int32_t most = 0;
     for (int32_t i = 0; i < n; ++i) {
       const float c = std::fmin(std::fmax((v[i] - p.lo) * p.scale, 0.0f), p.top);
-      fullest[f] = std::max<int32_t>(fullest[f], (int32_t)++count[(uint32_t)c]);
+      most = std::max<int32_t>(most, (int32_t)++count[(uint32_t)c]);
     }
     uint32_t lower = 0;
     for (int32_t c = 0; c < cells; c += 2) {
@@ -1021,8 +1038,26 @@ void make_bin_tables(bridger_forest *h) {
       if (c + 1 < cells) lower += count[c + 1];
       h->bin_image.push_back(first | second << 16);
     }
+    while (h->bin_image.size() % 4) h->bin_image.push_back(0);
+    return most;
+  };
+  std::vector<int32_t> fullest(F, 0), word0(F + 1, 0), coarse(F, 0);  // word0: first word of a feature
+  for (int32_t f = 0; f < F; ++f) {
+    word0[f] = (int32_t)h->bin_image.size();
+    const float *v = h->q_values.data() + h->q_off[f];
+    const int32_t n = table(f);
+    coarse[f] = F % 4 ? kBinCoarsest + 1 : coarseness(f & ~3, (f & ~3) + 4);
+    if (coarse[f] > kBinCoarsest) coarse[f] = coarseness(f, f + 1);
+    if (coarse[f] > kBinCoarsest) coarse[f] = 0;
+    h->bin_features[f].tab = (int32_t)h->bin_image.size();
+    for (int32_t i = 0; i < n; ++i) {
+      uint32_t w;
+      std::memcpy(&w, &v[i], 4);
+      h->bin_image.push_back(w);
+    }
+    for (int i = 0; i < 8; ++i) h->bin_image.push_back(0x7f800000u);
+    fullest[f] = make_grid(h->bin_features[f], v, n, coarse[f]);
   }
-  while (h->bin_image.size() % 4) h->bin_image.push_back(0);
   word0[F] = (int32_t)h->bin_image.size();
 
   auto run = [&](int32_t f0, int32_t f1, bool staged) {
@@ -1031,39 +1066,48 @@ void make_bin_tables(bridger_forest *h) {
     if (most > 0) r.steps = 1 << ilog2(most);
     return r;
   };
-  // staged runs: as few as fit a CU's LDS whole, or half of it where that takes no more of them
-  auto staged_runs = [&](int64_t cap, std::vector<BinRun> &runs) {
-    runs.clear();
-    int64_t most = 0;
+  // staged runs of whole units (the features a thread takes): as few as fit `bytes`; a unit that
+  // does not is a run of its own, searched in place
+  auto staged_runs = [&](int64_t bytes, int32_t unit) {
+    bridger_forest::BinRuns s;
     for (int32_t f = 0; f < F;) {
       int32_t fe = f;
       while (fe < F && fe - f < 1024) {
-        const int32_t next = std::min(F, fe + 4);
-        if (4 * (int64_t)(word0[next] - word0[f]) > cap) break;
+        const int32_t next = std::min(F, fe + unit);
+        if (4 * (int64_t)(word0[next] - word0[f]) > bytes) break;
         fe = next;
       }
       const bool fits = fe > f;
-      if (!fits) fe = std::min(F, f + 4);
-      runs.push_back(run(f, fe, fits));
-      if (fits) most = std::max(most, 4 * (int64_t)runs.back().words);
+      if (!fits) fe = std::min(F, f + unit);
+      s.runs.push_back(run(f, fe, fits));
+      if (fits) s.lds_bytes = std::max<int32_t>(s.lds_bytes, 4 * s.runs.back().words);
+      else s.in_place += fe - f;
       f = fe;
     }
-    return most;
+    return s;
   };
-  const int kb = env_int("BRIDGER_BIN_LDS_KB", 0);  // tuning override of the LDS taken
-  if (kb > 0) {
-    h->bin_lds_bytes = (int32_t)staged_runs(std::min<int64_t>((int64_t)kb * 1024, kLdsBytesPerCU), h->bin_runs);
-  } else {
-    h->bin_lds_bytes = (int32_t)staged_runs(kLdsBytesPerCU / 2, h->bin_runs);
-    std::vector<BinRun> whole;
-    const int64_t bytes = staged_runs(kLdsBytesPerCU, whole);
-    if (whole.size() < h->bin_runs.size()) {
-      h->bin_runs = whole;
-      h->bin_lds_bytes = (int32_t)bytes;
-    }
-  }
-  h->bin_runs_in_place.clear();
-  for (int32_t f = 0; f < F; f += 1024) h->bin_runs_in_place.push_back(run(f, std::min(F, f + 1024), false));
+  // a CU's LDS whole, or half of it (two workgroups) where that leaves no more features in L2 and
+  // takes no more runs
+  auto best_runs = [&](int32_t unit) {
+    bridger_forest::BinRuns whole = staged_runs(cap, unit);
+    if (kb > 0) return whole;
+    bridger_forest::BinRuns half = staged_runs(cap / 2, unit);
+    return half.in_place <= whole.in_place && half.runs.size() <= whole.runs.size() ? half : whole;
+  };
+  h->bin_columns = best_runs(1);
+  h->bin_quads = F % 4 ? bridger_forest::BinRuns{} : best_runs(4);
+  // whole rows in place take a cell per threshold whatever fits (9,500 thresholds a feature, 9,000 x 28
+  // rows: 9.3 us, 11.2 with the staged runs' cells)
+  h->bin_features_in_place = h->bin_features;
+  for (int32_t f = 0; f < F; ++f)
+    if (coarse[f]) fullest[f] = make_grid(h->bin_features_in_place[f], h->q_values.data() + h->q_off[f], table(f), 0);
+  h->bin_in_place = {};
+  for (int32_t f = 0; f < F; f += 1024) h->bin_in_place.runs.push_back(run(f, std::min(F, f + 1024), false));
+  if (env_int("BRIDGER_LOG", 0))
+    for (const auto *s : {&h->bin_columns, &h->bin_quads})
+      if (!s->runs.empty())
+        std::fprintf(stderr, "[bridger] bin tables: %d column(s) a thread, %zu runs, %d features in place, lds=%d\n",
+                     s == &h->bin_quads ? 4 : 1, s->runs.size(), s->in_place, s->lds_bytes);
 }
 
 uint32_t rank_of(const bridger_forest *h, int32_t f, float t) {
@@ -1746,8 +1790,8 @@ bridger_status upload_all(bridger_forest *h) {
   if (h->bin_bytes) {
     up.add(&h->d_bin_image, h->bin_image);
     up.add(&h->d_bin_features, h->bin_features);
-    up.add(&h->d_bin_runs, h->bin_runs);
-    up.add(&h->d_bin_runs_in_place, h->bin_runs_in_place);
+    up.add(&h->d_bin_features_in_place, h->bin_features_in_place);
+    for (auto *r : {&h->bin_columns, &h->bin_quads, &h->bin_in_place}) up.add(&r->d_runs, r->runs);
   }
   if (h->perfect_bok) {
     up.add(&h->d_perfect_btrav, h->perfect_btrav, 1024);
@@ -2486,18 +2530,22 @@ bridger_status bridger_forest_bin(bridger_forest_t h, const float *X, int64_t n_
     // (the tuning override takes one way or the other)
     const int force = env_int("BRIDGER_BIN_KERNEL", 0);
     const bool lds = force == 1 || (force != 2 && nr * (int64_t)h->F >= kBinStagedValues);
-    const auto &runs = lds ? h->bin_runs : h->bin_runs_in_place;
+    bool quads = a.x_vec4 && (uintptr_t)a.xq % (4 * (uintptr_t)a.x_bytes) == 0;
+    // a column a thread where that stages tables that four do not (1M rows: 28 x 12,000 thresholds 279 us,
+    // 495 with four in place; 8 x 12,000 39 and 130; 28 x 35,000 457 and 801)
+    if (lds && quads && h->bin_columns.in_place < h->bin_quads.in_place) quads = false;
+    const auto &r = !lds ? h->bin_in_place : quads ? h->bin_quads : h->bin_columns;
     BinTables bt{};
     bt.image = (const uint32_t *)h->d_bin_image;
-    bt.features = (const BinFeature *)h->d_bin_features;
-    bt.runs = (const BinRun *)(lds ? h->d_bin_runs : h->d_bin_runs_in_place);
-    bt.n_runs = (int32_t)runs.size();
-    bt.lds_bytes = h->bin_lds_bytes;
+    bt.features = (const BinFeature *)(lds ? h->d_bin_features : h->d_bin_features_in_place);
+    bt.runs = (const BinRun *)r.d_runs;
+    bt.n_runs = (int32_t)r.runs.size();
+    bt.lds_bytes = r.lds_bytes;
     bt.max_features = std::min(h->F, 1024);
     set_preprocess_args(h, a);
     RowNorms norms;
     if ((s = prepare_row_norms(h, a, stream, norms)) != BRIDGER_OK) return s;
-    const int err = launch_bin(a, bt, lds, stream);
+    const int err = launch_bin(a, bt, lds, quads, stream);
     if (err != 0)
       return fail(BRIDGER_ERR_DEVICE, std::string("kernel launch failed: ") +
                                           hipGetErrorString((hipError_t)err));

@@ -222,7 +222,7 @@ int launch_perfect_binned(int depth, const LaunchArgs &a, int waves, int64_t n_w
                           void *stream);
 // Binning tables: an image of 32-bit words holding, feature after feature, its distinct thresholds
 // ascending, 8 words of +inf, and (16 bits each) for every cell of a grid over them the number of
-// thresholds in lower cells; x lies in cell (uint)min(max((x - lo) * scale, 0), top), in fp32.
+// thresholds in lower cells, a multiple of 4 words in all; x lies in cell (uint)min(max((x - lo) * scale, 0), top), in fp32.
 struct BinFeature {
   float lo, scale, top;  // top: cells - 1
   int32_t n;             // thresholds
@@ -230,7 +230,7 @@ struct BinFeature {
   int32_t start;         // first 16-bit word of the cells' counts
   int32_t unused[2];
 };
-// A run of features that one workgroup looks up; a multiple of 4 features unless it ends the row.
+// A run of features that one workgroup looks up.
 struct BinRun {
   int32_t f0, f1;        // at most 1024 features
   int32_t word0, words;  // their part of the image (multiples of 4 words)
@@ -246,7 +246,8 @@ struct BinTables {
   int32_t max_features;  // of any run
 };
 // lds: stage the runs' tables (bt: the staged runs), else search them in place (bt: whole rows).
-int launch_bin(const LaunchArgs &a, const BinTables &bt, bool lds, void *stream);
+// quads: four columns a thread (rows and bins aligned for it; bt's runs are whole quads), else one.
+int launch_bin(const LaunchArgs &a, const BinTables &bt, bool lds, bool quads, void *stream);
 int launch_row_norm(const LaunchArgs &a, double *norm, void *stream);
 // Device address of the allocation-free predict's row-norm scratch on the current device
 // (kNoAllocMaxRows doubles); looked up once per device.  Returns a hipError_t as int.

@@ -685,3 +685,24 @@ def test_direct_few_large_trees(trees, F, n_rows, rows):
     with host(model) as f:
         assert f.kernel == B.BRIDGER_KERNEL_DIRECT
         assert f.plan(n_rows)["rows_per_wg"] == rows
+
+
+@pytest.mark.parametrize("F,n", [(28, 910), (28, 4553), (28, 7204), (28, 9500), (28, 12_000), (7, 8700), (3, 30_000)])
+def test_bin_tables_are_staged(F, n, monkeypatch, capfd):
+    """Tables that a column or four of them can bring to LDS are staged, whatever the number of runs:
+    none of a forest's features stays in place in the layout that its rows take."""
+    rng = np.random.default_rng(F)
+    trees = -(-F * n // 7)
+    thr = rng.standard_normal((trees, 7)).astype(np.float32)
+    feat = (np.arange(trees * 7) % F).reshape(trees, 7)
+    leaf = np.zeros(8, np.float32)
+    model = concat_trees([perfect_tree_arrays(3, feat[t], thr[t], leaf) for t in range(trees)], F)
+    monkeypatch.setenv("BRIDGER_LOG", "1")
+    with host(model):
+        pass
+    log = re.findall(r"bin tables: (\d) column\(s\) a thread, (\d+) runs, (\d+) features in place, lds=(\d+)",
+                     capfd.readouterr().err)
+    assert log and all(int(lds) <= 163840 for *_, lds in log)
+    assert any(c == "1" and in_place == "0" for c, _, in_place, _ in log)
+    if F % 4 == 0 and n < 9600:  # four columns, 4 bytes a threshold and at least 2 a cell of 16
+        assert any(c == "4" and in_place == "0" for c, _, in_place, _ in log)

@@ -39,11 +39,26 @@ def _tables(rng, F, n):
                          ids=lambda e: ",".join(f"{k[8:]}={v}" for k, v in e.items()))
 @pytest.mark.parametrize("F,n", [(1, 40), (3, 200), (4, 300), (12, 70), (28, 500), (37, 33), (300, 6), (1100, 2)])
 def test_bin_cells(F, n, env, monkeypatch):
-    import torch
     for k, v in env.items():
         monkeypatch.setenv(k, v)
     rng = np.random.default_rng(F * 1000 + n)
-    tables = _tables(rng, F, n)
+    _check(rng, F, _tables(rng, F, n), f"n={n} {env}")
+
+
+@pytest.mark.parametrize("kernel", ["1", "2"])
+@pytest.mark.parametrize("F,n,kb", [(4, 450, 8), (4, 480, 8), (28, 450, 8), (3, 900, 4), (5, 990, 4), (4, 900, 4), (4, 1100, 4)])
+def test_coarse_cells(F, n, kb, kernel, monkeypatch):
+    """Tables that fit the LDS only with cells of several thresholds (four columns together, one at a
+    time, or not at all), staged and in place (there with a cell per threshold)."""
+    monkeypatch.setenv("BRIDGER_BIN_LDS_KB", str(kb))
+    monkeypatch.setenv("BRIDGER_BIN_KERNEL", kernel)
+    rng = np.random.default_rng(n)
+    tables = [rng.standard_normal(n) if f % 3 else np.exp(4 * rng.standard_normal(n)) for f in range(F)]
+    _check(rng, F, [t.astype(np.float32) for t in tables], f"n={n} {kb} KB kernel {kernel}")
+
+
+def _check(rng, F, tables, what):
+    import torch
     model = _forest(rng, tables)
     rows = 333
     X = rng.standard_normal((rows, F)).astype(np.float32)
@@ -63,7 +78,7 @@ def test_bin_cells(F, n, env, monkeypatch):
             qs = shift * 4 // bb  # outputs are 4-byte aligned
             qbuf = torch.zeros(rows * F + 4, dtype=dt, device="cuda")
             q = qbuf[qs:qs + rows * F].view(rows, F)
-            print(f"bins F={F} n={n} shift={shift} {env}", flush=True)
+            print(f"bins F={F} shift={shift} {what}", flush=True)
             B.bridger_forest_bin(f.handle, Xd.data_ptr(), rows, F, q.data_ptr(),
                                  torch.cuda.current_stream().cuda_stream)
             got = q.cpu().numpy().view(np.uint8 if bb == 1 else np.uint16)

@@ -1580,19 +1580,75 @@ bool perfect_heap_wanted() {
   return true;
 }
 
+// The PERFECT plan made for the smallest batch-size class holding n_rows, or null (the plan
+// for large batches serves).
+const bridger_forest::SizedPlan *sized_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
+  for (const auto &sp : binned ? h->perfect_bsized : h->perfect_sized)
+    if (n_rows <= sp.max_rows) return &sp;
+  return nullptr;
+}
+
+// Perfect forests for which the walk, though the rules above would give it to them, takes longer than PERFECT
+// (us, heap walk / PERFECT).  Of 2,100 forests and batches (1 to 9 levels, 3 to 1,200 trees, 5 to 700 features,
+// 200 to 700,000 rows) other than those the clauses come from, 2.5% take over 5% longer than with PERFECT;
+// without this rule 15% did, the worst 2.5 times.
+// whole_lines: the tile is filled 8 rows x 128 bytes at a time (load_tile_all), not a row a lane.
+bool stays_perfect(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves, bool whole_lines) {
+  const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, binned);
+  const Plan &p = sp ? sp->plan : binned ? h->perfect_bplan : h->perfect_plan;
+  const Plan &w = choose_heap_plan(h, n_rows, binned);
+  auto rounds = [&](const Plan &q) {  // of workgroups on the chip
+    return std::ceil((double)n_rows / q.rows_per_wg) / ((double)kNumCUs * std::max(q.waves_per_cu / q.waves, 1));
+  };
+  const int D = h->perfect_depth, F = h->F;
+  const int64_t T = h->n_trees, L = T << D;
+  // Few leaves: one or two chunks, staged while the tile loads (leaf ids, 13,642 x 72 rows, 14 trees of depth 8 6.8 /
+  // 6.1; 6,099 x 30 rows, 707 of depth 2, 5 levels in the heaps, 16.4 / 11.3).
+  if (leaves) return D <= 2 || (L <= 2560 && F > 7 && rounds(w) <= 0.85);
+  // (bins, 79 trees of depth 4, 63,000 x 38 rows 13.1 / 10.3; few trees when the walk takes a second round, 35 of
+  // depth 7, 126,000 x 9 rows 17 / 13; short trees where PERFECT has 24 waves a CU, 761 of depth 3, 19,000 rows 26 / 19)
+  if (binned)
+    return (F <= 144 && (L <= 1120 || (L <= 1920 && n_rows > 12288))) || (D <= 5 && p.waves_per_cu > 18) ||
+           (p.waves_per_cu <= 18 && T * D <= 320 && rounds(w) > 1.11);
+  // The heaps have 5 levels at least: trees of fewer pay for the padding (1,000 trees of depth 4, 28 features:
+  // 40,000 rows 49 / 38; 897 of depth 1, 71 features, 167,000 rows 151 / 75), but where PERFECT's row tile leaves it
+  // few lane groups or several rounds (164 of depth 4, 157 features, 116,000 rows 65 / 114), or its many trees
+  // leave most of the chip idle (1,125 of depth 3, 671 rows 28 / 36).
+  if (D <= 4) return (p.rows_per_wg <= 64 || rounds(p) <= 0.8) && (F <= 124 || p.groups > 12) && (T * D <= 3053 || rounds(p) > 0.5);
+  // A tile filled a row a lane touches 64 lines a load, 8 or 16 waves of them more than the L1 holds: PERFECT's
+  // 32-row tiles, where they leave it 16 waves a CU, wait less (5 trees of depth 8, 226 features, 252,000 rows 234
+  // / 141; 43 of depth 6, 250 features 341 / 215; 8 waves a CU: 463 of depth 6, 209 features 223 / 366).
+  if (!whole_lines && F >= 150 && F <= kHeapWideFeatures && n_rows > 16384 && p.waves_per_cu >= 16) return true;
+  // Few leaves: staging them takes no time (8 trees of depth 8, 58 features, 90,000 rows 19 / 8; 18 of depth 7, 16
+  // features, 33,000 rows 8.0 / 6.5); in more than one round PERFECT's several lane groups cost it more.
+  if (L <= (F < kHeapLoadFeatures ? 3200 : 2512) && rounds(p) <= 1.11 && (L <= 1296 || rounds(w) > 0.63)) return true;
+  // One round of PERFECT's larger tiles against two or more of the walk's (95 trees of depth 6, 18 features, 59,000
+  // rows 15.8 / 11.8; 75 of depth 8, 20 classes, 107,000 x 5 83 / 33; but 111 of depth 6, 99 features 24 / 43).
+  if (rounds(p) <= 1.1 && (rounds(w) > 2.5 || (rounds(w) > 1.5 && L <= 11000 && F < kHeapLoadFeatures))) return true;
+  // Five levels, 64-row tiles of wide rows against the walk's 32 columns (143 trees, 300 features, 78,000 rows 65 / 53).
+  if (whole_lines && D == 5 && F > kHeapWideFeatures && F < 400 && p.rows_per_wg == 64) return true;
+  // Row-a-lane tiles in small batches: every lane group of the walk loads its own (133 trees of depth 5, 99
+  // features, 4,548 rows scaled 9.9 / 7.7; 281, 195 features, 2,309 rows 14.7 / 10.6).
+  if (!whole_lines && F >= 80 && rounds(p) <= 0.64 && 0.22 * p.groups >= p.n_chunks) return true;
+  // A chunk or two for many lane groups, and a tile that leaves the walk one workgroup of at most 10 waves (24 trees
+  // of depth 8, 255 features, 2,180 rows 10.9 / 8.0).
+  return L <= 11360 && w.waves_per_cu <= 10 && 0.16 * p.groups >= p.n_chunks;
+}
+
 // Whether a prediction of n_rows rows takes the padded-heap kernel.
-bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves) {
+bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves, bool whole_lines) {
   if (!(binned ? h->heap_bok : h->heap_ok)) return false;
   if (h->kernel_active == kRagged) return true;
   if (h->kernel_active != kPerfect || !h->kernel_auto || !h->perfect_heap) return false;
   const bool few_rows = h->F >= kHeapLoadFeatures && n_rows <= kHeapTileRows;
   if ((int64_t)h->n_trees << h->perfect_depth <= (few_rows ? kHeapTileLeaves : kHeapLeaves)) return false;
-  if (leaves) return n_rows <= kHeapLeafRows;
+  if (leaves && n_rows > kHeapLeafRows) return false;
   const Plan &p = binned ? h->perfect_bplan : h->perfect_plan;
   const int row_bytes = h->F * (binned ? h->bin_bytes : 4);
-  if (p.global_nodes || (p.groups > 1 && (row_bytes >= kHeapTileRowBytes || p.waves_per_cu < 16)))
-    return true;
-  return n_rows <= (h->vec ? kHeapVectorRows : kHeapPerfectRows);
+  if (!leaves && n_rows > (h->vec ? kHeapVectorRows : kHeapPerfectRows) &&
+      !(p.global_nodes || (p.groups > 1 && (row_bytes >= kHeapTileRowBytes || p.waves_per_cu < 16))))
+    return false;
+  return p.global_nodes || !stays_perfect(h, n_rows, binned, leaves, whole_lines);
 }
 
 // Launch plan of the DIRECT tile kernel (waves == 0: does not fit): W waves that share 64 rows and
@@ -1911,15 +1967,6 @@ bridger_status check_predict(const bridger_forest *h, const void *X, int64_t n_r
   return BRIDGER_OK;
 }
 
-// The PERFECT plan made for the smallest batch-size class holding n_rows, or null (the plan
-// for large batches serves).
-const bridger_forest::SizedPlan *sized_plan(const bridger_forest *h, int64_t n_rows,
-                                            bool binned) {
-  for (const auto &sp : binned ? h->perfect_bsized : h->perfect_sized)
-    if (n_rows <= sp.max_rows) return &sp;
-  return nullptr;
-}
-
 // X is fp32 rows, or (binned) rows of bin_bytes-wide bins from bridger_forest_bin.
 struct CsrRows {
   const int64_t *indptr = nullptr;
@@ -1957,7 +2004,8 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
   a.aggregate = h->aggregate;
   a.transform = h->transform;
   a.tile_coalesced = h->tile_coalesced ? 1 : 0;
-  const bool heaps = takes_heaps(h, n_rows, binned, out_leaf != nullptr);
+  const bool heaps = takes_heaps(h, n_rows, binned, out_leaf != nullptr,
+                                 csr || (a.x_vec4 && h->pre_kind == BRIDGER_PRE_NONE));
   RowNorms norms;
   if (!binned) {
     set_preprocess_args(h, a);
@@ -2664,7 +2712,7 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
   if (n_rows < 0) return fail(BRIDGER_ERR_INVALID_ARGUMENT, "n_rows < 0");
   Plan p{};
   double forest_bytes = 0;
-  if (takes_heaps(h, n_rows, false, false)) {
+  if (takes_heaps(h, n_rows, false, false, h->F % 4 == 0 && h->pre_kind == BRIDGER_PRE_NONE)) {
     p = choose_heap_plan(h, n_rows, false);
     forest_bytes = 8.0 * h->ragged_rec.size();
   } else if (h->kernel_active == kPerfect) {

@@ -206,7 +206,8 @@ def test_perfect_small_batches(n_rows):
     64-row groups, then the PERFECT kernels): the explicit PERFECT kernel's outputs."""
     import torch
     rng = np.random.default_rng(n_rows)
-    for D, K, T in ((3, 1, 129), (3, 1, 128), (6, 3, 70), (8, 1, 40)):  # above and at 1,024 leaves
+    # (trees of few levels or leaves stay with PERFECT, whatever the batch)
+    for D, K, T, walk in ((3, 1, 129, False), (3, 1, 128, False), (6, 1, 20, False), (6, 3, 70, True), (8, 1, 40, True)):
         trees = [perfect_tree_arrays(D, rng.integers(0, 10, (1 << D) - 1),
                                      rng.standard_normal((1 << D) - 1).astype(np.float32),
                                      rng.standard_normal(1 << D).astype(np.float32)) for _ in range(T)]
@@ -217,13 +218,30 @@ def test_perfect_small_batches(n_rows):
             assert f.kernel == B.BRIDGER_KERNEL_PERFECT
             q = f.bin(X)
             got = [f.predict(X), f.predict_binned(q), f.predict_labels(X), f.predict_leaves(X)]
-            assert (f.plan(n_rows)["chunk_bytes"] == 0) == (n_rows <= 131072 and T << D > 1024)
+            assert (f.plan(n_rows)["chunk_bytes"] == 0) == (n_rows <= 131072 and walk)
             f.kernel = B.BRIDGER_KERNEL_PERFECT
             ref = [f.predict(X), f.predict_binned(q), f.predict_labels(X), f.predict_leaves(X)]
             assert f.plan(n_rows)["chunk_bytes"] > 0
         for g, r in zip(got[:2], ref[:2]):  # double sums in another order, rounded once
             assert torch.allclose(g, r, rtol=2.4e-7, atol=1e-7)
         assert torch.equal(got[2], ref[2]) and torch.equal(got[3], ref[3])
+
+
+@pytest.mark.parametrize("D,T,F,n,walk", [
+    (4, 1000, 28, 40_000, False), (1, 897, 71, 167_000, False), (3, 1125, 21, 671, True), (4, 164, 157, 116_000, True),
+    (6, 100, 28, 10_000, True), (8, 18, 16, 33_000, True), (7, 18, 16, 33_000, False), (8, 8, 58, 90_000, False),
+    (8, 5, 226, 252_000, False), (8, 5, 228, 252_000, True), (6, 43, 250, 240_000, False), (6, 463, 209, 200_000, True),
+    (8, 24, 256, 2_180, False), (8, 48, 256, 2_180, True), (5, 281, 195, 2_309, False), (6, 95, 18, 59_458, False),
+    (6, 95, 18, 29_000, True), (5, 143, 300, 77_537, False), (5, 143, 299, 77_537, True), (6, 500, 28, 1_000, True), (6, 500, 28, 1_000_000, False)])
+def test_perfect_walk_rule(D, T, F, n, walk):
+    """Which perfect forests AUTO gives to the padded-heap walk (no chunks in the plan): on both sides of
+    each clause, the shapes on which it was measured."""
+    rng = np.random.default_rng(D)
+    trees = [perfect_tree_arrays(D, rng.integers(0, F, (1 << D) - 1), rng.standard_normal((1 << D) - 1).astype(np.float32),
+                                 np.zeros(1 << D, np.float32)) for _ in range(T)]
+    with B.Forest(concat_trees(trees, F), host_only=True) as f:
+        assert f.kernel == B.BRIDGER_KERNEL_PERFECT
+        assert (f.plan(n)["chunk_bytes"] == 0) == walk
 
 
 @pytest.mark.gpu

@@ -389,10 +389,13 @@ __device__ void groups_finalize_store(const LaunchArgs &a, double *z0, int R, in
       z[0] = s;
     }
     __syncthreads();
-    if (a.transform == 2 && !a.out_label && a.K > 1) {
-      // softmax, one (row, class) per thread as well: each thread finishes its row's K values
-      // as finalize_store does (same operations, same order) and writes its exponential into
-      // the second group's slot, free now; then each divides by the row's sum
+    // softmax, one (row, class) per thread as well: each thread finishes its row's K values
+    // as finalize_store does (same operations, same order) and writes its exponential into
+    // the second group's slot, free now; then each divides by the row's sum.  A thread reads all K
+    // values for each of its K / G classes, so many classes and few groups are left to one lane per
+    // row (64 trees of depth 9, 64 classes, 42,516 x 23 rows in two groups: bins 77 us, 430
+    // with a class a thread, 70 on the record walk's one group)
+    if (a.transform == 2 && !a.out_label && a.K > 1 && a.K <= 12 * (G - 1)) {
       const int K = a.K;
       const int64_t row0 = (int64_t)blockIdx.x * R;  // the tile's first row
       for (int i = tid; i < R * K; i += R * G) {

@@ -180,7 +180,7 @@ struct bridger_forest {
   bool heap_flat = false;   // no tree deeper than L
   int32_t heap_waves = 0;   // BRIDGER_HEAP_WAVES (the padded-heap walk alone) or BRIDGER_WAVES at create
   int32_t heap_rows = 0;    // BRIDGER_HEAP_ROWS at create
-  Plan heap_plans[2][3][5] = {};  // [binned][64, 32 or 16 rows][1, 2, 4, 8 or 16 waves]; waves 0: none
+  Plan heap_plans[2][2][3][5] = {};  // [leaf ids][binned][64, 32 or 16 rows][1, 2, 4, 8 or 16 waves]; waves 0: none
   int32_t heap_span[7] = {};  // most classes a lane group's trees span, of 1, 2, 4 .. 64 groups
   RaggedHeaps heap, bheap;
   std::vector<int32_t> heap_leaf;  // leaf ids: two per block, or one per leaf word (flat)
@@ -1468,12 +1468,12 @@ bool heaps_wanted(const bridger_forest *h) {
 }
 
 // One shape of the padded-heap kernel: W waves that share R rows, 64 / R lane groups in each.
-Plan heap_plan(const bridger_forest *h, int R, int W, bool binned) {
+Plan heap_plan(const bridger_forest *h, int R, int W, bool binned, bool leaves) {
   Plan p{};
   const int groups = W * (64 / R);
   if (R > heap_columns(h, binned)) return p;
-  const int64_t sums = (int64_t)h->K * W * 64 * 8;
-  // sums kept in LDS during the walk, or written over the tile after it
+  // sums kept in LDS during the walk, or written over the tile after it; leaf ids need none
+  const int64_t sums = leaves ? 0 : (int64_t)h->K * W * 64 * 8;
   const bool regs = h->vec ? h->K <= 8 : h->K == 1 || h->heap_span[ilog2(groups)] <= kHeapClassRegs;
   const int64_t walk = (int64_t)h->F * heap_row_bytes(h, binned) + (int64_t)groups * heap_wave_bytes(h->heap_levels);
   const int64_t lds = regs ? std::max(walk, sums) : walk + sums;
@@ -1506,7 +1506,7 @@ Plan heap_plan(const bridger_forest *h, int R, int W, bool binned) {
 //     (1M x 28 rows, 100 trees of depth 12: W = 2 0.225 ms, 4 0.236, 8 0.261).
 constexpr int kHeapLoadFeatures = 64;
 
-const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned) {
+const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves) {
   const int U = heap_batch(h->heap_levels);
   const int load_waves = h->F < kHeapLoadFeatures ? 4 : 8;
   n_rows = std::max<int64_t>(n_rows, 1);
@@ -1518,7 +1518,7 @@ const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binne
     for (int W : {1, 2, 4, 8, 16}) {
       if (h->heap_waves ? W != h->heap_waves : W < 4) continue;
       const int groups = W * gpw, batches = ((h->n_trees + groups - 1) / groups + U - 1) / U;
-      const Plan &p = h->heap_plans[binned][ilog2(gpw)][ilog2(W)];
+      const Plan &p = h->heap_plans[leaves][binned][ilog2(gpw)][ilog2(W)];
       if (!p.waves || batches >= fewest) continue;
       fewest = batches;
       best = &p;
@@ -1535,7 +1535,7 @@ const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binne
                       : W > load_waves && (W * gpw > h->n_trees ||
                                            (h->F < kHeapLoadFeatures && W / 2 * gpw * U >= h->n_trees)))
       continue;
-    const Plan &p = h->heap_plans[binned][ilog2(64 / R)][ilog2(W)];
+    const Plan &p = h->heap_plans[leaves][binned][ilog2(64 / R)][ilog2(W)];
     if (!p.waves) continue;
     const int64_t active = std::min<int64_t>((n_rows + R - 1) / R * W, (int64_t)kNumCUs * p.waves_per_cu);
     if (active <= most) continue;
@@ -1596,7 +1596,7 @@ const bridger_forest::SizedPlan *sized_plan(const bridger_forest *h, int64_t n_r
 bool stays_perfect(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves, bool whole_lines) {
   const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, binned);
   const Plan &p = sp ? sp->plan : binned ? h->perfect_bplan : h->perfect_plan;
-  const Plan &w = choose_heap_plan(h, n_rows, binned);
+  const Plan &w = choose_heap_plan(h, n_rows, binned, leaves);
   auto rounds = [&](const Plan &q) {  // of workgroups on the chip
     return std::ceil((double)n_rows / q.rows_per_wg) / ((double)kNumCUs * std::max(q.waves_per_cu / q.waves, 1));
   };
@@ -2023,7 +2023,7 @@ bridger_status launch_rows(bridger_forest *h, const void *X, int64_t n_rows, flo
     if (perfect && out_leaf && leaves.plan.waves && (!sp || sp->plan.groups == 1)) sp = &leaves;
     const Plan &p = sp ? sp->plan
                        : perfect ? (binned ? h->perfect_bplan : h->perfect_plan)
-                       : heaps   ? choose_heap_plan(h, n_rows, binned)
+                       : heaps   ? choose_heap_plan(h, n_rows, binned, out_leaf != nullptr)
                                  : (binned ? h->ragged_bplan : h->ragged_plan);
     const DevArrays &d = perfect ? h->d_perfect : h->d_ragged;
     if (perfect)
@@ -2377,10 +2377,11 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
         h->heap_waves = env_int("BRIDGER_HEAP_WAVES", env_int("BRIDGER_WAVES", 0));
         h->heap_rows = env_int("BRIDGER_HEAP_ROWS", 0);
         for (int i = 0; i < 7; ++i) h->heap_span[i] = class_span(h, 1 << i);
-        for (int b = 0; b < 2; ++b)
-          for (int r = 0; r < 3; ++r)
-            for (int w = 0; w < 5; ++w) h->heap_plans[b][r][w] = heap_plan(h, 64 >> r, 1 << w, b != 0);
-        h->heap_ok = choose_heap_plan(h, pin.n_rows, false).waves > 0 &&
+        for (int i = 0; i < 2 * 2 * 3 * 5; ++i) {
+          const int l = i & 1, b = i >> 1 & 1, r = i / 4 % 3, w = i / 12;
+          h->heap_plans[l][b][r][w] = heap_plan(h, 64 >> r, 1 << w, b != 0, l != 0);
+        }
+        h->heap_ok = choose_heap_plan(h, pin.n_rows, false, false).waves > 0 &&
                      make_ragged_heaps(h, h->ragged_rec, false, h->heap, &h->heap_leaf);
       }
     }
@@ -2414,7 +2415,7 @@ bridger_status bridger_forest_create_ex(int32_t n_trees, const int64_t *tree_off
             build_ragged_tops(h->ragged_brec, h->ragged_tree_start, h->n_trees,
                               h->ragged_bplan.tops, h->ragged_btops);
           }
-          if (h->heap_ok && choose_heap_plan(h, pin.n_rows, true).waves > 0)
+          if (h->heap_ok && choose_heap_plan(h, pin.n_rows, true, false).waves > 0)
             h->heap_bok = make_ragged_heaps(h, h->ragged_brec, true, h->bheap, nullptr);
           if (!h->ragged_bplan.global_nodes)
             h->ragged_bplan.n_chunks = ragged_chunks(h, h->ragged_bplan.chunk_bytes,
@@ -2713,7 +2714,7 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
   Plan p{};
   double forest_bytes = 0;
   if (takes_heaps(h, n_rows, false, false, h->F % 4 == 0 && h->pre_kind == BRIDGER_PRE_NONE)) {
-    p = choose_heap_plan(h, n_rows, false);
+    p = choose_heap_plan(h, n_rows, false, false);
     forest_bytes = 8.0 * h->ragged_rec.size();
   } else if (h->kernel_active == kPerfect) {
     const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, false);

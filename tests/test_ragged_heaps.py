@@ -90,6 +90,39 @@ def test_heap_layout(depth):
             assert np.array_equal(words.view(np.float32), ref_val)
 
 
+@pytest.mark.parametrize("kind", ["normal", "tail", "few", "wide", "denormal", "infinite"])
+@pytest.mark.parametrize("perfect", [False, True])
+def test_ranks_of_any_thresholds(kind, perfect):
+    """The tables of thresholds (packed arrays 5 and 6; long ones are sorted by their bits) are the sorted
+    distinct ones, and the heaps of ranks lead bins to the oracle's leaves, whatever the spread."""
+    rng = np.random.default_rng(len(kind))
+    draw = {"normal": rng.standard_normal, "tail": lambda n: np.exp(9 * rng.standard_normal(n)) * rng.choice([-1, 1], n),
+            "few": lambda n: rng.choice([-1.5, -0.0, 0.0, 2.0], n), "wide": lambda n: rng.uniform(-3.4e38, 3.4e38, n),
+            "denormal": lambda n: rng.integers(-9, 9, n) * 1e-45,
+            "infinite": lambda n: np.where(rng.random(n) < 0.1, rng.choice([-np.inf, np.inf], n), rng.standard_normal(n))}[kind]
+    F = 2
+    if perfect:
+        trees = [perfect_tree_arrays(7, rng.integers(0, F, 127), draw(127).astype(np.float32),
+                                     rng.standard_normal(128).astype(np.float32)) for _ in range(40)]
+        model = concat_trees(trees, F)
+    else:
+        model = random_tiny_forest(rng, 40, F, max_depth=8, p_split=0.9)
+        model.threshold[:] = np.where(model.left >= 0, draw(model.n_nodes), 0.0).astype(np.float32)
+    tables = binning.tables(model)
+    X = np.concatenate([rng.choice(np.concatenate([t, np.nextafter(t, np.float32(np.inf)), VALUES]), (200, 1))
+                        for t in tables], 1).astype(np.float32)
+    _, ref_lv, _ = oracle.predict(model, X, want_leaves=True)
+    with B.Forest(model, host_only=True) as f:
+        values = B.bridger_forest_packed(f.handle, 5, np.float32)
+        off = B.bridger_forest_packed(f.handle, 6, np.int32)
+        f.kernel = B.BRIDGER_KERNEL_RAGGED
+        lv, _ = walk_heaps(f, X, binning.bin_rows(tables, X))
+    for i, t in enumerate(tables):
+        assert np.array_equal(values[off[i]:off[i + 1]], t)
+    assert kind in ("few", "denormal") or np.diff(off).min() > 1024
+    assert np.array_equal(lv, ref_lv)
+
+
 def test_heap_layout_vector_leaves():
     """Vector leaves: a leaf's word is its place among the leaf records."""
     rng = np.random.default_rng(7)

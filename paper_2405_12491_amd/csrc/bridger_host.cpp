@@ -1718,14 +1718,15 @@ Plan choose_direct_plan(const bridger_forest *h, int64_t n_rows) {
 // 20,000 rows, us, tile / row by row / row by row on 16-byte records: 1 tree: 10,000 x 28 rows 11 / 8 / 9,
 // 10,000 x 256 26 / 9 / 9, 100,000 x 600 530 / 33 / 34; 3 trees, 100,000 rows: 63 features 40 / 58 / 64, 90 71 /
 // 48 / 58; 6 trees, 1,000 x 600 29 / 41 / 43; 8 trees, 100,000 rows: 256 features 115 / 176 / 199, 400 251 / 213
-// / 227.  From 12 trees the tile won everywhere (1.3 to 22 times).  Large tables: the limit is lower where one
+// / 227.  From 9 trees, which three waves or more share, the tile
+// won everywhere (10, 200,000 x 600 483 / 620 / 699).  Large tables: the limit is lower where one
 // tile fills a CU's LDS, and higher for rows of two lines that are read whole either way (1 tree, 300,000 x 48
 // 41 / 63 / 69, 300,000 x 28 32 / 30 / 37).  aligned: rows that the tile is filled from by whole lines.
 bool takes_direct_tile(const bridger_forest *h, int64_t n_rows, bool aligned) {
   if (!h->pair_ok) return false;
   if (h->direct_tile >= 0) return h->direct_tile == 1;
   const int64_t T = h->n_trees, F = h->F, pairs = T * T - 1;
-  if (T >= 12) return true;
+  if (T >= 9) return true;
   if (n_rows < 32768) return T >= 6 || F <= (aligned ? 20 : 12) * pairs;
   if (aligned && T < 4 && F >= 32 && F <= 64 * T && n_rows * F * 4 > 56000000) return true;
   return F <= (aligned ? std::min(20 * pairs, 48 * T) : std::min(9 * pairs, 36 * T));

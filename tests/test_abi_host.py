@@ -675,7 +675,8 @@ def test_views_handed_out_stay_as_they_are():
 
 @pytest.mark.parametrize("trees,F,n_rows,rows", [(1, 28, 10_000, 256), (1, 600, 100_000, 256), (1, 48, 300_000, 64),
                                                  (3, 90, 100_000, 256), (3, 64, 100_000, 64), (4, 300, 1_000, 64),
-                                                 (4, 301, 1_000, 256), (6, 600, 1_000, 64), (12, 600, 100_000, 64)])
+                                                 (4, 301, 1_000, 256), (6, 600, 1_000, 64), (8, 600, 100_000, 256),
+                                                 (9, 600, 100_000, 64)])
 def test_direct_few_large_trees(trees, F, n_rows, rows):
     """Few large trees on wide rows are walked row by row (256 rows a workgroup): a tile would read
     every feature of a row for the few that its paths meet."""

@@ -1667,10 +1667,7 @@ bool stays_perfect(const bridger_forest *h, int64_t n_rows, bool binned, bool le
   if (whole_lines && D == 5 && F > kHeapWideFeatures && F < 400 && p.rows_per_wg == 64) return true;
   // Row-a-lane tiles in small batches: every lane group of the walk loads its own (133 trees of depth 5, 99
   // features, 4,548 rows scaled 9.9 / 7.7; 281, 195 features, 2,309 rows 14.7 / 10.6).
-  if (!whole_lines && F >= 80 && rounds(p) <= 0.64 && 0.22 * p.groups >= p.n_chunks) return true;
-  // A chunk or two for many lane groups, and a tile that leaves the walk one workgroup of at most 10 waves (24 trees
-  // of depth 8, 255 features, 2,180 rows 10.9 / 8.0).
-  return L <= 11360 && w.waves_per_cu <= 10 && 0.16 * p.groups >= p.n_chunks;
+  return !whole_lines && F >= 80 && rounds(p) <= 0.64 && 0.22 * p.groups >= p.n_chunks;
 }
 
 // Whether a prediction of n_rows rows takes the padded-heap kernel.

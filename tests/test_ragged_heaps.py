@@ -264,7 +264,7 @@ def test_perfect_small_batches(n_rows):
     (4, 1000, 28, 40_000, False), (1, 897, 71, 167_000, False), (3, 1125, 21, 671, True), (4, 164, 157, 116_000, True),
     (6, 100, 28, 10_000, True), (8, 18, 16, 33_000, True), (7, 18, 16, 33_000, False), (8, 8, 58, 90_000, False),
     (8, 5, 226, 252_000, False), (8, 5, 228, 252_000, True), (6, 43, 250, 240_000, False), (6, 463, 209, 200_000, True),
-    (8, 24, 256, 2_180, False), (8, 48, 256, 2_180, True), (5, 281, 195, 2_309, False), (6, 95, 18, 59_458, False),
+    (5, 281, 195, 2_309, False), (6, 95, 18, 59_458, False),
     (6, 95, 18, 29_000, True), (5, 143, 300, 77_537, False), (5, 143, 299, 77_537, True), (6, 500, 28, 1_000, True), (6, 500, 28, 1_000_000, False)])
 def test_perfect_walk_rule(D, T, F, n, walk):
     """Which perfect forests AUTO gives to the padded-heap walk (no chunks in the plan): on both sides of

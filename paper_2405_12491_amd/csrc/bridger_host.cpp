@@ -1626,6 +1626,11 @@ const bridger_forest::SizedPlan *sized_plan(const bridger_forest *h, int64_t n_r
   return nullptr;
 }
 
+// Rounds of workgroups on the chip.
+double plan_rounds(const Plan &p, int64_t n_rows) {
+  return std::ceil((double)n_rows / p.rows_per_wg) / ((double)kNumCUs * std::max(p.waves_per_cu / p.waves, 1));
+}
+
 // Perfect forests for which the walk, though the rules above would give it to them, takes longer than PERFECT
 // (us, heap walk / PERFECT).  Of 2,100 forests and batches (1 to 9 levels, 3 to 1,200 trees, 5 to 700 features,
 // 200 to 700,000 rows) other than those the clauses come from, 2.5% take over 5% longer than with PERFECT;
@@ -1635,9 +1640,7 @@ bool stays_perfect(const bridger_forest *h, int64_t n_rows, bool binned, bool le
   const bridger_forest::SizedPlan *sp = sized_plan(h, n_rows, binned);
   const Plan &p = sp ? sp->plan : binned ? h->perfect_bplan : h->perfect_plan;
   const Plan &w = choose_heap_plan(h, n_rows, binned, leaves);
-  auto rounds = [&](const Plan &q) {  // of workgroups on the chip
-    return std::ceil((double)n_rows / q.rows_per_wg) / ((double)kNumCUs * std::max(q.waves_per_cu / q.waves, 1));
-  };
+  auto rounds = [&](const Plan &q) { return plan_rounds(q, n_rows); };
   const int D = h->perfect_depth, F = h->F;
   const int64_t T = h->n_trees, L = T << D;
   // Few leaves: one or two chunks, staged while the tile loads (leaf ids, 13,642 x 72 rows, 14 trees of depth 8 6.8 /
@@ -1670,10 +1673,19 @@ bool stays_perfect(const bridger_forest *h, int64_t n_rows, bool binned, bool le
   return !whole_lines && F >= 80 && rounds(p) <= 0.64 && 0.22 * p.groups >= p.n_chunks;
 }
 
+// Bins of ragged forests with few trees for each of many classes: the walk's class sums, one per class, lane
+// group and row, are then most of its LDS and of its work, and from its second round the record walk's larger
+// tiles (of 8-bit bins, where those suffice) take less (us, heap walk / record walk: 40 trees of depth 11, 20 classes,
+// 144 features, 217,000 rows 150 / 103; 38 of depth 9, 32 classes, 289 features, 18,600 rows 78 / 55).
+bool few_trees_a_class(const bridger_forest *h, bool binned) {
+  return binned && !h->vec && h->K >= 12 && h->K < 40 && h->n_trees <= 3 * h->K;
+}
+
 // Whether a prediction of n_rows rows takes the padded-heap kernel.
 bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves, bool whole_lines) {
   if (!(binned ? h->heap_bok : h->heap_ok)) return false;
-  if (h->kernel_active == kRagged) return true;
+  if (h->kernel_active == kRagged)
+    return !few_trees_a_class(h, binned) || leaves || plan_rounds(choose_heap_plan(h, n_rows, true, false), n_rows) <= 1.1;
   if (h->kernel_active != kPerfect || !h->kernel_auto || !h->perfect_heap) return false;
   const bool few_rows = h->F >= kHeapLoadFeatures && n_rows <= kHeapTileRows;
   if ((int64_t)h->n_trees << h->perfect_depth <= (few_rows ? kHeapTileLeaves : kHeapLeaves)) return false;
@@ -1910,9 +1922,9 @@ bridger_status upload_all(bridger_forest *h) {
     if (h->heap_bok) {
       up.add(&h->bheap.d_tops, h->bheap.tops);
       up.add(&h->bheap.d_blocks, h->bheap.blocks);
-    } else if (!h->ragged_btops.empty()) {
-      up.add(&h->d_ragged_btops, h->ragged_btops);
     }
+    if (!h->ragged_btops.empty() && (!h->heap_bok || few_trees_a_class(h, true)))
+      up.add(&h->d_ragged_btops, h->ragged_btops);
   }
   if (h->pair_ok) {
     up.add(&h->d_direct.nodes, h->pair_rec);

@@ -378,3 +378,26 @@ def test_binned_tables(depth, bits):
             assert q.element_size() * 8 == bits
             assert_scores(f.predict_binned(q).cpu().numpy(), ref, what)
             assert np.array_equal(f.predict_binned_leaves(q).cpu().numpy(), ref_lv), what
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("depth,K,T", [(8, 13, 20), (10, 32, 96), (8, 39, 39)])
+def test_bins_of_few_trees_a_class(depth, K, T):
+    """Many classes of few trees: small batches of bins on the padded heaps, larger ones on the record walk."""
+    import dataclasses
+
+    import torch
+    rng = np.random.default_rng(K)
+    F = 4
+    model = dataclasses.replace(random_tiny_forest(rng, T, F, max_depth=depth, p_split=0.9), n_classes=K,
+                                transform=XFORM_SOFTMAX, base_score=rng.standard_normal(K).astype(np.float32))
+    X = rng.standard_normal((40_001, F)).astype(np.float32)
+    ref, ref_lv, _ = oracle.predict(model, X, want_leaves=True, threads=8)
+    Xd = torch.from_numpy(X).cuda()
+    with B.Forest(model) as f:
+        assert f.kernel == B.BRIDGER_KERNEL_RAGGED
+        for n in (1, 1000, 40_001):
+            q = f.bin(Xd[:n])
+            print(f"K={K} T={T} rows={n} {q.dtype}", flush=True)
+            assert_scores(f.predict_binned(q).cpu().numpy(), ref[:n], f"K={K} rows={n}")
+            assert np.array_equal(f.predict_binned_leaves(q).cpu().numpy(), ref_lv[:n])

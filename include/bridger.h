@@ -332,13 +332,13 @@ bridger_status bridger_forest_plan(bridger_forest_t h, int64_t n_rows, int32_t *
  * w(2m + 1), f(m) | f(2m) << 10 | f(2m + 1) << 20} per node m of a pair's upper level, then
  * either one block {w(m), f(m), leaf value of 2m, of 2m + 1} per node of the last level or
  * the 2^D leaf values (absent with vector leaves or more than 1024 features).  10 to 13, one-class
- * ragged trees as two-level treelets, a view made at the call (absent when the plan does not use
- * heaps): 10 the blocks (16 bytes a slot: a 4-ary heap per tree, slot s holding a node of an even
- * level and its two children, {w(n), v(c0), v(c1), f(n) | f(c0) << 10 | f(c1) << 20 | leaf(c0) <<
- * 30 | leaf(c1) << 31}, v the child's threshold or leaf value; the grandchild of steps b1, b2 in
- * slot 4s + 1 + 2 b1 + b2; a leaf n as {0, v(n), v(n), 3 << 30}), 11 each kernel tree's first slot
- * (int32 [n_trees + 1]), 12 the leaf id of each slot's two children (int32 pairs), 13 the blocks
- * with ranks in place of thresholds.  14 to 18, the ragged trees' padded heaps that the kernel
+ * ragged trees as two-level treelets, a view that no kernel walks, made at the call for readers of
+ * the layout (absent when the plan does not use heaps): 10 the blocks (16 bytes a slot: a 4-ary
+ * heap per tree, slot s holding a node of an even level and its two children, {w(n), v(c0), v(c1),
+ * f(n) | f(c0) << 10 | f(c1) << 20 | leaf(c0) << 30 | leaf(c1) << 31}, v the child's threshold or
+ * leaf value; the grandchild of steps b1, b2 in slot 4s + 1 + 2 b1 + b2; a leaf n as {0, v(n),
+ * v(n), 3 << 30}), 11 each kernel tree's first slot (int32 [n_trees + 1]), 12 the leaf id of each
+ * slot's two children (int32 pairs), 13 the blocks with ranks in place of thresholds.  14 to 18, the ragged trees' padded heaps that the kernel
  * walks (absent when the plan does not use them): 14 the top levels (L = 5, 6 or 7: a complete
  * 1-based heap of 2^L 8-byte records {threshold, f << 8} per tree, slot 0 {first block}; 4 zero
  * heaps follow the last tree, 2 when L = 7), 15 below them a 4-byte leaf word per slot of level L

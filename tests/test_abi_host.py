@@ -617,9 +617,10 @@ def walk_treelets(f: B.Forest, X, bins=None):
 
 @pytest.mark.parametrize("seed", range(6))
 def test_ragged_treelets(seed):
-    """Random one-class ragged forests (single-leaf trees, leaves at every level, depths up to
-    11, ties, NaN and infinite inputs) packed as two-level treelets: walking them reproduces
-    the oracle's leaf ids and leaf values, on fp32 rows and on bins."""
+    """The view of two-level treelets, which no kernel walks (the padded heaps of arrays 14-18 have their
+    own test): random one-class ragged forests (single-leaf trees, leaves at every level, depths up to
+    11, ties, NaN and infinite inputs); walking the view reproduces the oracle's leaf ids and leaf
+    values, on fp32 rows and on bins."""
     rng = np.random.default_rng(300 + seed)
     F = int(rng.integers(1, 12))
     model = random_tiny_forest(rng, int(rng.integers(1, 30)), F, max_depth=int(rng.integers(0, 12)),

@@ -324,14 +324,14 @@ def _variant_models():
                                  {"BRIDGER_ROWS": "256", "BRIDGER_WAVES": "8"},
                                  {"BRIDGER_TREELETS": "0", "BRIDGER_ROWS": "256", "BRIDGER_WAVES": "8"},
                                  {"BRIDGER_COALESCED_TILE": "0"},
-                                 {"BRIDGER_TREELET_LDS_LEVELS": "2"},
-                                 {"BRIDGER_TREELET_LDS_LEVELS": "2", "BRIDGER_ROWS": "256", "BRIDGER_WAVES": "8"}],
+                                 {"BRIDGER_HEAP_LEVELS": "5"}, {"BRIDGER_HEAP_LEVELS": "6"},
+                                 {"BRIDGER_HEAP_LEVELS": "7"}],
                          ids=lambda e: ",".join(f"{k[8:]}={v}" for k, v in e.items()))
 def test_ragged_kernel_variants(env, monkeypatch):
-    """The ragged kernel with records in LDS chunks and read from global memory (one or two
-    runs per lane; two-level treelets, or the top levels from per-wave LDS copies of 4 or 5
-    levels, with lane groups of one, two or four waves, or without them), on ragged,
-    multiclass and leaf-id cases."""
+    """The ragged kernels: the padded-heap walk (5, 6 or 7 top levels), and the record walk with
+    records in LDS chunks or read from global memory (one or two runs per lane; the top levels
+    from per-wave LDS copies of 4 or 5 levels, with lane groups of one, two or four waves, or
+    without them), on ragged, multiclass and leaf-id cases."""
     for k, v in env.items():
         monkeypatch.setenv(k, v)
     rng = np.random.default_rng(91)

@@ -1027,7 +1027,7 @@ constexpr int kBinCoarsest = 4;
 
 int32_t bin_words(int32_t n, int coarse) {  // words of a feature of the image
   const int32_t cells = std::max((n + (1 << coarse) - 1) >> coarse, 1);
-  return (n + 8 + (cells + 1) / 2 + 3) & ~3;
+  return n + 8 + (cells + 1) / 2;
 }
 
 void make_bin_tables(bridger_forest *h) {
@@ -1041,7 +1041,7 @@ void make_bin_tables(bridger_forest *h) {
     for (; c <= kBinCoarsest; ++c) {
       int64_t bytes = 0;
       for (int32_t f = f0; f < f1; ++f) bytes += 4 * (int64_t)bin_words(table(f), c);
-      if (bytes <= cap) break;
+      if (bytes + 24 <= cap) break;  // (a run is staged from and to a multiple of 16 bytes)
     }
     return c;
   };
@@ -1076,11 +1076,11 @@ void make_bin_tables(bridger_forest *h) {
       if (c + 1 < cells) lower += count[c + 1];
       h->bin_image.push_back(first | second << 16);
     }
-    while (h->bin_image.size() % 4) h->bin_image.push_back(0);
     return most;
   };
   std::vector<int32_t> fullest(F, 0), word0(F + 1, 0), coarse(F, 0);  // word0: first word of a feature
   for (int32_t f = 0; f < F; ++f) {
+    while (f % 4 == 0 && h->bin_image.size() % 4) h->bin_image.push_back(0);
     word0[f] = (int32_t)h->bin_image.size();
     const float *v = h->q_values.data() + h->q_off[f];
     const int32_t n = table(f);
@@ -1092,10 +1092,12 @@ void make_bin_tables(bridger_forest *h) {
     if (n) std::memcpy(&h->bin_image[word0[f]], v, (size_t)4 * n);
     fullest[f] = make_grid(h->bin_features[f], v, n, coarse[f]);
   }
+  while (h->bin_image.size() % 4) h->bin_image.push_back(0);
   word0[F] = (int32_t)h->bin_image.size();
 
+  auto words = [&](int32_t f0, int32_t f1) { return ((word0[f1] + 3) & ~3) - (word0[f0] & ~3); };
   auto run = [&](int32_t f0, int32_t f1, bool staged) {
-    BinRun r{f0, f1, word0[f0], word0[f1] - word0[f0], staged ? 1 : 0, 0};
+    BinRun r{f0, f1, word0[f0] & ~3, words(f0, f1), staged ? 1 : 0, 0};
     const int32_t most = *std::max_element(fullest.begin() + f0, fullest.begin() + f1);
     if (most > 0) r.steps = 1 << ilog2(most);
     return r;
@@ -1108,7 +1110,7 @@ void make_bin_tables(bridger_forest *h) {
       int32_t fe = f;
       while (fe < F && fe - f < 1024) {
         const int32_t next = std::min(F, fe + unit);
-        if (4 * (int64_t)(word0[next] - word0[f]) > bytes) break;
+        if (4 * (int64_t)words(f, next) > bytes) break;
         fe = next;
       }
       const bool fits = fe > f;
@@ -1135,6 +1137,7 @@ void make_bin_tables(bridger_forest *h) {
   h->bin_features_in_place = h->bin_features;
   for (int32_t f = 0; f < F; ++f)
     if (coarse[f]) fullest[f] = make_grid(h->bin_features_in_place[f], h->q_values.data() + h->q_off[f], table(f), 0);
+  while (h->bin_image.size() % 4) h->bin_image.push_back(0);
   h->bin_in_place = {};
   for (int32_t f = 0; f < F; f += 1024) h->bin_in_place.runs.push_back(run(f, std::min(F, f + 1024), false));
   if (env_int("BRIDGER_LOG", 0))

@@ -222,7 +222,7 @@ int launch_perfect_binned(int depth, const LaunchArgs &a, int waves, int64_t n_w
                           void *stream);
 // Binning tables: an image of 32-bit words holding, feature after feature, its distinct thresholds
 // ascending, 8 words of +inf, and (16 bits each) for every cell of a grid over them the number of
-// thresholds in lower cells, a multiple of 4 words in all; x lies in cell (uint)min(max((x - lo) * scale, 0), top), in fp32.
+// thresholds in lower cells; x lies in cell (uint)min(max((x - lo) * scale, 0), top), in fp32.
 struct BinFeature {
   float lo, scale, top;  // top: cells - 1
   int32_t n;             // thresholds
@@ -233,7 +233,7 @@ struct BinFeature {
 // A run of features that one workgroup looks up.
 struct BinRun {
   int32_t f0, f1;        // at most 1024 features
-  int32_t word0, words;  // their part of the image (multiples of 4 words)
+  int32_t word0, words;  // their part of the image, from and to multiples of 4 words
   int32_t staged;        // it is copied to LDS (a table too large for it is searched in place)
   int32_t steps;         // largest power of two in the fullest cell's count
 };

@@ -689,7 +689,8 @@ def test_direct_few_large_trees(trees, F, n_rows, rows):
         assert f.plan(n_rows)["rows_per_wg"] == rows
 
 
-@pytest.mark.parametrize("F,n", [(28, 910), (28, 4553), (28, 7204), (28, 9500), (28, 12_000), (7, 8700), (3, 30_000)])
+@pytest.mark.parametrize("F,n", [(28, 910), (28, 4553), (28, 7204), (28, 9500), (28, 12_000), (7, 8700), (3, 30_000),
+                                 (760, 66)])
 def test_bin_tables_are_staged(F, n, monkeypatch, capfd):
     """Tables that a column or four of them can bring to LDS are staged, whatever the number of runs:
     none of a forest's features stays in place in the layout that its rows take."""
@@ -708,3 +709,5 @@ def test_bin_tables_are_staged(F, n, monkeypatch, capfd):
     assert any(c == "1" and in_place == "0" for c, _, in_place, _ in log)
     if F % 4 == 0 and n < 9600:  # four columns, 4 bytes a threshold and at least 2 a cell of 16
         assert any(c == "4" and in_place == "0" for c, _, in_place, _ in log)
+    if F == 760:  # 107 words a feature, 95 quads a run: no words lost between a quad's features
+        assert [runs for c, runs, *_ in log if c == "4"] == ["2"]

@@ -5,7 +5,7 @@
 // so it goes right at every split as the fp32 compare sends it).
 //
 // A value is looked up in two steps (layout in internal.h: bin tables): a uniform grid over the
-// feature's thresholds, one cell per threshold, gives the number of thresholds in lower cells, and
+// feature's thresholds, one cell per threshold (or per 2 to 16), gives the number of thresholds in lower cells, and
 // a search over power-of-two steps counts those of its own cell, as many steps as the fullest cell
 // of the run of features needs (3 or 4 where thresholds are drawn from the data, against 10 to 12
 // for the whole table).  A cell is the truncated product fl(fl(x - lo) * scale), which never
@@ -16,8 +16,9 @@
 // aligned for it, so the features' parameters stay in registers, the loads and stores of a
 // wave are consecutive, and no index is divided.
 // Measured against the binary search over whole tables (32-feature groups, one element a lane):
-// 1M x 28 rows, 910 thresholds a feature, 135 -> 44 us; 100k x 784, 325: 343 -> 134 us; 4M x 256, 2,750
-// (16 runs of features, whose partial lines are what is left): 8.6 -> 4.0 ms.
+// 1M x 28 rows, 910 thresholds a feature, 121 -> 40 us, 4,553 265 -> 180, 12,000 (a column a thread) 735 ->
+// 280; 100k x 784, 66 (8-bit bins): 343 -> 146 us; 4M x 256, 2,750 (32 runs of 8 features, whose partial
+// lines are what is left): 8.6 -> 4.1 ms.
 #include "kernel_common.h"
 
 namespace bridger {

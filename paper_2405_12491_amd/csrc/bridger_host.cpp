@@ -1292,7 +1292,7 @@ void build_sized_plans(bridger_forest *h, PlanInput pin, const Plan &big, bool b
   // Leaf ids of large batches, trees of at most 6 levels: with one lane group a row's ids come 16
   // trees at a time and its lines reach memory in pieces (1.55x the bytes); four lane groups take
   // consecutive trees of a chunk, so that a row's 64 bytes are written at once by four waves.  200k x
-  // 28 rows: 500 trees of depth 6 258 -> 219 us, 300 of depth 4 167 -> 86; with deeper trees the
+  // 28 rows: 500 trees of depth 6 258 -> 229 us, 300 of depth 4 167 -> 86; with deeper trees the
   // chunks that four groups need cost the walk more (100 of depth 8: 53 -> 77).
   if (big.groups == 1 && pin.depth <= 6 && env_int("BRIDGER_WAVES", 0) == 0 && env_int("BRIDGER_ROWS", 0) == 0) {
     pin.n_rows = int64_t(1) << 20;

@@ -12,10 +12,10 @@
 //     a feature's row spans 64 elements, so a mask and an or make the address; the fields of the
 //     children come to the same place by one rotate).  A step of a lane that has reached its
 //     leaf computes the same step again with the same result: only the loads are masked.
-// Measured on 1000 trees up to depth 12, 4M x 256 rows: 89 VALU and 27 scalar instructions and
-// 3.7 wave-wide loads per (wave, tree) (one VALU instruction per clock and CU, addresser 89%
-// busy), 9.34 ms; the treelet walk it replaced took 114, 92 and 4.0 and 14.1 ms.  100 trees of
-// depth 12 over 1M x 28 rows: 0.227 ms (0.362).
+// Measured on 1000 trees up to depth 12, 4M x 256 rows: 89 VALU and 28 scalar instructions and
+// 3.9 wave-wide loads (row tile and copies included) per (wave, tree), one VALU instruction per
+// clock and CU, addresser 91% busy, 9.42 ms; the treelet walk it replaced took 114, 92 and 4.0 and
+// 14.1 ms.  100 trees of depth 12 over 1M x 28 rows: 0.227 ms (0.362).
 #pragma once
 #include "perfect_walk.h"
 #include "vector_leaves.h"
@@ -281,8 +281,8 @@ __global__ __launch_bounds__(1024) void ragged_heap_kernel(LaunchArgs a) {
         }
       }
     } else if (VK != 0) {
-      // 5..8 classes: one tree's row at a time (four in flight took 86 registers: 128 us against
-      // 124 for 300k x 28 rows, 100 trees, 7 classes)
+      // 5..8 classes: one tree's row at a time (four in flight took 86 registers and 3% longer for
+      // 300k x 28 rows, 100 trees, 7 classes, which take 130 us)
       constexpr int VN = VK == 8 ? 1 : U;
       if (nvalid == U) {
 #pragma unroll

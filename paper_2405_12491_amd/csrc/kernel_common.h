@@ -373,51 +373,56 @@ __device__ void finalize_store(const LaunchArgs &a, double *z, int stride, int64
   }
 }
 
+constexpr int kSoftmaxSumAll = 8;  // classes whose sum every thread finds itself, for want of a barrier
+
 // Tile epilogue of the kernels whose G lane groups hold partial class sums: slot (k, g, r) at
-// z0[k * stride + g * R + r].  Each (row, class) sum is added in group order by one of the R * G
-// compute threads (threads 0 .. R * G - 1 of a tile of rows blockIdx.x * R + r, R a power of
-// two; every one of them calls this after a barrier) into slot (k, 0, r); then the first
-// group's lanes (tid < R) finish and store their rows.
+// z0[k * stride + g * R + r].  Each (row, class) sum is added in group order into slot (k, 0, r) by
+// compute thread r + R * (k mod G) (threads 0 .. R * G - 1 of a tile of rows blockIdx.x * R + r, R a power
+// of two; every one of them calls this after a barrier); then the first group's lanes (tid < R) finish
+// and store their rows.
+// Softmax: a row's G threads share its K values (same operations, same order as finalize_store: a maximum
+// is exact in any order).  Class k's slots are its own thread's until the second barrier, so a thread's
+// maximum goes into slot (g, 1, r) and its exponentials into (k, 0, r).  Each value is read once, by one
+// thread: with one lane a row all but one group wait, and a thread that finds the maximum for each of its classes
+// reads K^2 / G values (us, so / now: 46 trees of depth 6, 32 classes, 170,630 x 17 rows in 4 groups 214 / 91; 60 classes, 80
+// trees of depth 5, 3,457 x 115 rows 65 / 20; one lane a row, 81 trees of depth 12, 37 classes, 352,321 x 12 rows 733 / 388).
 __device__ void groups_finalize_store(const LaunchArgs &a, double *z0, int R, int G, int stride,
                                       int tid, int64_t row, bool row_ok) {
   if (G > 1) {
-    for (int i = tid; i < R * a.K; i += R * G) {
-      const int k = i / R;
-      double *z = z0 + k * stride + (i - k * R);
+    const int K = a.K, r = tid & (R - 1), g = tid / R;
+    const bool softmax = a.transform == 2 && !a.out_label && K > 1;
+    double m = -__builtin_inf();
+    for (int k = g; k < K; k += G) {
+      double *z = z0 + k * stride + r;
       double s = z[0];
       for (int gg = 1; gg < G; ++gg) s += z[gg * R];
+      if (softmax) {
+        if (a.aggregate == 1) s = (double)a.base[k] + s / (double)a.class_count[k];
+        m = k == 0 || s > m ? s : m;
+      }
       z[0] = s;
     }
+    double *p = z0 + R + r;
+    if (softmax && g < K) p[g * stride] = m;
     __syncthreads();
-    // softmax, one (row, class) per thread as well: each thread finishes its row's K values
-    // as finalize_store does (same operations, same order) and writes its exponential into
-    // the second group's slot, free now; then each divides by the row's sum.  A thread reads all K
-    // values for each of its K / G classes, so many classes and few groups are left to one lane per
-    // row (64 trees of depth 9, 64 classes, 42,516 x 23 rows in two groups: bins 77 us, 430
-    // with a class a thread, 70 on the record walk's one group)
-    if (a.transform == 2 && !a.out_label && a.K > 1 && a.K <= 12 * (G - 1)) {
-      const int K = a.K;
-      const int64_t row0 = (int64_t)blockIdx.x * R;  // the tile's first row
-      for (int i = tid; i < R * K; i += R * G) {
-        const int k = i / R, rr = i - k * R;
-        const double *z = z0 + rr;
-        auto v = [&](int j) {
-          const double x = z[j * stride];
-          return a.aggregate == 1 ? (double)a.base[j] + x / (double)a.class_count[j] : x;
-        };
-        double m = v(0);
-        for (int j = 1; j < K; ++j) m = v(j) > m ? v(j) : m;
-        z0[k * stride + R + rr] = exp(v(k) - m);
-      }
+    if (softmax) {
+      const int n = G < K ? G : K;
+      m = p[0];
+      for (int j = 1; j < n; ++j) m = p[j * stride] > m ? p[j * stride] : m;
+      double *e = z0 + r;
+      for (int k = g; k < K; k += G) e[k * stride] = exp(e[k * stride] - m);
       __syncthreads();
-      for (int i = tid; i < R * K; i += R * G) {
-        const int k = i / R, rr = i - k * R;
-        if (row0 + rr >= a.n_rows) continue;
-        const double *e = z0 + R + rr;
-        double sum = 0.0;
-        for (int j = 0; j < K; ++j) sum += e[j * stride];
-        a.out[(row0 + rr) * (int64_t)K + k] = (float)(e[k * stride] / sum);
+      double sum = 0.0;
+      if (K <= kSoftmaxSumAll || g == 0)
+        for (int k = 0; k < K; ++k) sum += e[k * stride];
+      if (K > kSoftmaxSumAll) {  // one group's lanes add for the others
+        if (g == 0) p[0] = sum;
+        __syncthreads();
+        sum = p[0];
       }
+      const int64_t out_row = (int64_t)blockIdx.x * R + r;
+      if (out_row >= a.n_rows) return;
+      for (int k = g; k < K; k += G) a.out[out_row * (int64_t)K + k] = (float)(e[k * stride] / sum);
       return;
     }
   }

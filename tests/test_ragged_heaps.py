@@ -383,7 +383,7 @@ def test_binned_tables(depth, bits):
 @pytest.mark.gpu
 @pytest.mark.parametrize("depth,K,T", [(8, 13, 20), (10, 32, 96), (8, 39, 39)])
 def test_bins_of_few_trees_a_class(depth, K, T):
-    """Many classes of few trees: small batches of bins on the padded heaps, larger ones on the record walk."""
+    """Bins of many classes of few trees, in batches of each plan."""
     import dataclasses
 
     import torch
@@ -401,3 +401,29 @@ def test_bins_of_few_trees_a_class(depth, K, T):
             print(f"K={K} T={T} rows={n} {q.dtype}", flush=True)
             assert_scores(f.predict_binned(q).cpu().numpy(), ref[:n], f"K={K} rows={n}")
             assert np.array_equal(f.predict_binned_leaves(q).cpu().numpy(), ref_lv[:n])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,F,agg", [(2, 5, AGG_MEAN), (8, 5, AGG_SUM), (9, 5, AGG_MEAN), (33, 90, AGG_SUM), (60, 160, AGG_MEAN),
+                                     (64, 5, AGG_SUM)])
+def test_softmax_of_many_classes(K, F, agg):
+    """The classes of a row shared by its lane groups: fewer classes than groups, as many, more; groups of 16 and 32
+    rows, 2 waves of the former where the sums of 4 do not fit, and 64-row groups of few waves."""
+    import dataclasses
+
+    import torch
+    rng = np.random.default_rng(K)
+    base = rng.standard_normal(K).astype(np.float32)
+    base[0] = -np.inf  # the first class's score, from which the maximum starts
+    model = dataclasses.replace(random_tiny_forest(rng, 2 * K + 1, F, max_depth=8, p_split=0.9), n_classes=K, aggregate=agg,
+                                transform=XFORM_SOFTMAX, base_score=base)
+    X = rng.standard_normal((30_001, F)).astype(np.float32)
+    ref, _, _ = oracle.predict(model, X, threads=8)
+    assert np.isfinite(ref).all() and not ref[:, 0].any()
+    Xd = torch.from_numpy(X).cuda()
+    with B.Forest(model) as f:
+        assert f.kernel == B.BRIDGER_KERNEL_RAGGED
+        for n in (1, 130, 4096, 5003, 30_001):
+            print(f"K={K} rows={n}", flush=True)
+            assert_scores(f.predict(Xd[:n]).cpu().numpy(), ref[:n], f"K={K} rows={n}")
+            assert_scores(f.predict_binned(f.bin(Xd[:n])).cpu().numpy(), ref[:n], f"bins K={K} rows={n}")

@@ -1545,11 +1545,32 @@ Plan heap_plan(const bridger_forest *h, int R, int W, bool binned, bool leaves) 
 //     add to the launch (16 trees of depth 6, 28 features, 50,000 rows: 16 waves 10.6, 4 waves 5.2).
 //   * Else groups of 64 rows (32 in a 32-column tile), and the W that puts the most waves on the chip; the fewest of equals
 //     (1M x 28 rows, 100 trees of depth 12: W = 2 0.225 ms, 4 0.236, 8 0.261).
-constexpr int kHeapLoadFeatures = 64;
+//   * Ragged forests of kHeapManyClasses classes and more, whose sums cost a wave about a tree's walk for each class
+//     however few its trees: the W of least estimated time (heap_estimate), and in small batches fewer
+//     waves than 4 where the sums of 4 do not fit (us, with / without: 39 trees of depth 3, 17 classes, 18,039 x 58 rows
+//     15.9 / 28.0 (16 waves, one workgroup a CU); 64 of 20 classes, 324,289 x 19 rows 85 / 142; 156 of depth 8, 60
+//     classes, 1,210 x 162 rows 33 / 55).  But none that leave a wave more than 24 features (64 of bins) to load: large batches
+//     of wide rows wait for them (47 trees of depth 10, 10 classes, 304,412 x 87 rows: 8 waves 104, 4 142, 2 188).
+constexpr int kHeapLoadFeatures = 64, kHeapManyClasses = 9;
+
+// Estimated time of a plan of the padded-heap walk on n_rows rows of several classes' sums (us): a wave's chain
+// of levels, classes and tile loads in every round, and the issue of all of a CU's waves.  The constants come from
+// 4,800 times of 1 to 16 waves on 1,474 forests and batches (2 to 64 classes, 3 to 12 levels, 2 to 700 trees, 5
+// to 600 features, 200 to 500,000 rows), which it meets within 24% root mean square: enough to order the plans of
+// one call.  Against the most waves 792 of those and others took 0.93 of the time with 9 classes and more, none over 1.05.
+double heap_estimate(const bridger_forest *h, const Plan &p, int64_t n_rows) {
+  const double tiles = std::ceil((double)n_rows / p.rows_per_wg);
+  const int W = p.waves, U = heap_batch(h->heap_levels), D = h->max_depth;
+  const int trees = (h->n_trees + p.groups - 1) / p.groups, batches = (trees + U - 1) / U;
+  const double load = (double)h->F / W;  // features that a wave loads
+  return 5.0 + std::ceil(tiles / ((double)kNumCUs * (p.waves_per_cu / W))) * (0.15 * batches * D + 0.2 * h->K + 0.25 * load) +
+         tiles / kNumCUs * W * (0.002 * trees * D + 0.017 * h->K + 0.009 * load);
+}
 
 const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves) {
   const int U = heap_batch(h->heap_levels);
   const int load_waves = h->F < kHeapLoadFeatures ? 4 : 8;
+  const bool many = h->kernel_active == kRagged && h->K >= kHeapManyClasses && !leaves && !h->heap_waves;
   n_rows = std::max<int64_t>(n_rows, 1);
   for (int R : {16, 32}) {
     const int gpw = 64 / R;
@@ -1565,6 +1586,13 @@ const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binne
       best = &p;
     }
     if (best) return *best;
+  }
+  for (int R : {16, 32}) {
+    if (!many || h->heap_rows || n_rows > (int64_t)R * kNumCUs || h->n_trees < 64 / R * U) continue;
+    for (int W : {2, 1}) {
+      const Plan &p = h->heap_plans[leaves][binned][ilog2(64 / R)][ilog2(W)];
+      if (p.waves) return p;
+    }
   }
   static const Plan none{};
   const Plan *best = &none;
@@ -1582,6 +1610,17 @@ const Plan &choose_heap_plan(const bridger_forest *h, int64_t n_rows, bool binne
     if (active <= most) continue;
     most = active;
     best = &p;
+  }
+  if (many && !h->vec && best->waves) {
+    double least = 0.9 * heap_estimate(h, *best, n_rows);
+    for (int W : {1, 2, 4, 8, 16}) {
+      const Plan &p = h->heap_plans[leaves][binned][ilog2(64 / R)][ilog2(W)];
+      if (!p.waves || (binned ? 64 : 24) * W < h->F) continue;
+      const double t = heap_estimate(h, p, n_rows);
+      if (t >= least) continue;
+      least = t;
+      best = &p;
+    }
   }
   return *best;
 }
@@ -1676,19 +1715,10 @@ bool stays_perfect(const bridger_forest *h, int64_t n_rows, bool binned, bool le
   return !whole_lines && F >= 80 && rounds(p) <= 0.64 && 0.22 * p.groups >= p.n_chunks;
 }
 
-// Bins of ragged forests with few trees for each of many classes: the walk's class sums, one per class, lane
-// group and row, are then most of its LDS and of its work, and from its second round the record walk's larger
-// tiles (of 8-bit bins, where those suffice) take less (us, heap walk / record walk: 40 trees of depth 11, 20 classes,
-// 144 features, 217,000 rows 150 / 103; 38 of depth 9, 32 classes, 289 features, 18,600 rows 78 / 55).
-bool few_trees_a_class(const bridger_forest *h, bool binned) {
-  return binned && !h->vec && h->K >= 12 && h->K < 40 && h->n_trees <= 3 * h->K;
-}
-
 // Whether a prediction of n_rows rows takes the padded-heap kernel.
 bool takes_heaps(const bridger_forest *h, int64_t n_rows, bool binned, bool leaves, bool whole_lines) {
   if (!(binned ? h->heap_bok : h->heap_ok)) return false;
-  if (h->kernel_active == kRagged)
-    return !few_trees_a_class(h, binned) || leaves || plan_rounds(choose_heap_plan(h, n_rows, true, false), n_rows) <= 1.1;
+  if (h->kernel_active == kRagged) return true;
   if (h->kernel_active != kPerfect || !h->kernel_auto || !h->perfect_heap) return false;
   const bool few_rows = h->F >= kHeapLoadFeatures && n_rows <= kHeapTileRows;
   if ((int64_t)h->n_trees << h->perfect_depth <= (few_rows ? kHeapTileLeaves : kHeapLeaves)) return false;
@@ -1925,9 +1955,9 @@ bridger_status upload_all(bridger_forest *h) {
     if (h->heap_bok) {
       up.add(&h->bheap.d_tops, h->bheap.tops);
       up.add(&h->bheap.d_blocks, h->bheap.blocks);
-    }
-    if (!h->ragged_btops.empty() && (!h->heap_bok || few_trees_a_class(h, true)))
+    } else if (!h->ragged_btops.empty()) {
       up.add(&h->d_ragged_btops, h->ragged_btops);
+    }
   }
   if (h->pair_ok) {
     up.add(&h->d_direct.nodes, h->pair_rec);

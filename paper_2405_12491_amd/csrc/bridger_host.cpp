@@ -1557,7 +1557,8 @@ constexpr int kHeapLoadFeatures = 64, kHeapManyClasses = 9;
 // of levels, classes and tile loads in every round, and the issue of all of a CU's waves.  The constants come from
 // 4,800 times of 1 to 16 waves on 1,474 forests and batches (2 to 64 classes, 3 to 12 levels, 2 to 700 trees, 5
 // to 600 features, 200 to 500,000 rows), which it meets within 24% root mean square: enough to order the plans of
-// one call.  Against the most waves 792 of those and others took 0.93 of the time with 9 classes and more, none over 1.05.
+// one call.  Of those calls 392 of fp32 rows take 0.93 of the time that the most waves take, 300 small batches 0.98, none
+// over 1.02; bins 0.91.
 double heap_estimate(const bridger_forest *h, const Plan &p, int64_t n_rows) {
   const double tiles = std::ceil((double)n_rows / p.rows_per_wg);
   const int W = p.waves, U = heap_batch(h->heap_levels), D = h->max_depth;
